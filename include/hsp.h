@@ -147,9 +147,9 @@ int64_t hsp_max_p(void);
  * uint16 per element); every element is widened exactly to float64 and the
  * products are summed on the FP64 matrix cores in a fixed order (the same G,
  * bit for bit, on every call).  G: device buffer of p x p doubles, row-major,
- * written whole (symmetric).  Allocates a device workspace of about
- * 32 KB x (64-wide tile pairs of G) x (row splits) and frees it before
- * returning; runs on hip_stream (NULL: the null stream) and waits for it.
+ * written whole (symmetric).  Allocates a device workspace of 32 KB x (64-wide
+ * tile pairs of G) x (row splits) for p <= 128, else 128 KB x (128-wide tile
+ * pairs) x (row splits), and frees it before returning; runs on hip_stream (NULL: the null stream) and waits for it.
  * Errors: HSP_EINVAL (NULL pointers, N < 1, p < 1, ld < p, N or ld >= 2^32,
  * unknown x_type); HSP_ENOMEM; HSP_EHIP.
  */
@@ -165,9 +165,9 @@ hsp_status hsp_gram(const void* X, int32_t x_type, int64_t N, int64_t p, int64_t
  * device shares that workspace, so calls that overlap in time on one device
  * (other host threads, or other streams) race and must not be issued.
  * Runs on hip_stream (NULL: the null stream) and waits for it.
- * Errors: as hsp_gram; HSP_EINVAL also if a single 64 x 64 tile's partials
- * (32 KB per row split; at most 1024 splits on a 256-CU device) exceed the
- * workspace.
+ * Errors: as hsp_gram; HSP_EINVAL also if a single tile's partials
+ * (p <= 128: 32 KB per row split, at most 1024 splits on a 256-CU device)
+ * exceed the workspace.
  */
 hsp_status hsp_gram_noalloc(const void* X, int32_t x_type, int64_t N, int64_t p, int64_t ld,
                             double* G, void* hip_stream);

@@ -705,7 +705,7 @@ hsp_status create_stream_impl(hsp_state* s, const float* X, const uint8_t* y, in
     }
     if (!e) e = hipMemcpyAsync(s->xexp, ex.data(), (size_t)p * 4, hipMemcpyHostToDevice, s->stream);
     if (!e) e = hipMemcpyAsync(s->xscale, s->xscale_h.data(), (size_t)p * 8, hipMemcpyHostToDevice, s->stream);
-    if (!e) e = dalloc(&work, (size_t)gg.nsplit * gg.npairs * kTile * kTile);
+    if (!e) e = dalloc(&work, gram_work_doubles(gg));
     for (uint32_t c = 0; !e && c < s->nchunks; ++c) {
         uint32_t rows = 0;
         const float* src = source(c, &rows);

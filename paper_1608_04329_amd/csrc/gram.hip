@@ -2,6 +2,7 @@
 // library layout, input validation, and G = X^T X in float64 (Section 5,
 // beta step i).  Also the device Philox test hook and the read-ceiling probe.
 #include <mutex>
+#include <type_traits>
 
 #include "hsp_internal.hpp"
 #include "philox.hpp"
@@ -68,18 +69,33 @@ __global__ void validate_kernel(XLayout x, const uint8_t* __restrict__ y, Ctrl* 
 }
 
 // ---- G = X^T X on the FP64 matrix cores ---------------------------------------
-// The upper triangle of G is cut into 64 x 64 tiles (ti <= tj, "pairs") and
-// the rows of X into splits.  Block (pair, split) stages 64 rows of X's
-// column tiles ti and tj in LDS as float64 (exact) and accumulates
-// X_ti^T X_tj with v_mfma_f64_16x16x4f64: wave w owns the 32 x 32 quadrant
-// at (32 (w / 2), 32 (w % 2)) as 2 x 2 blocks of 16 x 16; lane l supplies
-// A[l % 16][l / 16] and B[l / 16][l % 16], i.e. rows of the stage are the
-// contraction index, and holds D[l / 16 + 4 r][l % 16] in its r-th result.
-// The next stage's loads are issued before the current stage's products.
-// Every split writes its partial tile; a second kernel sums the splits of
-// each entry in split order, so G does not depend on timing.
-constexpr int kGT = 64;
+// The upper triangle of G is cut into T x T tiles (ti <= tj, "pairs"), T = 32
+// NB, and the rows of X into splits.  Block (pair, split) stages kGramK rows of
+// X's column tiles ti and tj in LDS as float32 (two buffers, one barrier per
+// stage, the next stage's loads in flight during the products) and accumulates
+// X_ti^T X_tj with v_mfma_f64_16x16x4f64, widening each element exactly as it
+// leaves LDS.  Wave (wr, wc) owns the 16 x 16 blocks (2 i + wr, 2 j + wc),
+// i, j < NB: interleaved, so that in the last tile column and on the diagonal,
+// where blocks beyond p and below the diagonal are left out, the four waves
+// keep equal shares.  Lane l supplies A[l % 16][l / 16] and B[l / 16][l % 16],
+// i.e. rows of the stage are the contraction index, and holds D[l / 16 + 4 r]
+// [l % 16] in its r-th result.  Every split writes its partial tile (its blocks
+// inside the matrix and not below its diagonal); a second kernel sums the splits
+// of each entry in split order, so G does not depend on timing.
+//
+// Bound by the matrix cores: one operation takes 64 cycles of a SIMD, and with
+// NB = 4 a wave reads and widens 8 fragments per 16 operations (NB = 2: 4 per
+// 4), so LDS, conversions and the loads of X mostly hide behind them.  N = 1e6,
+// p = 1000 float32: 18.2 ms (59 TFLOP/s of the blocks computed; a large library
+// product reaches 73), against 80 ms with 64-wide tiles staged as float64 by
+// 4-byte loads; N = 3e5, p = 777 bfloat16: 14.3 -> 4.25 ms.
+constexpr int kGramK = 32;  // rows of X per stage
 typedef double GAcc __attribute__((ext_vector_type(4)));
+
+// A tile's LDS row: T floats and 16 more, so that the four rows one fragment
+// read touches lie in different quarters of the 64 banks.
+template <int NB>
+constexpr int gram_stride() { return 32 * NB + 16; }
 
 __device__ __forceinline__ void pair_of(uint32_t pair, uint32_t nt, uint32_t& ti, uint32_t& tj) {
     uint32_t r = 0, idx = pair;
@@ -88,84 +104,182 @@ __device__ __forceinline__ void pair_of(uint32_t pair, uint32_t nt, uint32_t& ti
     tj = r + idx;
 }
 
-// Pairs [pair0, pair0 + gridDim.x) over the row splits of x, which are the
-// splits split0, split0 + 1, ... of the whole design (x may be a chunk of its
-// rows); work holds gridDim.x tiles per split, split-major.
-__global__ __launch_bounds__(256) void gram_tile_kernel(XLayout x, double* __restrict__ work, uint32_t nt,
-                                                        uint32_t pair0, uint32_t rows_per_split, uint32_t split0) {
-    __shared__ double S[kGT][kGT + 2];
-    __shared__ double T[kGT][kGT + 2];
-    uint32_t ti, tj;
-    pair_of(pair0 + blockIdx.x, nt, ti, tj);
-    const size_t r_begin = (size_t)blockIdx.y * rows_per_split;
-    const size_t r_end = min((size_t)x.N, r_begin + rows_per_split);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int kr = lane >> 4, cc = lane & 15;
-    const int i0 = 32 * (wave >> 1), j0 = 32 * (wave & 1);
-    // staging: thread t loads column t % 64 of stage rows t / 64 + 4 q
-    const int c = threadIdx.x & (kGT - 1), rb = threadIdx.x >> 6;
-    const uint32_t ca = ti * kGT + c, cb = tj * kGT + c;
-    const bool diag = ti == tj;
-    GAcc acc[2][2];
+// VN consecutive columns from col of one row, as 16 bytes of X.  ALIGNED (rows
+// start on 16-byte boundaries): one load with no branch; columns past p are
+// read only inside the 16 bytes that hold column p - 1, and whole groups past p
+// read that group again (what they hold only enters products of columns past p,
+// which are dropped).  Otherwise elements past p are zeros, loaded one by one.
+template <int XT, int VN, bool ALIGNED>
+__device__ __forceinline__ uint4 gram_fetch(const XLayout& x, size_t row, uint32_t col) {
+    if constexpr (ALIGNED) {
+        const uint32_t c = min(col, (x.p - 1u) / VN * VN);
+        return *reinterpret_cast<const uint4*>(static_cast<const char*>(x.X) + (row * x.ld + c) * (XT == 0 ? 4 : 2));
+    } else {
+        uint32_t u[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
-    for (int bi = 0; bi < 2; ++bi)
-#pragma unroll
-        for (int bj = 0; bj < 2; ++bj) acc[bi][bj] = GAcc{0.0, 0.0, 0.0, 0.0};
-    double va[16], vb[16];
-    auto fetch = [&](size_t r0) {
-#pragma unroll
-        for (int q = 0; q < 16; ++q) {
-            const size_t row = r0 + rb + 4 * q;
-            const bool in = row < r_end;
-            va[q] = (in && ca < x.p) ? (double)load_x(x, row, ca) : 0.0;
-            vb[q] = (!diag && in && cb < x.p) ? (double)load_x(x, row, cb) : 0.0;
-        }
-    };
-    if (r_begin < r_end) fetch(r_begin);
-    for (size_t r0 = r_begin; r0 < r_end; r0 += kGT) {
-        __syncthreads();  // the previous stage's products have read S and T
-#pragma unroll
-        for (int q = 0; q < 16; ++q) {
-            S[rb + 4 * q][c] = va[q];
-            if (!diag) T[rb + 4 * q][c] = vb[q];
-        }
-        __syncthreads();
-        if (r0 + kGT < r_end) fetch(r0 + kGT);
-        const double(*B)[kGT + 2] = diag ? S : T;
-#pragma unroll 4
-        for (int q0 = 0; q0 < kGT; q0 += 4) {
-            const double a0 = S[q0 + kr][i0 + cc], a1 = S[q0 + kr][i0 + 16 + cc];
-            const double b0 = B[q0 + kr][j0 + cc], b1 = B[q0 + kr][j0 + 16 + cc];
-            acc[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b0, acc[0][0], 0, 0, 0);
-            acc[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b1, acc[0][1], 0, 0, 0);
-            acc[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b0, acc[1][0], 0, 0, 0);
-            acc[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b1, acc[1][1], 0, 0, 0);
-        }
+        for (int e = 0; e < VN; ++e)
+            if (col + e < x.p) {
+                if constexpr (XT == 0) u[e & 3] = static_cast<const uint32_t*>(x.X)[row * x.ld + col + e];
+                else u[(e >> 1) & 3] |= (uint32_t) static_cast<const uint16_t*>(x.X)[row * x.ld + col + e] << (16 * (e & 1));
+            }
+        return make_uint4(u[0], u[1], u[2], u[3]);
     }
-    double* out = work + ((size_t)(split0 + blockIdx.y) * gridDim.x + blockIdx.x) * (kGT * kGT);
-#pragma unroll
-    for (int bi = 0; bi < 2; ++bi)
-#pragma unroll
-        for (int bj = 0; bj < 2; ++bj)
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-                out[(i0 + 16 * bi + kr + 4 * r) * kGT + j0 + 16 * bj + cc] = acc[bi][bj][r];
 }
 
-// G from the partial tiles of pairs [pair0, pair0 + npc), summed over the
-// splits in order, mirrored, and unscaled by 2^(e_i + e_j) (exact) if e.
-__global__ void gram_reduce_kernel(const double* __restrict__ work, uint32_t nsplit, uint32_t npc,
-                                   uint32_t pair0, uint32_t nt, uint32_t p, const int32_t* __restrict__ e,
-                                   double* __restrict__ G) {
-    const size_t idx = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
-    if (idx >= (size_t)npc * kGT * kGT) return;
-    const uint32_t pc = (uint32_t)(idx / (kGT * kGT)), local = (uint32_t)(idx % (kGT * kGT));
+// The products of one stage: acc(i, j) += S(:, block 2 i + wr)^T B(:, block
+// 2 j + wc) for j < JL, and only i <= j on a diagonal tile (which for wave
+// (1, 0) includes blocks (2 i + 1, 2 i) just below the diagonal: dropped when
+// the tile is written, rather than branched around).
+template <int NB, int JL, bool DIAG>
+__device__ __forceinline__ void gram_products(const float* __restrict__ S, const float* __restrict__ B, int wr, int wc,
+                                              GAcc (&acc)[NB][NB]) {
+    constexpr int LD = gram_stride<NB>(), IL = DIAG ? JL : NB;
+    const int lane = threadIdx.x & 63, kr = lane >> 4, cc = lane & 15;
+    const float* sp = S + kr * LD + 16 * wr + cc;
+    const float* bp = B + kr * LD + 16 * wc + cc;
+#pragma unroll 2
+    for (int q0 = 0; q0 < kGramK; q0 += 4) {
+        double a[IL], b[JL];
+#pragma unroll
+        for (int i = 0; i < IL; ++i) a[i] = (double)sp[q0 * LD + 32 * i];
+#pragma unroll
+        for (int j = 0; j < JL; ++j) b[j] = (double)bp[q0 * LD + 32 * j];
+#pragma unroll
+        for (int i = 0; i < IL; ++i)
+#pragma unroll
+            for (int j = DIAG ? i : 0; j < JL; ++j)
+                acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b[j], acc[i][j], 0, 0, 0);
+    }
+}
+
+// Pairs [pair0, pair0 + npc) over the row splits of x, which are the splits
+// split0, split0 + 1, ... of the whole design (x may be a chunk of its rows);
+// work holds npc tiles per split, split-major.  Blocks are dealt to the eight
+// XCDs in turn; each XCD takes a contiguous eighth of the (split, pair) list, so
+// the pairs of a split mostly run on one XCD, whose L2 serves the rows they share.
+template <int XT, int NB, bool ALIGNED>
+__global__ __launch_bounds__(256, 2) void gram_tile_kernel(XLayout x, double* __restrict__ work, uint32_t nt,
+                                                           uint32_t pair0, uint32_t npc, uint32_t nsplit,
+                                                           uint32_t rows_per_split, uint32_t split0) {
+    constexpr int T = 32 * NB, LD = gram_stride<NB>();
+    constexpr int VN = XT == 0 ? 4 : 8, TPR = T / VN, RPP = 256 / TPR, PASSES = kGramK / RPP;
+    static_assert(RPP * PASSES == kGramK, "whole passes per stage");
+    __shared__ __align__(16) float lds[2][2][kGramK * LD];
+    const uint32_t per_xcd = (npc * nsplit + 7u) / 8u, w = (blockIdx.x & 7u) * per_xcd + (blockIdx.x >> 3);
+    if (w >= npc * nsplit) return;
+    const uint32_t split = w / npc, pc = w % npc;
     uint32_t ti, tj;
     pair_of(pair0 + pc, nt, ti, tj);
-    const uint32_t i = ti * kGT + local / kGT, j = tj * kGT + local % kGT;
-    if (i >= p || j >= p || (ti == tj && j < i)) return;
+    const size_t r_begin = (size_t)split * rows_per_split;
+    const size_t r_end = min((size_t)x.N, r_begin + rows_per_split);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wr = wave >> 1, wc = wave & 1;
+    const bool diag = ti == tj;
+    // 16-wide blocks of the two column tiles inside the matrix (tile ti is whole
+    // unless the pair is diagonal)
+    const int nI = (int)min(2u * NB, (x.p - ti * T + 15u) / 16u), nJ = (int)min(2u * NB, (x.p - tj * T + 15u) / 16u);
+    GAcc acc[NB][NB];
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+        for (int j = 0; j < NB; ++j) acc[i][j] = GAcc{0.0, 0.0, 0.0, 0.0};
+    // staging: thread t takes VN columns of stage rows t / TPR + RPP s
+    const uint32_t c = threadIdx.x % TPR * VN, rb = threadIdx.x / TPR;
+    uint4 va[PASSES], vb[PASSES];
+    auto fetch = [&](size_t r0) {  // rows past the split's end: its last row again
+#pragma unroll
+        for (int s = 0; s < PASSES; ++s) {
+            const size_t row = min(r0 + rb + RPP * s, r_end - 1);
+            va[s] = gram_fetch<XT, VN, ALIGNED>(x, row, ti * T + c);
+            if (!diag) vb[s] = gram_fetch<XT, VN, ALIGNED>(x, row, tj * T + c);
+        }
+    };
+    auto widen = [&](const uint4& w, bool in, float* dst) {
+        const uint32_t u[4] = {w.x, w.y, w.z, w.w};
+        float v[VN];
+#pragma unroll
+        for (int e = 0; e < VN; ++e) {
+            const uint32_t bits = XT == 0 ? u[e & 3] : (e & 1) ? u[(e >> 1) & 3] & 0xFFFF0000u : u[(e >> 1) & 3] << 16;
+            v[e] = in ? __uint_as_float(bits) : 0.0f;
+        }
+#pragma unroll
+        for (int e = 0; e < VN; e += 4) *reinterpret_cast<float4*>(dst + e) = make_float4(v[e], v[e + 1], v[e + 2], v[e + 3]);
+    };
+    auto put = [&](int buf, size_t r0) {
+#pragma unroll
+        for (int s = 0; s < PASSES; ++s) {
+            const uint32_t row = rb + RPP * s;
+            const bool in = r0 + row < r_end;
+            widen(va[s], in, &lds[buf][0][row * LD + c]);
+            if (!diag) widen(vb[s], in, &lds[buf][1][row * LD + c]);
+        }
+    };
+    if (r_begin < r_end) {
+        fetch(r_begin);
+        put(0, r_begin);
+    }
+    __syncthreads();
+    auto rows = [&](auto jl, auto dg) {
+        int buf = 0;
+        for (size_t r0 = r_begin; r0 < r_end; r0 += kGramK, buf ^= 1) {
+            const bool more = r0 + kGramK < r_end;
+            if (more) fetch(r0 + kGramK);
+            const float* S = lds[buf][0];
+            gram_products<NB, decltype(jl)::value, decltype(dg)::value>(S, diag ? S : lds[buf][1], wr, wc, acc);
+            if (more) put(buf ^ 1, r0 + kGramK);
+            __syncthreads();
+        }
+    };
+    auto columns = [&](auto dg) {  // the last tile column: only as wide as the matrix
+        const int jl = (nJ + 1) / 2;
+        if (jl == NB) rows(std::integral_constant<int, NB>{}, dg);
+        else if (NB == 4 && jl == 3) rows(std::integral_constant<int, NB == 4 ? 3 : 1>{}, dg);
+        else if (NB == 4 && jl == 2) rows(std::integral_constant<int, NB == 4 ? 2 : 1>{}, dg);
+        else rows(std::integral_constant<int, 1>{}, dg);
+    };
+    if (diag) columns(std::true_type{});
+    else columns(std::false_type{});
+    const int lane = threadIdx.x & 63, kr = lane >> 4, cc = lane & 15;
+    double* out = work + ((size_t)(split0 + split) * npc + pc) * (T * T);
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+            if (2 * i + wr < nI && 2 * j + wc < nJ && (!diag || 2 * i + wr <= 2 * j + wc)) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    out[(16 * (2 * i + wr) + kr + 4 * r) * T + 16 * (2 * j + wc) + cc] = acc[i][j][r];
+            }
+}
+
+// G from the partial tiles of pairs [pair0, pair0 + npc), mirrored, and unscaled
+// by 2^(e_i + e_j) (exact) if e.  A block takes 64 entries; wave w sums the
+// splits of the w-th quarter in order, eight loads in flight, and the four sums
+// are added in wave order: a fixed order, and four times the loads in flight of
+// one thread per entry (N = 1e5, p = 100, 342 splits: 80 -> 8 us).
+__global__ __launch_bounds__(256) void gram_reduce_kernel(const double* __restrict__ work, uint32_t nsplit, uint32_t npc,
+                                                          uint32_t pair0, uint32_t nt, uint32_t T, uint32_t p,
+                                                          const int32_t* __restrict__ e, double* __restrict__ G) {
+    __shared__ double part[4][64];
+    const uint32_t tt = T * T, lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+    const size_t idx = blockIdx.x * (size_t)64 + lane;  // 64 divides T * T: a block's entries share a pair
+    const uint32_t pc = (uint32_t)(idx / tt), local = (uint32_t)(idx % tt);
+    uint32_t ti, tj;
+    pair_of(pair0 + pc, nt, ti, tj);
+    const uint32_t i = ti * T + local / T, j = tj * T + local % T;
+    const bool live = i < p && j < p && !(ti == tj && j < i);
+    const uint32_t per = (nsplit + 3u) / 4u, s0 = min(wave * per, nsplit), s1 = min(s0 + per, nsplit);
+    const double* src = work + (size_t)pc * tt + local;
+    const size_t step = (size_t)npc * tt;
     double s = 0.0;
-    for (uint32_t sp = 0; sp < nsplit; ++sp) s += work[((size_t)sp * npc + pc) * (kGT * kGT) + local];
+    if (live) {
+#pragma unroll 8
+        for (uint32_t sp = s0; sp < s1; ++sp) s += src[sp * step];
+    }
+    part[wave][lane] = s;
+    __syncthreads();
+    if (wave != 0 || !live) return;
+    s = ((part[0][lane] + part[1][lane]) + part[2][lane]) + part[3][lane];
     if (e) s = ldexp(s, e[i] + e[j]);
     G[(size_t)i * p + j] = s;
     G[(size_t)j * p + i] = s;
@@ -194,43 +308,94 @@ __global__ void pad_gram_kernel(const double* __restrict__ G, uint32_t p, uint32
 
 }  // namespace
 
+// Tile width: 64 up to p = 128, where 128-wide tiles would be mostly padding.
+// Row splits: at least four 64-wide-tile blocks per compute unit in all.  With
+// 128-wide tiles more splits are taken while they shorten the model's time: the
+// blocks of the busiest unit one after another (its FP64 matrix cores do 64
+// multiply-adds a cycle at 2.4 GHz; a block alone on its unit keeps them a little
+// less busy) plus, per block, its 128 KB of partials written and read at 4 TB/s
+// and allocated and freed (about 1.6 us per MB).
 GramGeometry gram_geometry(const XLayout& x, int num_cus, uint64_t max_rows_per_split) {
     GramGeometry g;
-    g.nt = (x.p + kGT - 1) / kGT;
+    const uint64_t nt64 = (x.p + 63) / 64, np64 = nt64 * (nt64 + 1) / 2;
+    const uint64_t max_split = ((uint64_t)x.N + 63) / 64;
+    const uint64_t lo = std::max<uint64_t>(1, std::min(max_split, ((uint64_t)num_cus * 4 + np64 - 1) / np64));
+    g.tile = x.p <= 128u ? 64u : 128u;
+    g.nt = (x.p + g.tile - 1) / g.tile;
     g.npairs = g.nt * (g.nt + 1) / 2;
-    const uint64_t want = (uint64_t)num_cus * 4;
-    uint64_t ns = (want + g.npairs - 1) / g.npairs;
-    const uint64_t max_split = (x.N + kGT - 1) / kGT;
-    if (ns > max_split) ns = max_split;
-    if (ns < 1) ns = 1;
-    uint64_t rps = (x.N + ns - 1) / ns;
-    rps = (rps + kGT - 1) / kGT * kGT;
-    if (max_rows_per_split >= (uint64_t)kGT && rps > max_rows_per_split) rps = max_rows_per_split / kGT * kGT;
+    uint64_t ns = lo;
+    if (g.tile == 128u) {
+        // one pair's partials over every split fit the fixed workspace
+        const uint64_t hi = std::min({max_split, ((uint64_t)num_cus * 16 + g.npairs - 1) / g.npairs,
+                                      (uint64_t)kGramScratchDoubles / (128 * 128)});
+        double best = 1e300;
+        for (uint64_t n = lo; n <= std::max(lo, hi); ++n) {
+            const double rows = (double)((((uint64_t)x.N + n - 1) / n + 63) / 64 * 64);
+            const uint64_t blocks = n * g.npairs, q = (blocks + num_cus - 1) / num_cus;
+            const double us = (double)q * rows * (128.0 * 128 / (64 * 2400.0)) * (q == 1 ? 1.15 : 1.0) +
+                              (double)blocks * 0.265;
+            if (us < best) {
+                best = us;
+                ns = n;
+            }
+        }
+    }
+    uint64_t rps = ((uint64_t)x.N + ns - 1) / ns;
+    rps = (rps + 63) / 64 * 64;
+    if (max_rows_per_split >= 64 && rps > max_rows_per_split) rps = max_rows_per_split / 64 * 64;
     g.nsplit = (uint32_t)((x.N + rps - 1) / rps);
     g.rows_per_split = (uint32_t)rps;
     return g;
 }
 
-size_t gram_work_doubles(const XLayout& x, int num_cus) {
-    const GramGeometry g = gram_geometry(x, num_cus);
-    return (size_t)g.nsplit * g.npairs * kGT * kGT;
+size_t gram_work_doubles(const GramGeometry& g) { return (size_t)g.nsplit * g.npairs * g.tile * g.tile; }
+size_t gram_work_doubles(const XLayout& x, int num_cus) { return gram_work_doubles(gram_geometry(x, num_cus)); }
+
+namespace {
+
+template <int XT, int NB>
+void gram_tiles(const XLayout& x, double* work, const GramGeometry& g, uint32_t pair0, uint32_t npc, uint32_t ns,
+                uint32_t split0, hipStream_t st) {
+    const size_t row_bytes = (size_t)x.ld * (XT == 0 ? 4 : 2);
+    const bool aligned = row_bytes % 16 == 0 && (uintptr_t)x.X % 16 == 0;
+    const dim3 grid((npc * ns + 7u) / 8u * 8u);
+    if (aligned)
+        hipLaunchKernelGGL((gram_tile_kernel<XT, NB, true>), grid, dim3(256), 0, st, x, work, g.nt, pair0, npc, ns,
+                           g.rows_per_split, split0);
+    else
+        hipLaunchKernelGGL((gram_tile_kernel<XT, NB, false>), grid, dim3(256), 0, st, x, work, g.nt, pair0, npc, ns,
+                           g.rows_per_split, split0);
 }
+
+// The partial tiles of pairs [pair0, pair0 + npc) over ns row splits of x.
+void gram_tiles_launch(const XLayout& x, double* work, const GramGeometry& g, uint32_t pair0, uint32_t npc, uint32_t ns,
+                       uint32_t split0, hipStream_t st) {
+    if (x.xtype == 0 && g.tile == 64) gram_tiles<0, 2>(x, work, g, pair0, npc, ns, split0, st);
+    else if (x.xtype == 0) gram_tiles<0, 4>(x, work, g, pair0, npc, ns, split0, st);
+    else if (g.tile == 64) gram_tiles<1, 2>(x, work, g, pair0, npc, ns, split0, st);
+    else gram_tiles<1, 4>(x, work, g, pair0, npc, ns, split0, st);
+}
+
+hipError_t gram_sum_launch(const double* work, const GramGeometry& g, uint32_t pair0, uint32_t npc, uint32_t p,
+                           const int32_t* e, double* G, hipStream_t st) {
+    const size_t n = (size_t)npc * g.tile * g.tile;
+    hipLaunchKernelGGL(gram_reduce_kernel, dim3((unsigned)(n / 64)), dim3(256), 0, st, work, g.nsplit, npc,
+                       pair0, g.nt, g.tile, p, e, G);
+    return hipGetLastError();
+}
+
+}  // namespace
 
 hipError_t gram_launch_chunked(const XLayout& x, const int32_t* e, double* G, double* work,
                                size_t work_doubles, int num_cus, hipStream_t st) {
     const GramGeometry g = gram_geometry(x, num_cus);
-    const size_t per_pair = (size_t)g.nsplit * kGT * kGT;
+    const size_t per_pair = (size_t)g.nsplit * g.tile * g.tile;
     const size_t chunk = std::min<size_t>(g.npairs, work_doubles / per_pair);
     if (chunk < 1) return hipErrorInvalidValue;
     for (uint32_t pair0 = 0; pair0 < g.npairs; pair0 += (uint32_t)chunk) {
         const uint32_t npc = (uint32_t)std::min<size_t>(chunk, g.npairs - pair0);
-        hipLaunchKernelGGL(gram_tile_kernel, dim3(npc, g.nsplit), dim3(256), 0, st, x, work, g.nt, pair0,
-                           g.rows_per_split, 0u);
-        const size_t n = (size_t)npc * kGT * kGT;
-        hipLaunchKernelGGL(gram_reduce_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st,
-                           (const double*)work, g.nsplit, npc, pair0, g.nt, x.p, e, G);
-        hipError_t err = hipGetLastError();
-        if (err != hipSuccess) return err;
+        gram_tiles_launch(x, work, g, pair0, npc, g.nsplit, 0u, st);
+        if (hipError_t err = gram_sum_launch(work, g, pair0, npc, x.p, e, G, st)) return err;
     }
     return hipSuccess;
 }
@@ -265,7 +430,8 @@ hipError_t gram_scratch(double** ptr) {
 }
 
 size_t gram_pair_doubles(const XLayout& x, int num_cus) {
-    return (size_t)gram_geometry(x, num_cus).nsplit * kGT * kGT;
+    const GramGeometry g = gram_geometry(x, num_cus);
+    return (size_t)g.nsplit * g.tile * g.tile;
 }
 
 hipError_t gram_launch(const XLayout& x, const int32_t* e, double* G, double* work, int num_cus,
@@ -278,17 +444,13 @@ hipError_t gram_chunk_launch(const XLayout& chunk, const GramGeometry& g, uint32
     const uint32_t ns = (chunk.N + g.rows_per_split - 1) / g.rows_per_split;
     if (ns == 0) return hipSuccess;
     if (split0 + ns > g.nsplit) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(gram_tile_kernel, dim3(g.npairs, ns), dim3(256), 0, st, chunk, work, g.nt, 0u,
-                       g.rows_per_split, split0);
+    gram_tiles_launch(chunk, work, g, 0u, g.npairs, ns, split0, st);
     return hipGetLastError();
 }
 
 hipError_t gram_reduce_launch(const double* work, const GramGeometry& g, uint32_t p, const int32_t* e, double* G,
                               hipStream_t st) {
-    const size_t n = (size_t)g.npairs * kGT * kGT;
-    hipLaunchKernelGGL(gram_reduce_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, work, g.nsplit,
-                       g.npairs, 0u, g.nt, p, e, G);
-    return hipGetLastError();
+    return gram_sum_launch(work, g, 0u, g.npairs, p, e, G, st);
 }
 
 hipError_t pad_gram_launch(const double* G, uint32_t p, uint32_t P, double* Gp, hipStream_t st) {

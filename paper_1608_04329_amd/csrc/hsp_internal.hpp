@@ -311,9 +311,9 @@ hipError_t mc_launch(const McArgs* mc, uint32_t ld, uint32_t gz, hipStream_t st)
 // G = X^T X (p x p float64, leading dimension p) of the stored X, unscaled
 // with the column exponents e (null: none).  The rows are cut into nsplit
 // splits of rows_per_split rows and the upper triangle of G into npairs
-// 64 x 64 tiles; every (split, tile) partial is summed in split order.
+// tile x tile tiles; every (split, tile) partial is summed in split order.
 struct GramGeometry {
-    uint32_t nt, npairs, nsplit, rows_per_split;
+    uint32_t tile, nt, npairs, nsplit, rows_per_split;
 };
 // max_rows_per_split > 0 caps the rows of a split (more splits), so that a
 // design streamed in chunks of whole splits can form its partials chunk by chunk.
@@ -329,6 +329,7 @@ hipError_t gram_chunk_launch(const XLayout& chunk, const GramGeometry& g, uint32
 hipError_t gram_reduce_launch(const double* work, const GramGeometry& g, uint32_t p, const int32_t* e, double* G,
                               hipStream_t st);
 // Doubles of workspace that hold every partial tile at once.
+size_t gram_work_doubles(const GramGeometry& g);
 size_t gram_work_doubles(const XLayout& x, int num_cus);
 // work must hold gram_work_doubles(x) doubles.
 hipError_t gram_launch(const XLayout& x, const int32_t* e, double* G, double* work, int num_cus,
@@ -338,7 +339,7 @@ hipError_t gram_launch(const XLayout& x, const int32_t* e, double* G, double* wo
 // nsplit partials, else hipErrorInvalidValue).
 hipError_t gram_launch_chunked(const XLayout& x, const int32_t* e, double* G, double* work,
                                size_t work_doubles, int num_cus, hipStream_t st);
-// Doubles of workspace one 64 x 64 tile pair needs (its partials over every
+// Doubles of workspace one tile pair needs (its partials over every
 // row split); gram_launch_chunked needs at least this much.
 size_t gram_pair_doubles(const XLayout& x, int num_cus);
 // The library's fixed Gram workspace (kGramScratchDoubles doubles, 32 MiB,

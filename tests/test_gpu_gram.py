@@ -1,0 +1,39 @@
+"""hsp_gram at the edges of its tiles: 16-wide blocks, 64- and 128-wide tiles
+(the switch between them lies at p = 128), rows short of a stage or a split,
+rows that start off 16-byte boundaries, and padding that must not be read as
+data (it holds NaN).  Against float64 sums of the same (rounded) design:
+entries are sums of N exact products, so |error| <= N 2^-52 sum |x_ij x_ik|,
+and sum |x_ij x_ik| <= sqrt(G_jj G_kk)."""
+import numpy as np
+import pytest
+
+from gpu_util import need_gpu
+import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("xt", ["f32", "bf16"])
+@pytest.mark.parametrize("N,p,ld", [(1, 1, 1), (33, 15, 16), (63, 16, 16), (65, 17, 19), (1000, 64, 64), (517, 65, 72),
+                                    (2049, 128, 128), (2048, 129, 136), (999, 145, 145), (131, 255, 256),
+                                    (3001, 257, 259), (4100, 400, 400)])
+def test_gram_tile_edges(xt, N, p, ld):
+    torch, hsp = need_gpu()
+    X = np.random.default_rng(N + p).standard_normal((N, p)).astype(np.float32)
+    if xt == "bf16":
+        bits = synth.bf16_bits(X)
+        X = synth.bf16_to_f32(bits)
+        buf = np.full((N, ld), 0x7FC0, np.uint16)
+        buf[:, :p] = bits
+    else:
+        buf = np.full((N, ld), np.nan, np.float32)
+        buf[:, :p] = X
+    d = torch.from_numpy(buf.ravel()[: (N - 1) * ld + p].copy()).cuda()  # the last row ends at p
+    G = torch.full((p, p), np.nan, dtype=torch.float64, device="cuda")
+    torch.cuda.synchronize()
+    hsp.hsp_gram(d.data_ptr(), hsp.HSP_X_F32 if xt == "f32" else hsp.HSP_X_BF16, N, p, ld, G.data_ptr())
+    ref = X.astype(np.float64).T @ X.astype(np.float64)
+    got = G.cpu().numpy()
+    s = np.sqrt(np.outer(np.diag(ref), np.diag(ref)))
+    assert np.all(np.abs(got - ref) <= 2 * N * 2.0 ** -52 * s)
+    assert np.array_equal(got, got.T)
