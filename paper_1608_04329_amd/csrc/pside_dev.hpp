@@ -311,7 +311,7 @@ constexpr uint32_t kSmallBOff = 512;
 static_assert(kSmallP * (kSmallP + 1) / 2 <= (int)kSmallBOff && kSmallBOff + kSmallP <= (uint32_t)kLdsDoubles,
               "one-block path LDS layout");
 
-__device__ void small_path(Args& a, Group& g, uint32_t k, double* lds) {
+__device__ __forceinline__ void small_path(Args& a, Group& g, uint32_t k, double* lds) {
     const uint32_t p = a.x.p;
     const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
     double tau = hyper_lambda_tau(a, k, true, lds);
@@ -476,8 +476,7 @@ struct MAcc {
     Acc4 v[2][2];
 };
 
-// acc = S^T T, or S T when TA (S read transposed: its rows are the product's rows).
-template <bool TA = false>
+// acc = S^T T
 __device__ __forceinline__ void gemm_tn(const Tile& S, const Tile& T, MAcc& acc) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int i0 = 32 * (wave >> 1), j0 = 32 * (wave & 1);
@@ -488,8 +487,7 @@ __device__ __forceinline__ void gemm_tn(const Tile& S, const Tile& T, MAcc& acc)
         for (int bj = 0; bj < 2; ++bj) acc.v[bi][bj] = Acc4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll 4
     for (int q0 = 0; q0 < kTile; q0 += 4) {
-        const double a0 = TA ? S[i0 + cc][q0 + kr] : S[q0 + kr][i0 + cc];
-        const double a1 = TA ? S[i0 + 16 + cc][q0 + kr] : S[q0 + kr][i0 + 16 + cc];
+        const double a0 = S[q0 + kr][i0 + cc], a1 = S[q0 + kr][i0 + 16 + cc];
         const double b0 = T[q0 + kr][j0 + cc], b1 = T[q0 + kr][j0 + 16 + cc];
         acc.v[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b0, acc.v[0][0], 0, 0, 0);
         acc.v[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b1, acc.v[0][1], 0, 0, 0);
@@ -554,24 +552,11 @@ __device__ __forceinline__ void put_tile_m(double* M, uint32_t P, uint32_t r0, u
             for (int r = 0; r < 4; ++r) stc(M + (size_t)(ri + 16 * bi + 4 * r) * P + cj + 16 * bj, out[bi][bj][r]);
 }
 
-// X = old + sign * acc in LDS (the matrix-core layout, X's own rows and columns).
-__device__ __forceinline__ void acc_to_lds(Tile& X, const MAcc& acc, double sign, const MTile& old) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int ri = 32 * (wave >> 1) + (lane >> 4), cj = 32 * (wave & 1) + (lane & 15);
-#pragma unroll
-    for (int bi = 0; bi < 2; ++bi)
-#pragma unroll
-        for (int bj = 0; bj < 2; ++bj)
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-                X[ri + 16 * bi + 4 * r][cj + 16 * bj] = fma(sign, acc.v[bi][bj][r], old.v[bi][bj][r]);
-}
-
-__device__ __forceinline__ double rdlane(double v, int l) {
-    const unsigned long long u = (unsigned long long)__double_as_longlong(v);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, l);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), l);
-    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+// v, or zero, with no branch (a branch around a load or store would make the
+// next one wait for it).
+__device__ __forceinline__ double keep_if(bool keep, double v) {
+    const long long m = keep ? -1ll : 0ll;
+    return __longlong_as_double(__double_as_longlong(v) & m);
 }
 
 // 1 / sqrt(d) for d > 0: the hardware estimate and one Newton step.
@@ -581,112 +566,141 @@ __device__ __forceinline__ double rsqrt_nr(double d) {
     return fma(0.5 * y, e, y);
 }
 
-// Factor a 64 x 64 diagonal block: S holds its upper part (zeros below,
-// identity beyond the matrix edge); on return S = U (upper) and T = U^-T
-// (lower), i.e. the factorisation of [S | I] by row operations.
+// Lane C of each row of 16 lanes, in every lane of that row.
+template <int C>
+__device__ __forceinline__ double row_bcast(double v) {
+    return __builtin_amdgcn_update_dpp(0.0, v, 0x150 + C, 0xf, 0xf, true);
+}
+// acc -= (lane C of x's row of 16 lanes) * y, in one instruction.  x must have
+// passed settle() since it was written.
+template <int C>
+__device__ __forceinline__ void fmsub_bcast(double& acc, double x, double y) {
+    asm("v_fmac_f64_dpp %0, -%1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(x), "v"(y), "n"(C));
+}
+// The two wait states that a vector write of x needs before its use as the source
+// of a cross-lane operand, where the write or the use is inside fmsub_bcast and
+// the compiler does not see it.
+__device__ __forceinline__ void settle(double& x) { asm("s_nop 1" : "+v"(x)); }
+
+// Pivots C .. 15 of a 16-row panel: d holds the panel's diagonal block (column
+// l % 16 in lane l, a copy in each row of 16 lanes), a the 64 other columns of
+// the panel, one per lane.  Row C is scaled by 1 / sqrt(pivot), then every later
+// row i loses (row C's entry at column i) times row C: the multiplier is lane
+// i's entry of row C's diagonal part, which a row of 16 lanes broadcasts to
+// itself, so each row costs two instructions and no scalar registers.
+template <int C, int I>
+__device__ __forceinline__ void panel_rows(double (&d)[16], double (&a)[16]) {
+    if constexpr (I < 16) {
+        fmsub_bcast<I>(d[I], d[C], d[C]);
+        fmsub_bcast<I>(a[I], d[C], a[C]);
+        panel_rows<C, I + 1>(d, a);
+    }
+}
+template <int C>
+__device__ __forceinline__ void panel_pivots(double (&d)[16], double (&a)[16]) {
+    if constexpr (C < 16) {
+        settle(d[C]);
+        const double rs = rsqrt_nr(row_bcast<C>(d[C]));
+        d[C] *= rs;
+        a[C] *= rs;
+        settle(d[C]);
+        panel_rows<C, C + 1>(d, a);
+        panel_pivots<C + 1>(d, a);
+    }
+}
+
+// One wave eliminates row panel P (16 rows from r0 = 16 P) of [S | T]: the
+// panel's columns are its 16 x 16 diagonal block of S, S's 48 - r0 columns to
+// the right of it and T's first r0 + 16 columns, the last 16 of which start as
+// the identity: 64 columns beside the diagonal block whatever P.  Returns
+// whether every pivot was positive (a failed one leaves NaN in the last).
+__device__ __forceinline__ bool factor_panel(Tile& S, Tile& T, int P) {
+    const int lane = threadIdx.x & 63, r0 = 16 * P, right = 48 - r0;
+    const int tcol = lane - right;  // this lane's column of T, if not negative
+    double* col = tcol < 0 ? &S[r0][r0 + 16 + lane] : &T[r0][tcol];
+    const double* dcol = &S[r0][r0 + (lane & 15)];
+    double d[16], a[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        d[i] = dcol[i * kTileLd];
+        a[i] = col[i * kTileLd];
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) a[i] = tcol < r0 ? a[i] : (tcol - r0 == i ? 1.0 : 0.0);
+    panel_pivots<0>(d, a);
+    if (lane < 16) {
+        double* dw = &S[r0][r0 + lane];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) dw[i * kTileLd] = d[i];  // valid on and above the diagonal
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) col[i * kTileLd] = a[i];
+    return row_bcast<15>(d[15]) > 0.0;
+}
+
+// B(I, J) -= S(P, I)^T B(P, J) on 16 x 16 blocks; fresh: B(I, J) starts at zero.
+__device__ __forceinline__ void panel_update(const Tile& S, Tile& B, int P, int I, int J, bool fresh) {
+    const int lane = threadIdx.x & 63, kr = lane >> 4, cc = lane & 15;
+    double x[4], y[4];
+    Acc4 acc;
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {
+        x[kk] = -S[16 * P + 4 * kk + kr][16 * I + cc];
+        y[kk] = B[16 * P + 4 * kk + kr][16 * J + cc];
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) acc[r] = fresh ? 0.0 : B[16 * I + kr + 4 * r][16 * J + cc];
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(x[kk], y[kk], acc, 0, 0, 0);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) B[16 * I + kr + 4 * r][16 * J + cc] = acc[r];
+}
+
+// Factor a 64 x 64 diagonal block by row operations on [S | I]: on return the
+// upper part of S is U and the lower part of T is U^-T (the rest of both tiles
+// is not written or read).  Only the upper part of S is read; rows 16.. of it
+// may still be completed by waves 1..3 in `rest`, which runs beside the first
+// panel (wave 0).
 //
-// Four row panels of 16.  For each, wave 0 eliminates the panel in registers,
-// columns across the lanes.  At step c the pivot d is lane (r0 + c)'s entry of
-// row c and every later panel row i loses m_i / d times row c, m_i being row
-// c's entry in lane r0 + i, in the S part and in the identity part alike; row
-// c is then scaled by 1/sqrt(d).  The multipliers are read from row c before
-// it is scaled, so those reads do not wait for the square root, and row c + 1
-// is updated first, so the next pivot's chain overlaps the other rows'
-// updates.  That factors the panel's diagonal block and solves its other
-// columns at once.  Then all four waves subtract the panel's rank-16
-// contribution from the rows below on the matrix cores, as 16 x 16 blocks:
-// S(I, J) -= U(P, I)^T U(P, J) for P < I <= J, and T(I, J) -= U(P, I)^T T(P, J)
-// for J <= P < I.  Returns false on a non-positive pivot (uniformly: the flag
-// goes through LDS).
-__device__ bool factor_diag(Tile& S, Tile& T, uint64_t* rec) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    double* flag = &T[kTile - 1][kTile];  // padding corner, not part of the tile
-    // T starts as the identity: wave 0 makes its first panel's rows in
-    // registers, the other waves write rows 16.. meanwhile (the first
-    // barrier below orders them before any reader).
-    if (wave > 0)
-        for (int e = threadIdx.x - kWave + 16 * kTile; e < kTile * kTile; e += kThreads - kWave)
-            T[e / kTile][e % kTile] = e / kTile == e % kTile ? 1.0 : 0.0;
-#pragma unroll
+// Four row panels of 16, each on wave 0 (factor_panel); then the blocks of the
+// next panel's rows take the panel's rank-16 update on the matrix cores -- there
+// are four of them whatever the panel, one per wave: S(P+1, J > P) and
+// T(P+1, J <= P) -- and the blocks of later rows take it on waves 1..3 while
+// wave 0 eliminates the next panel.
+//
+// Bound by wave 0's chain of 64 pivots.  Whole tile, phase trace at N = 1e6,
+// p = 1000: 11.3 -> 7.5 us (a panel 2.1 -> 1.4) against multipliers broadcast
+// through scalar registers, the identity in a second set of columns and every
+// update before the next panel; a panel step of the chain block 17.3 -> 10.8 us.
+template <class F>
+__device__ __forceinline__ bool factor_diag(Tile& S, Tile& T, double* flag, uint64_t* rec, F rest) {
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+#pragma unroll 1
     for (int P = 0; P < 4; ++P) {
-        const int r0 = 16 * P;
         if (wave == 0) {
-            double a[16], w[16];
-#pragma unroll
-            for (int c = 0; c < 16; ++c) {
-                a[c] = S[r0 + c][lane];
-                w[c] = P == 0 ? (lane == c ? 1.0 : 0.0) : T[r0 + c][lane];
+            const bool ok = factor_panel(S, T, P);
+            if (threadIdx.x == 0) *flag = ok ? 0.0 : 1.0;
+        } else if (P == 0) {
+            rest();
+        } else {
+            // the rank-16 update of panel P - 1 on the rows after panel P
+            int n = 0;
+            for (int I = P + 1; I < 4; ++I) {
+                for (int J = I; J < 4; ++J)
+                    if (n++ % 3 == wave - 1) panel_update(S, S, P - 1, I, J, false);
+                for (int J = 0; J < P; ++J)
+                    if (n++ % 3 == wave - 1) panel_update(S, T, P - 1, I, J, J == P - 1);
             }
-            bool ok = true;
-            double d = rdlane(a[0], r0);
-#pragma unroll
-            for (int c = 0; c < 16; ++c) {
-                double m[16];
-#pragma unroll
-                for (int i = c + 1; i < 16; ++i) m[i] = rdlane(a[c], r0 + i);
-                ok = ok && (d > 0.0);
-                const double rs = rsqrt_nr(d);
-                const double inv = rs * rs;
-                const double ta = a[c] * inv, tw = w[c] * inv;
-                double dn = 0.0;
-                if (c + 1 < 16) {
-                    a[c + 1] = fma(-m[c + 1], ta, a[c + 1]);
-                    w[c + 1] = fma(-m[c + 1], tw, w[c + 1]);
-                    dn = rdlane(a[c + 1], r0 + c + 1);
-                }
-#pragma unroll
-                for (int i = c + 2; i < 16; ++i) {
-                    a[i] = fma(-m[i], ta, a[i]);
-                    w[i] = fma(-m[i], tw, w[i]);
-                }
-                a[c] = lane == r0 + c ? d * rs : a[c] * rs;
-                w[c] *= rs;
-                d = dn;
-            }
-#pragma unroll
-            for (int c = 0; c < 16; ++c) {
-                S[r0 + c][lane] = lane >= r0 + c ? a[c] : 0.0;
-                T[r0 + c][lane] = w[c];
-            }
-            if (lane == 0) *flag = ok ? 0.0 : 1.0;
         }
         __syncthreads();
         stamp_at(rec, 1 + 2 * P);
         if (*flag != 0.0) return false;
         if (P < 3) {
-            // blocks below the panel: S part (I, J), P < I <= J <= 3, then the
-            // T part (I, J), I > P, J <= P; wave w takes blocks w, w + 4, ...
-            const int nS = (3 - P) * (4 - P) / 2, nT = (3 - P) * (P + 1);
-            const int kr = lane >> 4, cc = lane & 15;
-            for (int blk = wave; blk < nS + nT; blk += kThreads / kWave) {
-                int I, J;
-                bool spart = blk < nS;
-                if (spart) {
-                    int idx = blk;
-                    I = P + 1;
-                    while (idx >= 4 - I) {
-                        idx -= 4 - I;
-                        ++I;
-                    }
-                    J = I + idx;
-                } else {
-                    const int t2 = blk - nS;
-                    I = P + 1 + t2 / (P + 1);
-                    J = t2 % (P + 1);
-                }
-                Tile& B = spart ? S : T;
-                Acc4 acc = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-                for (int kk = 0; kk < 4; ++kk) {
-                    const double x = S[r0 + 4 * kk + kr][16 * I + cc];
-                    const double y = B[r0 + 4 * kk + kr][16 * J + cc];
-                    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(x, y, acc, 0, 0, 0);
-                }
-#pragma unroll
-                for (int r = 0; r < 4; ++r) B[16 * I + kr + 4 * r][16 * J + cc] -= acc[r];
-            }
+            const int J = P + 1 + wave;
+            if (J < 4) panel_update(S, S, P, P + 1, J, false);
+            else panel_update(S, T, P, P + 1, J - 4, J - 4 == P);
+            __syncthreads();
         }
-        __syncthreads();
         stamp_at(rec, 2 + 2 * P);
     }
     stamp_at(rec, 9);
@@ -694,19 +708,21 @@ __device__ bool factor_diag(Tile& S, Tile& T, uint64_t* rec) {
 }
 
 // Factor diagonal block kb held in S (its upper part; the rest is not read)
-// and store L^-1_kk = U_kk^-T into Linv: the triangular solves read it from
-// there (U_kk itself is needed by nothing after this block).  Reports a
-// failed pivot.  On return S = U_kk and T = U_kk^-T.
-__device__ void diag_factor(Args& a, uint32_t kb, Tile& S, Tile& T, uint64_t* rec) {
+// and store L^-1_kk = U_kk^-T into Linv, zeros above its diagonal: the
+// triangular solves read it from there (U_kk itself is needed by nothing after
+// this block).  Reports a failed pivot.  On return the lower part of T is U_kk^-T.
+template <class F>
+__device__ __forceinline__ void diag_factor(Args& a, uint32_t kb, Tile& S, Tile& T, double* flag, uint64_t* rec, F rest) {
     const uint32_t P = padded(a.x.p), k0 = kb * kTile;
     stamp_at(rec, 0);
-    if (factor_diag(S, T, rec)) {
+    if (factor_diag(S, T, flag, rec, rest)) {
         const int c = threadIdx.x & (kTile - 1), rb = threadIdx.x >> 6;
+        double v[16];
 #pragma unroll
-        for (int q = 0; q < 16; ++q) {
-            const int r = rb + 4 * q;
-            stc(a.Linv + (size_t)(k0 + r) * P + k0 + c, T[r][c]);
-        }
+        for (int q = 0; q < 16; ++q) v[q] = T[rb + 4 * q][c];
+#pragma unroll
+        for (int q = 0; q < 16; ++q)
+            stc(a.Linv + (size_t)(k0 + rb + 4 * q) * P + k0 + c, keep_if(c <= rb + 4 * q, v[q]));
     } else if (threadIdx.x == 0) {
         atomicOr(&a.ctrl->err, kErrNotPD);
         atomicCAS(&a.ctrl->chol_info, 0, (int)(k0 + 1));
@@ -715,14 +731,74 @@ __device__ void diag_factor(Args& a, uint32_t kb, Tile& S, Tile& T, uint64_t* re
     stamp_at(rec, 10);
 }
 
+// Four 16 x 16 blocks of a tile in the matrix-core layout, one block column:
+// block I's r-th value of lane l is row 16 I + l / 16 + 4 r, column l % 16.
+struct MCol {
+    Acc4 v[4];
+};
+
+// Wave w's block column of W X for a lower triangular W (its upper part is
+// not read): rows of block I need only the column blocks K <= I of W, 40
+// matrix operations instead of 64.
+__device__ __forceinline__ void trsm_tri(const Tile& W, const Tile& X, MCol& out) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, kr = lane >> 4, cc = lane & 15;
+#pragma unroll
+    for (int I = 0; I < 4; ++I) out.v[I] = Acc4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int K = 0; K < 4; ++K) {
+        double y[4];
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) y[kk] = X[16 * K + 4 * kk + kr][16 * wave + cc];
+#pragma unroll
+        for (int I = K; I < 4; ++I)
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk) {
+                const int k = 16 * K + 4 * kk + kr, i = 16 * I + cc;
+                const double w = I > K ? W[i][k] : keep_if(k <= i, W[i][k]);
+                out.v[I] = __builtin_amdgcn_mfma_f64_16x16x4f64(w, y[kk], out.v[I], 0, 0, 0);
+            }
+    }
+}
+
+// Store a wave's block column of the tile at (r0, c0) of M.
+__device__ __forceinline__ void put_col(double* M, uint32_t P, uint32_t r0, uint32_t c0, const MCol& v) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, kr = lane >> 4, cc = lane & 15;
+#pragma unroll
+    for (int I = 0; I < 4; ++I)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) stc(M + (size_t)(r0 + 16 * I + kr + 4 * r) * P + c0 + 16 * wave + cc, v.v[I][r]);
+}
+
+// The blocks (I, J), I <= J, of a diagonal tile that each wave updates in a
+// panel step: first (0, wave), which the first row panel needs, then for waves
+// 1..3 two of the other six.
+__device__ __forceinline__ void rest_block(int wave, int n, int& I, int& J) {
+    I = wave == 3 && n == 0 ? 2 : wave == 3 ? 3 : wave == 2 && n == 1 ? 2 : 1;
+    J = wave == 1 ? 1 + n : wave == 2 ? 3 - n : 3;
+}
+
+// C(I, J) = old - (U^T U)(I, J) over 64 rows, U in LDS, into D.
+__device__ __forceinline__ void syrk_block(const Tile& U, Tile& D, int I, int J, Acc4 acc) {
+    const int lane = threadIdx.x & 63, kr = lane >> 4, cc = lane & 15;
+#pragma unroll
+    for (int q0 = 0; q0 < kTile; q0 += 4)
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-U[q0 + kr][16 * I + cc], U[q0 + kr][16 * J + cc], acc, 0, 0, 0);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) D[16 * I + kr + 4 * r][16 * J + cc] = acc[r];
+}
+
 // Run block `rank`'s list of factorisation tasks.  Tile versions: U tile
 // (i, j), i <= j, has had v of its i updates (plus 1 once final); L^-1 tile
 // (i, j), j <= i, v of its i - j updates (plus 1 once final).  Each task waits
 // for the versions it reads, then publishes the version it wrote.  Returns
 // false if the group is failing.
-__device__ bool run_tasks(Args& a, Group& g, uint32_t rank, double tau, Tile& S, Tile& T,
+__device__ __forceinline__ bool run_tasks(Args& a, Group& g, uint32_t rank, double tau, Tile& S, Tile& T,
                           double* flag) {
     const uint32_t p = a.x.p, P = padded(p), nt = P / kTile;
+    // flags of the factorisation and of the queue, in T's padding columns
+    double* fact_flag = &T[kTile - 1][kTile];
+    double* next_lds = &T[kTile - 2][kTile];
+    bool swapped = false;  // the chain block's two tiles trade places with every panel step
     uint32_t* vU = a.ver;
     uint32_t* vL = a.ver + nt * nt;
     // Block 0 (or a group of one) runs its own list; the others claim tasks
@@ -730,7 +806,6 @@ __device__ bool run_tasks(Args& a, Group& g, uint32_t rank, double tau, Tile& S,
     // starts one.  The claimed index travels to the block through LDS.
     const bool queue = g.size > 1 && rank > 0;
     const uint32_t n0 = queue ? a.task_off[1] : 0u, n1 = queue ? a.task_off[2] : a.task_off[1];
-    double* next_lds = &T[kTile - 2][kTile];  // padding, not part of the tile
     uint32_t n = n0;
     if (queue) {
         if (threadIdx.x == 0) *next_lds = (double)atomicAdd(&a.ctrl->task_next, 1u);
@@ -786,36 +861,73 @@ __device__ bool run_tasks(Args& a, Group& g, uint32_t rank, double tau, Tile& S,
             uint64_t* rec = nullptr;
             if (g.trace && g.npotrf < (uint32_t)kTraceRecs) rec = g.trace + kTraceSeq + kTraceRec * g.npotrf;
             g.npotrf++;
+            Acc4 dg[3];
+            int I1 = 0, J1 = 0, I2 = 0, J2 = 0;
+            Tile& Sc = swapped ? T : S;  // (a step's tiles trade places with the previous one's)
+            Tile& Tc = swapped ? S : T;
             if (type == kTaskPotrf) {
-                load_tile(S, kb == 0 ? a.Gp : a.A, P, k0, k0, kb == 0, tau, a.lam_m2, p);
+                load_tile(Sc, kb == 0 ? a.Gp : a.A, P, k0, k0, kb == 0, tau, a.lam_m2, p);
                 __syncthreads();
                 stamp(g);
             } else {
-                // U_{k-1,k} = D_{k-1}^T A_{k-1,k} with D_{k-1}^T still in T, then
-                // A_kk -= U_{k-1,k}^T U_{k-1,k}, all in this block
+                // U_{k-1,k} = L^-1_{k-1,k-1} A_{k-1,k} with L^-1_{k-1,k-1} still in
+                // T, then A_kk -= U_{k-1,k}^T U_{k-1,k} and its factorisation, all
+                // in this block.  U overwrites A_{k-1,k} in S (a wave reads and
+                // writes its own 16 columns only), the updated A_kk takes T's
+                // place, and the new inverse takes S's: the six blocks of A_kk
+                // outside its first 16 rows read U's columns 16.. while the first
+                // panel is factored, which writes columns 0..15 only.
                 const uint32_t km = kb - 1, r1 = km * kTile;
                 const double* src = km == 0 ? a.Gp : a.A;
-                MTile dg;
-                load_tile_m(dg, src, P, k0, k0, km == 0, tau, a.lam_m2, p);
-                load_tile(S, src, P, r1, k0, false, 0.0, nullptr, p);
+                const int lane = threadIdx.x & 63, kr = lane >> 4, cc = lane & 15;
+                const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+                // this wave's blocks of A_kk: (0, wave), then rest_block's
+                auto diag_block = [&](int I, int J) {
+                    const uint32_t i0 = k0 + 16 * I + kr, j = k0 + 16 * J + cc;
+                    Acc4 v;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) v[r] = ldc(src + (size_t)(i0 + 4 * r) * P + j);
+                    if (km == 0 && I == J) {
+#pragma unroll
+                        for (int r = 0; r < 4; ++r)
+                            if (i0 + 4 * r == j && j < p) v[r] += tau * ldc(a.lam_m2 + j);
+                    }
+                    return v;
+                };
+                rest_block(wave, 0, I1, J1);
+                rest_block(wave, 1, I2, J2);
+                dg[0] = diag_block(0, wave);
+                if (wave != 0) {
+                    dg[1] = diag_block(I1, J1);
+                    dg[2] = diag_block(I2, J2);
+                }
+                load_tile(Sc, src, P, r1, k0, false, 0.0, nullptr, p);
                 __syncthreads();
                 stamp(g);
-                MAcc acc;
-                gemm_tn<true>(T, S, acc);
-                MTile zero;
-                load_tile_m(zero, nullptr, P, 0, 0, false, 0.0, nullptr, p);
-                put_tile_m(a.A, P, r1, k0, acc, 1.0, zero);
-                __syncthreads();
-                acc_to_lds(S, acc, 1.0, zero);
-                __syncthreads();
-                gemm_tn(S, S, acc);
+                MCol u;
+                trsm_tri(Tc, Sc, u);
+                put_col(a.A, P, r1, k0, u);
+#pragma unroll
+                for (int I = 0; I < 4; ++I)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) Sc[16 * I + kr + 4 * r][16 * wave + cc] = u.v[I][r];
+                __syncthreads();  // all of U in S; T has been read
+                syrk_block(Sc, Tc, 0, wave, dg[0]);
                 // U_{k-1,k} is published once its stores are complete; the
                 // product above hid their latency
                 publish(&vU[km * nt + kb], kb);
-                acc_to_lds(S, acc, -1.0, dg);
-                __syncthreads();
+                swapped = !swapped;
             }
-            diag_factor(a, kb, S, T, rec);
+            {
+                Tile& Sd = swapped ? T : S;
+                Tile& Td = swapped ? S : T;
+                diag_factor(a, kb, Sd, Td, fact_flag, rec, [&] {
+                    if (type == kTaskPanel) {
+                        syrk_block(Td, Sd, I1, J1, dg[1]);
+                        syrk_block(Td, Sd, I2, J2, dg[2]);
+                    }
+                });
+            }
             if (threadIdx.x == 0 &&
                 (__hip_atomic_load(&a.ctrl->err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & kErrNotPD))
                 *flag = 1.0;
@@ -825,16 +937,14 @@ __device__ bool run_tasks(Args& a, Group& g, uint32_t rank, double tau, Tile& S,
             val = kb + 1;
             out2 = &vL[kb * nt + kb];
         } else if (type == kTaskTrsm) {
-            // row kb times U_kk^-1: X_kj = L^-1_kk X_kj, L^-1_kk from Linv
+            // X_kj = L^-1_kk X_kj, L^-1_kk from Linv
             const uint32_t j0 = jb * kTile;
             load_tiles(S, a.Linv, k0, k0, T, part == 0 ? (kb == 0 ? a.Gp : a.A) : a.Linv, k0, j0, P);
             __syncthreads();
             stamp(g);
-            MAcc acc;
-            gemm_tn<true>(S, T, acc);
-            MTile zero;
-            load_tile_m(zero, nullptr, P, 0, 0, false, 0.0, nullptr, p);
-            put_tile_m(part == 0 ? a.A : a.Linv, P, k0, j0, acc, 1.0, zero);
+            MCol x;
+            trsm_tri(S, T, x);
+            put_col(part == 0 ? a.A : a.Linv, P, k0, j0, x);
             out = part == 0 ? &vU[kb * nt + jb] : &vL[kb * nt + jb];
             val = part == 0 ? kb + 1 : kb - jb + 1;
         } else {
@@ -874,7 +984,7 @@ __device__ bool run_tasks(Args& a, Group& g, uint32_t rank, double tau, Tile& S,
 // U_ik beta_k, beta_i = U_ii^-1 r_i = (L^-1_ii)^T r_i.  A row waits only on
 // rows finished before it in the same direction, so the solve cannot
 // deadlock.  Flags sit after the tile versions and are cleared with them.
-__device__ void subst_solve(Args& a, Group& g, uint32_t rank, uint32_t k, double* lds, bool from_sum) {
+__device__ __forceinline__ void subst_solve(Args& a, Group& g, uint32_t rank, uint32_t k, double* lds, bool from_sum) {
     const uint32_t p = a.x.p, P = padded(p), nt = P / kTile;
     uint32_t* ff = a.ver + 2 * nt * nt;  // forward: w_i stored
     uint32_t* fb = ff + nt;              // backward: beta_i stored
@@ -984,7 +1094,7 @@ __device__ void subst_solve(Args& a, Group& g, uint32_t rank, uint32_t k, double
     group_sync(g);
 }
 
-__device__ void tile_path(Args& a, Group& g, uint32_t rank, uint32_t k, double* lds) {
+__device__ __forceinline__ void tile_path(Args& a, Group& g, uint32_t rank, uint32_t k, double* lds) {
     const uint32_t p = a.x.p, P = padded(p);
     Tile& S = *reinterpret_cast<Tile*>(lds);
     Tile& T = *reinterpret_cast<Tile*>(lds + kTile * kTileLd);
