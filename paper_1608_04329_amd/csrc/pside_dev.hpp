@@ -777,14 +777,16 @@ __device__ __forceinline__ void rest_block(int wave, int n, int& I, int& J) {
     J = wave == 1 ? 1 + n : wave == 2 ? 3 - n : 3;
 }
 
-// C(I, J) = old - (U^T U)(I, J) over 64 rows, U in LDS, into D.
-__device__ __forceinline__ void syrk_block(const Tile& U, Tile& D, int I, int J, Acc4 acc) {
+// D(I, J) = old - (U^T U)(I, J) over 64 rows, U in LDS: the sums and the
+// subtraction a GEMM task does (a group of one block factors with those).
+__device__ __forceinline__ void syrk_block(const Tile& U, Tile& D, int I, int J, const Acc4& old) {
     const int lane = threadIdx.x & 63, kr = lane >> 4, cc = lane & 15;
+    Acc4 acc = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
     for (int q0 = 0; q0 < kTile; q0 += 4)
-        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-U[q0 + kr][16 * I + cc], U[q0 + kr][16 * J + cc], acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(U[q0 + kr][16 * I + cc], U[q0 + kr][16 * J + cc], acc, 0, 0, 0);
 #pragma unroll
-    for (int r = 0; r < 4; ++r) D[16 * I + kr + 4 * r][16 * J + cc] = acc[r];
+    for (int r = 0; r < 4; ++r) D[16 * I + kr + 4 * r][16 * J + cc] = fma(-1.0, acc[r], old[r]);
 }
 
 // Run block `rank`'s list of factorisation tasks.  Tile versions: U tile
