@@ -84,7 +84,9 @@ typedef struct {
     int32_t debug_store_z;  /* 1: keep z, the accepted attempt and X^T z of the
                                last z step for hsp_get_debug (costs N*8 bytes
                                of writes per sweep) */
-    int32_t use_graph;      /* 1 (default): replay sweeps from a captured HIP graph */
+    int32_t use_graph;      /* no effect on draws or speed: a chain's sweep is one kernel,
+                               launched directly; a batch of several launches replays a
+                               captured HIP graph whatever this says (default 1) */
     int32_t multi_chain_z;  /* batches: 1 (default) = chains sharing a bfloat16 design
                                with rows of at most 1024 elements run one z pass for
                                up to 16 of them (X beta and X^T z as matrix-core
@@ -230,7 +232,8 @@ const char* hsp_last_error(const hsp_state* s);
  * chains of one design share its library copy of X, y and G = X^T X).  One
  * hsp_batch_sweep advances every chain by the same number of sweeps; each
  * batched sweep is a single replay of a captured HIP graph holding every
- * chain's sweep kernel, one after another on the batch's stream (the
+ * chain's sweep kernel (or, if one launch holds them all, that launch), one
+ * after another on the batch's stream (the
  * multi-chain passes described below may run on a second stream beside the
  * other chains' launches; the graph joins it before their p-side launch).
  * Every dataset of a batch is resident (x_stream is ignored).  Chain i

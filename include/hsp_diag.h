@@ -26,8 +26,7 @@ extern "C" {
  * (loaded, after each of the four panels and their updates, stored); and in
  * the last slot the moment the z pass was seen complete.
  * hsp_get_phase_trace copies group_blocks x slots uint64 values of the last
- * launch; ticks_per_us converts the timestamps.  Enabling drops the captured
- * graph. */
+ * launch; ticks_per_us converts the timestamps.  */
 hsp_status hsp_set_phase_trace(hsp_state* s, int32_t enable);
 hsp_status hsp_get_phase_trace(hsp_state* s, uint64_t* out, int64_t* group_blocks, int64_t* slots,
                                double* ticks_per_us);

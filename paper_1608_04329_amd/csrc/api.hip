@@ -116,7 +116,6 @@ struct hsp_state {
     uint64_t draw_base = 0;    // host mirror of ctrl->draw_base
     std::string err;
     bool poisoned = false;
-    hipGraphExec_t graph = nullptr;  // one whole sweep (one kernel), recording
     uint64_t* trace = nullptr;        // p-side phase timestamps (diagnostics)
     SweepArgs* dargs = nullptr;       // [0]: a whole sweep, [1]: the last hsp_step
     const SweepArgs** dtab = nullptr;  // device table {dargs, dargs + 1} for the launches
@@ -230,22 +229,6 @@ hipError_t enqueue_sweep(hsp_state* s, hipStream_t st) {
     return sweep_launch(h, s->dtab, s->plan, st);
 }
 
-hipError_t capture(hsp_state* s, hipGraphExec_t* out) {
-    hipGraph_t g = nullptr;
-    hipError_t e = hipStreamBeginCapture(s->stream, hipStreamCaptureModeThreadLocal);
-    if (e) return e;
-    hipError_t e2 = enqueue_sweep(s, s->stream);
-    e = hipStreamEndCapture(s->stream, &g);
-    if (e2) {
-        if (g) (void)hipGraphDestroy(g);
-        return e2;
-    }
-    if (e) return e;
-    e = hipGraphInstantiate(out, g, nullptr, nullptr, 0);
-    (void)hipGraphDestroy(g);
-    return e;
-}
-
 hsp_status check_device_flags(hsp_state* s) {
     Ctrl c;
     HIP_TRY(hipMemcpy(&c, s->ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost));
@@ -272,7 +255,6 @@ hsp_status sync_state(hsp_state* s) {
 void free_state(hsp_state* s) {
     if (!s) return;
     if (s->stream) (void)hipStreamSynchronize(s->stream);
-    if (s->graph) (void)hipGraphExecDestroy(s->graph);
     s->timer.reset();
     if (s->owner) {  // borrowed from the dataset's first chain
         s->Xbuf = nullptr;
@@ -359,10 +341,6 @@ hsp_status apply_plan(hsp_state* s, const SweepPlan& plan) {
     }
     SweepArgs h;
     HIP_TRY(put_args(s, kModeSweep, 0, &h));
-    if (s->graph) {
-        (void)hipGraphExecDestroy(s->graph);
-        s->graph = nullptr;
-    }
     return HSP_OK;
 }
 
@@ -1012,7 +990,7 @@ struct hsp_batch {
     std::vector<Pack> packs;         // how the chains share launches
     hipStream_t stream = nullptr;
     bool own_stream = false;
-    hipGraphExec_t graph = nullptr;  // every chain's sweep, one after another
+    hipGraphExec_t graph = nullptr;  // every chain's sweep, one after another (more than one launch)
     bool timing = false;
     EventTimer timer;  // timed batched sweeps
     std::string err;
@@ -1409,13 +1387,22 @@ hsp_status plan_packs(hsp_batch* b) {
     return HSP_OK;
 }
 
+// Whether a batched sweep is a single launch, which needs no graph.
+bool one_launch(const hsp_batch* b) { return b->packs.size() == 1 && !b->packs[0].mc; }
+
+hipError_t batch_enqueue(hsp_batch* b) {
+    if (b->graph) return hipGraphLaunch(b->graph, b->stream);
+    const Pack& pk = b->packs[0];
+    return pack_launch(pk.xtype, pk.chunks, pk.dtab, pk.dmap, pk.blocks, b->stream);
+}
+
 // The packs (if not planned yet) and the graph of one batched sweep.
 hsp_status batch_build(hsp_batch* b) {
     if (b->packs.empty()) {
         hsp_status st = plan_packs(b);
         if (st != HSP_OK) return st;
     }
-    if (b->graph) return HSP_OK;
+    if (b->graph || one_launch(b)) return HSP_OK;
     bool any_mc = false, any_pre = false;
     size_t n_plain = 0;
     for (const Pack& pk : b->packs) {
@@ -1530,9 +1517,9 @@ hsp_status time_batch(hsp_batch* b, int warm, int timed, double* ms) {
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (hipEventCreate(&e0) != hipSuccess) return batch_fail(b, HSP_EHIP, "event");
     hipError_t e = hipEventCreate(&e1);
-    for (int i = 0; !e && i < warm; ++i) e = hipGraphLaunch(b->graph, b->stream);
+    for (int i = 0; !e && i < warm; ++i) e = batch_enqueue(b);
     if (!e) e = hipEventRecord(e0, b->stream);
-    for (int i = 0; !e && i < timed; ++i) e = hipGraphLaunch(b->graph, b->stream);
+    for (int i = 0; !e && i < timed; ++i) e = batch_enqueue(b);
     if (!e) e = hipEventRecord(e1, b->stream);
     if (!e) e = hipEventSynchronize(e1);
     float t = 0.0f;
@@ -1806,7 +1793,7 @@ hsp_status hsp_batch_sweep(hsp_batch* b, int64_t n) {
         if (s->sweeps_done + (uint64_t)n >= (uint64_t(1) << 32) - 1)
             return batch_fail(b, HSP_EINVAL, "the sweep counter would exceed 2^32");
     }
-    if (!b->graph) {
+    if (!b->graph && !(one_launch(b) && !b->autotune)) {
         if (b->autotune) {
             b->autotune = false;  // once per batch
             hsp_status st = batch_tune(b);
@@ -1818,8 +1805,7 @@ hsp_status hsp_batch_sweep(hsp_batch* b, int64_t n) {
     for (int64_t i = 0; i < n; ++i) {
         if (b->timing && b->timer.begin(b->stream) != hipSuccess)
             return batch_fail(b, HSP_EHIP, "timing event");
-        if (hipGraphLaunch(b->graph, b->stream) != hipSuccess)
-            return batch_fail(b, HSP_EHIP, "batch graph launch");
+        if (batch_enqueue(b) != hipSuccess) return batch_fail(b, HSP_EHIP, "batch launch");
         if (b->timing && b->timer.end(b->stream) != hipSuccess)
             return batch_fail(b, HSP_EHIP, "timing event");
     }
@@ -1881,14 +1867,11 @@ hsp_status hsp_sweep(hsp_state* s, int64_t n) {
         s->sweeps_done += (uint64_t)n;
         return HSP_OK;
     }
-    if (s->opt.use_graph && !s->graph) {
-        hipError_t e = capture(s, &s->graph);
-        if (e) return fail_hip(s, "graph capture", e);
-    }
+    // a sweep is one kernel: launching it costs the host 1.6 us, replaying a graph
+    // that holds only it 13 us (and 8 us between sweeps on the device instead of 3)
     for (int64_t i = 0; i < n; ++i) {
         if (s->timing) HIP_TRY(s->timer.begin(s->stream));
-        if (s->graph) HIP_TRY(hipGraphLaunch(s->graph, s->stream));
-        else HIP_TRY(enqueue_sweep(s, s->stream));
+        HIP_TRY(enqueue_sweep(s, s->stream));
         if (s->timing) HIP_TRY(s->timer.end(s->stream));
     }
     s->sweeps_done += (uint64_t)n;
@@ -2066,10 +2049,6 @@ hsp_status hsp_set_phase_trace(hsp_state* s, int32_t enable) {
     if (!s) return HSP_EINVAL;
     HIP_TRY(hipStreamSynchronize(s->stream));
     s->sd_mode = 0;  // streamed launch descriptions carry the trace pointer
-    if (s->graph) {
-        (void)hipGraphExecDestroy(s->graph);
-        s->graph = nullptr;
-    }
     if (s->trace) {
         (void)hipFree(s->trace);
         s->trace = nullptr;
@@ -2207,10 +2186,6 @@ hsp_status hsp_sort_rows(hsp_state* s) {
     s->row_id = ido;
     SweepArgs h;
     HIP_TRY(put_args(s, kModeSweep, 0, &h));
-    if (s->graph) {
-        (void)hipGraphExecDestroy(s->graph);
-        s->graph = nullptr;
-    }
     return HSP_OK;
 }
 
