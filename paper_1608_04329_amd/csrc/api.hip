@@ -964,7 +964,7 @@ struct Pack {
     bool mc = false;
     McArgs* dmc = nullptr;          // device copy of the pass's description
     double* mc_partial = nullptr;   // mc_gz x kMcChains x mc_stride(ld)
-    uint32_t* mc_count = nullptr;   // group and unit counters
+    uint32_t* mc_count = nullptr;   // the pass's next unit
     uint32_t mc_gz = 0, mc_ld = 0;
     std::vector<size_t> chains;             // indices into hsp_batch::chains
     std::vector<uint32_t> gp, gz;           // the pack's blocks per chain
@@ -1371,16 +1371,14 @@ hsp_status plan_packs(hsp_batch* b) {
             m.y = dev_ptr(static_cast<const uint8_t*>(own->y));
             m.nchains = (uint32_t)nc;
             m.gz = pk.mc_gz;
-            m.zgroups = (m.gz + kZGroup - 1) / kZGroup;
-            const size_t ncount = (size_t)m.zgroups + 64;
             m.pstride = mc_stride(pk.mc_ld);
             if (dalloc(&pk.dmc, 1) || dalloc(&pk.mc_partial, (size_t)m.gz * kMcChains * m.pstride) ||
-                dalloc(&pk.mc_count, ncount))
+                dalloc(&pk.mc_count, 1))
                 return batch_fail(b, HSP_ENOMEM, "pack allocation failed");
             m.partial = dev_ptr(pk.mc_partial);
-            m.count = dev_ptr(pk.mc_count);
+            m.next_unit = dev_ptr(pk.mc_count);
             for (size_t j = 0; j < nc; ++j) m.chain[j] = dev_ptr(static_cast<const SweepArgs*>(pk.dargs + j));
-            if (hipMemset(pk.mc_count, 0, ncount * 4) || hipMemcpy(pk.dmc, &m, sizeof m, hipMemcpyHostToDevice))
+            if (hipMemset(pk.mc_count, 0, 4) || hipMemcpy(pk.dmc, &m, sizeof m, hipMemcpyHostToDevice))
                 return batch_fail(b, HSP_EHIP, "pack upload");
         }
     }
@@ -1438,7 +1436,8 @@ hsp_status batch_build(hsp_batch* b) {
         if (!e) e = hipEventRecord(b->fork, b->stream);
         if (!e) e = hipStreamWaitEvent(b->side, b->fork, 0);
         for (size_t i = 0; !e && i < b->packs.size(); ++i)
-            if (b->packs[i].mc) e = mc_launch(b->packs[i].dmc, b->packs[i].mc_ld, b->packs[i].mc_gz, b->side);
+            if (b->packs[i].mc) e = mc_launch(b->packs[i].dmc, b->packs[i].mc_ld, b->packs[i].mc_gz,
+                                               (uint32_t)b->packs[i].chains.size(), b->side);
         if (!e) e = hipEventRecord(b->join, b->side);
         if (any_pre) {
             if (!e) e = hipStreamWaitEvent(b->side2, b->fork, 0);
@@ -1473,7 +1472,7 @@ hsp_status batch_build(hsp_batch* b) {
         // in pack order: a pre pack comes just before its multi-chain pack
         for (size_t i = 0; !e && i < b->packs.size(); ++i) {
             const Pack& pk = b->packs[i];
-            if (pk.mc) e = mc_launch(pk.dmc, pk.mc_ld, pk.mc_gz, b->stream);
+            if (pk.mc) e = mc_launch(pk.dmc, pk.mc_ld, pk.mc_gz, (uint32_t)pk.chains.size(), b->stream);
             if (!e) e = launch(pk, b->stream);
         }
     }

@@ -226,11 +226,9 @@ struct McArgs {
     HSP_GLOBAL const uint8_t* y;
     uint32_t nchains;                   // chains served (<= kMcChains)
     uint32_t gz;                        // blocks of the launch
-    uint32_t zgroups;                   // ceil(gz / kZGroup)
     HSP_GLOBAL double* partial;         // gz x kMcChains x pstride float64 block partials of X^T z
     uint32_t pstride;                   // mc_stride(ld): every column a block's waves cover
-    HSP_GLOBAL uint32_t* count;         // [0, zgroups): group arrivals; [zgroups]: groups done;
-                                        // [zgroups + 32]: next unit (zero between launches)
+    HSP_GLOBAL uint32_t* next_unit;     // next unit to claim (zero between launches)
     HSP_GLOBAL const SweepArgs* chain[kMcChains];  // the chains' launch descriptions
 };
 
@@ -303,10 +301,11 @@ hipError_t sweep_launch(const SweepArgs& host, const SweepArgs* const* table, co
 int pack_capacity(int xtype, int chunks, int num_cus);
 hipError_t pack_launch(int xtype, int chunks, const SweepArgs* const* table, const uint16_t* chain_of_block,
                        uint32_t blocks, hipStream_t st);
-// The multi-chain z pass over a shared bfloat16 design (mc: device copy of
-// its description, gz blocks): every chain's X^T z is added into its bsum.
-// The chains' p-side groups follow in a launch of their own with kModeBsum.
-hipError_t mc_launch(const McArgs* mc, uint32_t ld, uint32_t gz, hipStream_t st);
+// The multi-chain z pass over a shared bfloat16 design for nchains chains (mc:
+// device copy of its description, gz blocks): every chain's X^T z is left in
+// its bsum.  The chains' p-side groups follow in a launch of their own with
+// kModeBsum.
+hipError_t mc_launch(const McArgs* mc, uint32_t ld, uint32_t gz, uint32_t nchains, hipStream_t st);
 
 // G = X^T X (p x p float64, leading dimension p) of the stored X, unscaled
 // with the column exponents e (null: none).  The rows are cut into nsplit

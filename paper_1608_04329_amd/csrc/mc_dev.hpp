@@ -29,11 +29,11 @@
 //  * At the end of a unit, each D entry is rounded to the 2^-24 grid (in the
 //    stored, column-scaled units) and added into the block's float64 partial;
 //    sums of grid values are exact in any order, so units may be claimed
-//    dynamically and the group sums added into each chain's X^T z
-//    accumulator with float64 atomics while every run stays bit-reproducible.
+//    dynamically while every run stays bit-reproducible.
 //
-// The pass is a launch of its own; the chains' p-side groups run in the next
-// launch and take b from the accumulators (the kernel boundary orders them).
+// The pass is two launches, the second of which sums the blocks' partials
+// (mc_sum_role); the chains' p-side groups run in the next and take b from the
+// accumulators (the kernel boundaries order them).
 #pragma once
 #include "hsp_internal.hpp"
 #include "philox.hpp"
@@ -115,19 +115,21 @@ __device__ void mc_role(McView& m, uint32_t rank, double* lds) {
     }
 
     // beta of chain n on this lane's columns, split, into LDS (every block
-    // holds all of it)
+    // holds all of it).  Eight columns at a time, with no branch around the
+    // loads: a chain or column that is not there reads one that is, then zero.
+    if (!live) b32 = ((Args*)m.chain[0])->beta32;
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
         U32x4 hv, lv;
+        const uint32_t col = 32u * (ks0 + s) + 8u * q;  // ld is a multiple of 8
+        const bool here = live && col < ld;
+        HSP_GLOBAL const F32x4* src = reinterpret_cast<HSP_GLOBAL const F32x4*>(b32 + min(col, ld - 8u));
+        const F32x4 b4[2] = {src[0], src[1]};
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             uint32_t h[2], l[2];
 #pragma unroll
-            for (int e = 0; e < 2; ++e) {
-                const uint32_t col = 32u * (ks0 + s) + 8u * q + 2u * i + e;
-                const float v = (live && col < ld) ? b32[col] : 0.0f;
-                split_bf16(v, h[e], l[e]);
-            }
+            for (int e = 0; e < 2; ++e) split_bf16(here ? b4[i >> 1][2 * (i & 1) + e] : 0.0f, h[e], l[e]);
             hv[i] = h[0] | h[1] << 16;
             lv[i] = l[0] | l[1] << 16;
         }
@@ -151,7 +153,7 @@ __device__ void mc_role(McView& m, uint32_t rank, double* lds) {
 
     const uint32_t n_tiles = (N + kMcRows - 1) / kMcRows;
     const uint32_t n_units = (n_tiles + kMcUnit - 1) / kMcUnit;
-    HSP_GLOBAL uint32_t* unit_next = m.count + m.zgroups + 32;
+    HSP_GLOBAL uint32_t* unit_next = m.next_unit;
     uint32_t maxatt = 0;
     bool capped = false, wrote = false;
 
@@ -195,7 +197,7 @@ __device__ void mc_role(McView& m, uint32_t rank, double* lds) {
                 for (int h = 0; h < 2; ++h)
 #pragma unroll
                     for (int r = 0; r < 4; ++r)
-                        old[s][h][r] = wrote ? ldc(dst + 32u * (ks0 + s0 + s) + 16u * h + 4u * q + r) : 0.0;
+                        old[s][h][r] = wrote ? dst[32u * (ks0 + s0 + s) + 16u * h + 4u * q + r] : 0.0;
 #pragma unroll
             for (int s = 0; s < 4; ++s)
 #pragma unroll
@@ -203,7 +205,7 @@ __device__ void mc_role(McView& m, uint32_t rank, double* lds) {
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
                         const double v = on_grid((double)db[s0 + s][h][r]);
-                        stc(dst + 32u * (ks0 + s0 + s) + 16u * h + 4u * q + r, wrote ? old[s][h][r] + v : v);
+                        dst[32u * (ks0 + s0 + s) + 16u * h + 4u * q + r] = wrote ? old[s][h][r] + v : v;
                     }
         }
         wrote = true;
@@ -330,36 +332,34 @@ __device__ void mc_role(McView& m, uint32_t rank, double* lds) {
         if (mx) atomicMax(&ctrl->max_attempts, mx);
         if (anycap) atomicOr(&ctrl->err, kErrTnCap);
     }
+}
 
-    // This block's partial is complete.  The last of each group of kZGroup
-    // blocks adds the group's partials in block order into every chain's X^T z
-    // accumulator (float64 atomics, exact on the grid); the last group resets
-    // the counters for the next launch.
-    __builtin_amdgcn_s_waitcnt(0);
+// The second launch of the pass: each chain's X^T z from the blocks' partials,
+// 64 columns of one chain per block, a quarter of the partials per wave with
+// sixteen loads in flight (sums on the grid are exact in any order), and the
+// unit counter back to zero.  As the tail of the pass itself (the last block of
+// each group of 16 summing that group's 2 MB) it took ~250 us of the 776 us pass
+// at N = 2.5e5, p = 1000, 16 chains; spread over the device it takes ~10.
+__device__ __forceinline__ void mc_sum_role(McView& m, double* lds) {
+    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6, c = blockIdx.y, ld = m.x.ld;
+    const uint32_t col = blockIdx.x * 64u + lane;
+    HSP_GLOBAL const double* src = m.partial + (size_t)c * m.pstride + min(col, m.pstride - 1u);
+    const size_t step = (size_t)kMcChains * m.pstride;
+    double s = 0.0;
+    for (uint32_t r0 = wave; r0 < m.gz; r0 += 64u) {
+        double v[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) v[i] = src[min(r0 + 4u * i, m.gz - 1u) * step];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) s += r0 + 4u * i < m.gz ? v[i] : 0.0;
+    }
+    lds[threadIdx.x] = s;
     __syncthreads();
-    const uint32_t grp = rank / kZGroup;
-    const uint32_t g0 = grp * kZGroup;
-    const uint32_t gsize = min((uint32_t)kZGroup, m.gz - g0);
-    if (threadIdx.x == 0) *slot = atomicAdd(&m.count[grp], 1u) == gsize - 1 ? 1u : 0u;
-    __syncthreads();
-    const bool last = *slot != 0u;
-    __syncthreads();
-    if (!last) return;
-    for (uint32_t e = threadIdx.x; e < C * ld; e += kThreads) {
-        const uint32_t c = e / ld, col = e % ld;
-        double v = 0.0;
-        for (uint32_t r = 0; r < gsize; ++r) v += ldc(&m.partial[((size_t)(g0 + r) * kMcChains + c) * m.pstride + col]);
+    if (wave == 0 && col < ld) {
         Args& a = *(Args*)m.chain[c];
-        __hip_atomic_fetch_add(&a.bsum[col], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        a.bsum[col] = (lds[lane] + lds[64 + lane]) + (lds[128 + lane] + lds[192 + lane]);
     }
-    if (threadIdx.x == 0) {
-        __hip_atomic_store(&m.count[grp], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (atomicAdd(&m.count[m.zgroups], 1u) == m.zgroups - 1) {
-            // every block has left its claim loop
-            __hip_atomic_store(&m.count[m.zgroups], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(unit_next, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-    }
+    if (blockIdx.x == 0 && c == 0 && threadIdx.x == 0) m.next_unit[0] = 0u;
 }
 
 }  // namespace hsp

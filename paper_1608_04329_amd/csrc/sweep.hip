@@ -68,6 +68,12 @@ __global__ __launch_bounds__(kThreads, 2) void mc_zpass_kernel(const McArgs* __r
     mc_role<KS>(m, blockIdx.x, lds);
 }
 
+__global__ __launch_bounds__(256) void mc_sum_kernel(const McArgs* __restrict__ mc) {
+    __shared__ double lds[256];
+    McView& m = *(McView*)mc;
+    mc_sum_role(m, lds);
+}
+
 using KernelFn = void (*)(const SweepArgs* const*, const uint16_t*);
 
 template <int XT, int... KCs>
@@ -189,12 +195,14 @@ int pack_capacity(int xtype, int chunks, int num_cus) {
     return per_cu * num_cus;
 }
 
-hipError_t mc_launch(const McArgs* mc, uint32_t ld, uint32_t gz, hipStream_t st) {
-    if (ld > kMcMaxLd) return hipErrorInvalidValue;
+hipError_t mc_launch(const McArgs* mc, uint32_t ld, uint32_t gz, uint32_t nchains, hipStream_t st) {
+    if (ld > kMcMaxLd || nchains < 1 || nchains > (uint32_t)kMcChains) return hipErrorInvalidValue;
     void* args[] = {&mc};
     const void* f = mc_steps(ld) == 4u ? reinterpret_cast<const void*>(&mc_zpass_kernel<4>)
                                        : reinterpret_cast<const void*>(&mc_zpass_kernel<kMcKs>);
-    return hipLaunchKernel(f, dim3(gz), dim3(kThreads), args, 0, st);
+    if (hipError_t e = hipLaunchKernel(f, dim3(gz), dim3(kThreads), args, 0, st)) return e;
+    return hipLaunchKernel(reinterpret_cast<const void*>(&mc_sum_kernel), dim3((ld + 63) / 64, nchains), dim3(256),
+                           args, 0, st);
 }
 
 hipError_t pack_launch(int xtype, int chunks, const SweepArgs* const* table, const uint16_t* chain_of_block,
