@@ -826,16 +826,21 @@ hsp_status chain_impl(hsp_state* s) {
         HIP_TRY(hipMemsetAsync(s->A, 0, P * P * sizeof(double), s->stream));
         HIP_TRY(hipMemsetAsync(s->Linv, 0, P * P * sizeof(double), s->stream));
     }
-    HIP_TRY(dalloc(&s->vec, 2 * (size_t)p + 8));
+    {
+        const size_t off = handoff_offset((uint32_t)p), n = off + (p > kSmallP ? 2 * P : 0);
+        std::vector<unsigned long long> init(n, 0ull);
+        std::fill(init.begin() + off, init.end(), kNotReady);
+        HIP_TRY(dalloc(&s->vec, n));
+        HIP_TRY(hipMemcpy(s->vec, init.data(), n * 8, hipMemcpyHostToDevice));
+    }
 
     HIP_TRY(sweep_plan(s->x, s->num_cus, &s->plan));
     s->plan_note = "built-in";
     if (p > kSmallP) {
         // the factorisation's task lists for the group, and its tile versions
         const uint32_t nt = (uint32_t)(P / kTile);
-        // tile versions, then the substitution's 2 nt row flags (p > kSubstP)
-        HIP_TRY(dalloc(&s->ver, 2 * (size_t)nt * nt + 2 * (size_t)nt));
-        HIP_TRY(hipMemsetAsync(s->ver, 0, (2 * (size_t)nt * nt + 2 * (size_t)nt) * 4, s->stream));
+        HIP_TRY(dalloc(&s->ver, 2 * (size_t)nt * nt));
+        HIP_TRY(hipMemsetAsync(s->ver, 0, 2 * (size_t)nt * nt * 4, s->stream));
         hsp_status st = upload_schedule(s);
         if (st) return st;
     }

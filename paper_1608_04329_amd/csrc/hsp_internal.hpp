@@ -153,7 +153,7 @@ struct SweepArgs {
     HSP_GLOBAL const double* Gp;   // tile path: P x P, G with an identity block on the padding
     HSP_GLOBAL double* A;          // tile path, P x P: U (P = p rounded up to 64)
     HSP_GLOBAL double* Linv;       // tile path, P x P: lower triangle holds L^-1 = U^-T
-    HSP_GLOBAL double* vec;        // 2 p scratch
+    HSP_GLOBAL double* vec;        // 2 p + 8 scratch, then the substitution's hand-off (handoff_offset)
     HSP_GLOBAL double* ring_beta;  // capacity x p
     HSP_GLOBAL double* ring_tau;   // capacity
     HSP_GLOBAL double* ring_lam;   // capacity x p or null
@@ -264,6 +264,10 @@ __host__ __device__ constexpr uint32_t task_code(uint32_t type, uint32_t part, u
 // against 1.23 ms; N = 5e5, p = 2048: 1.66 against 1.29 ms; N = 2e5, p = 4096:
 // 11.5 against 6.5 ms).
 constexpr int kSubstP = 1536;
+// The substitution's hand-off values (2 P doubles, P = p rounded up to 64) in a
+// chain's scratch vector, and what they hold until they are stored.
+__host__ __device__ constexpr uint32_t handoff_offset(uint32_t p) { return (2u * p + 8u + 15u) / 16u * 16u; }
+constexpr unsigned long long kNotReady = 0x7FF85EED5EED5EEDull;
 constexpr bool with_inverse(uint32_t nt) { return nt * (uint32_t)kTile <= (uint32_t)kSubstP; }
 // inverse: whether the L^-1 tasks are part of the graph (a lone chain:
 // with_inverse(nt); the chains of a multi-chain pass, whose factorisation

@@ -976,110 +976,164 @@ __device__ __forceinline__ bool run_tasks(Args& a, Group& g, uint32_t rank, doub
     return true;
 }
 
-// beta = U^-1 (U^-T b + s) by blocked substitution (p > kSubstP: there the
-// factorisation leaves L^-1 out beyond its diagonal tiles, half of its flops).
-// Block r of the group owns tile rows r, r + gp, ...  Forward, its rows in
-// increasing order: the owner of row i subtracts U_ki^T w_k from b_i for each
-// k < i as soon as row k's flag is up, then w_i = L^-1_ii r_i (the diagonal
-// tile of L^-1 the factorisation stored), stores it and raises row i's flag.
-// Backward, its rows in decreasing order: r_i = w_i + s_i - sum_{k > i}
-// U_ik beta_k, beta_i = U_ii^-1 r_i = (L^-1_ii)^T r_i.  A row waits only on
-// rows finished before it in the same direction, so the solve cannot
-// deadlock.  Flags sit after the tile versions and are cleared with them.
+// Values handed from row to row of the substitution: two P-vectors after the
+// 2 p + 8 scratch doubles, on a 128-byte boundary, which hold kNotReady (a NaN
+// no arithmetic produces) until the value is stored and again between launches.
+// A reader polls the values themselves, so a hand-off is one store and one load.
+__device__ __forceinline__ double* handoff(Args& a) { return (double*)(a.vec + handoff_offset(a.x.p)); }
+
+// One wave: hand[idx] of every lane once all are there.  After a failure of the
+// group (or a time-out, which sets one) it returns what is there.
+__device__ __forceinline__ double take(const double* hand, int idx, Ctrl* ctrl, uint64_t timeout, uint32_t cap) {
+    uint64_t t0 = 0;
+    uint32_t nap = 1;
+    for (int it = 0;; ++it) {
+        const double v = ldc(hand + idx);
+        const uint32_t err = __hip_atomic_load(&ctrl->err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (__ballot((unsigned long long)__double_as_longlong(v) == kNotReady) == 0ull) return v;
+        if (err & (kErrTimeout | kErrNotPD)) return v;
+        if (it == 0) t0 = wall_clock64();
+        if (wall_clock64() - t0 > timeout) {
+            if ((threadIdx.x & 63) == 0) atomicOr(&ctrl->err, kErrTimeout);
+            return v;
+        }
+        backoff(nap, cap);
+    }
+}
+
+// acc += sum_j x_j y[j], x_j being lane j of x's row of 16 lanes.
+template <int J = 0>
+__device__ __forceinline__ void dot_bcast(double& acc, double minus_x, const double (&y)[16]) {
+    if constexpr (J < 16) {
+        fmsub_bcast<J>(acc, minus_x, y[J]);
+        dot_bcast<J + 1>(acc, minus_x, y);
+    }
+}
+
+// beta = U^-1 (U^-T b + s) by blocked substitution (where the factorisation
+// leaves L^-1 out beyond its diagonal tiles, half of its flops).  Block r of the
+// group owns tile rows r, r + gp, ...  Forward, its rows in increasing order:
+// w_i = L^-1_ii (b_i - sum_{k < i} U_ki^T w_k); backward, in decreasing order:
+// beta_i = (L^-1_ii)^T (w_i + s_i - sum_{k > i} U_ik beta_k).  A row waits only on
+// rows finished before it in the same direction, so the solve cannot deadlock.
+//
+// Bound by the hand-off from row to row, so all that does not depend on the
+// last w_k (beta_k) is done before it arrives: the next tile and L^-1_ii are in
+// registers, the sums stay in each wave's registers (forward, wave q sums rows
+// 16 q .. of the tile, broadcast from the 16 lanes that polled them; backward,
+// rows 16 q .. of the output, one column per lane) and meet in LDS once per row,
+// and each wave then multiplies 16 rows of the diagonal tile.  Per row step: 1.45 us,
+// against 5.2-5.8 with flags beside the data, tiles loaded after the flag and
+// three barriers (p = 4096: 640 -> 184 us; p = 7003: 1270 -> 326 us).
 __device__ __forceinline__ void subst_solve(Args& a, Group& g, uint32_t rank, uint32_t k, double* lds, bool from_sum) {
     const uint32_t p = a.x.p, P = padded(p), nt = P / kTile;
-    uint32_t* ff = a.ver + 2 * nt * nt;  // forward: w_i stored
-    uint32_t* fb = ff + nt;              // backward: beta_i stored
-    double* yv = a.vec;                  // w (then read back for y = w + s)
+    double* hw = handoff(a);  // w
+    double* hb = hw + P;      // beta
     const double* s_noise = a.vec + p;
-    double* rv = lds;                    // the owned row's running vector (64)
-    double* part = lds + kTile;          // 4 x 64 partial sums
-    double* flag = lds + 5 * kTile;
-    const int c = threadIdx.x & (kTile - 1), q = threadIdx.x >> 6;
-    auto b_at = [&](uint32_t j) -> double {
-        if (j >= p) return 0.0;
-        return from_sum ? ldc(&a.bsum[j]) * a.xscale[j] : a.b[j];
+    double* part = lds;  // 4 x 64
+    const int lane = threadIdx.x & 63, c = lane & 15, grp = lane >> 4;
+    const int q = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // sum over the four groups of 16 lanes
+    auto over_groups = [](double v) {
+        v += __shfl_xor(v, 16);
+        return v + __shfl_xor(v, 32);
     };
-    auto wait_row = [&](uint32_t* f) -> bool {
-        if (threadIdx.x == 0) {
-            uint32_t* v[3] = {f, nullptr, nullptr};
-            const uint32_t need[3] = {1u, 0u, 0u};
-            *flag = wait_vers(v, need, 1, a.ctrl, g.timeout) ? 0.0 : 1.0;
-        }
-        __syncthreads();
-        return *flag == 0.0;
-    };
-    // rv -= the four partial sums (then every thread sees the new rv)
-    auto fold = [&](double acc) {
-        part[q * kTile + c] = acc;
-        __syncthreads();
-        if (threadIdx.x < (uint32_t)kTile)
-            rv[c] -= (part[c] + part[kTile + c]) + (part[2 * kTile + c] + part[3 * kTile + c]);
-        __syncthreads();
-    };
-    bool ok = true;
-    for (uint32_t i = rank; ok && i < nt; i += g.size) {
-        const uint32_t i0 = i * kTile;
-        if (threadIdx.x < (uint32_t)kTile) rv[c] = b_at(i0 + c);
-        __syncthreads();
-        for (uint32_t kk = 0; ok && kk < i; ++kk) {
-            if (!(ok = wait_row(&ff[kk]))) break;
-            // (U_kk,i^T w_kk)_c: thread (q, c) sums rows q, q + 4, ... of the tile
-            double acc = 0.0;
-#pragma unroll 4
-            for (int j = 0; j < 16; ++j) {
-                const uint32_t row = kk * kTile + q + 4 * j;
-                const double wv = row < p ? ldc(&yv[row]) : 0.0;
-                acc = fma(ldc(&a.A[(size_t)row * P + i0 + c]), wv, acc);
+    for (uint32_t i = rank; i < nt; i += g.size) {
+        const uint32_t i0 = i * kTile, j0 = i0 + lane;
+        const double b = j0 < p ? (from_sum ? ldc(&a.bsum[j0]) * a.xscale[j0] : a.b[j0]) : 0.0;
+        double l[16], t[16];  // L^-1_ii: row 16 q + c, columns 16 grp ..
+        const double* lp = a.Linv + (size_t)(i0 + 16 * q + c) * P + i0 + 16 * grp;
+#pragma unroll
+        for (int j = 0; j < 16; ++j) l[j] = ldc(lp + j);
+        const double* up = a.A + (size_t)(16 * q) * P + j0;  // U_0i: rows 16 q .., column `lane`
+#pragma unroll
+        for (int j = 0; j < 16; ++j) t[j] = i > 0 ? ldc(up + (size_t)j * P) : 0.0;
+        double acc = 0.0;  // minus this wave's share of sum_k (U_ki^T w_k)_lane
+        for (uint32_t kk = 0; kk < i; ++kk) {
+            double nx[16];
+            up += (size_t)kTile * P;
+            if (kk + 1 < i) {
+#pragma unroll
+                for (int j = 0; j < 16; ++j) nx[j] = ldc(up + (size_t)j * P);
+            } else {
+#pragma unroll
+                for (int j = 0; j < 16; ++j) nx[j] = 0.0;
             }
-            fold(acc);
+            double w = take(hw + kk * kTile + 16 * q, c, a.ctrl, g.timeout, min(i - kk, 8u));
+            settle(w);
+            dot_bcast(acc, w, t);
+#pragma unroll
+            for (int j = 0; j < 16; ++j) t[j] = nx[j];
         }
-        if (!ok) break;
-        // w_i = L^-1_ii r: thread (q, c) takes row c's columns 16 q .. 16 q + 15
-        double acc = 0.0;
-#pragma unroll 4
-        for (int j = 0; j < 16; ++j)
-            acc = fma(ldc(&a.Linv[(size_t)(i0 + c) * P + i0 + 16 * q + j]), rv[16 * q + j], acc);
-        part[q * kTile + c] = acc;
+        part[q * kTile + lane] = acc;
         __syncthreads();
-        if (threadIdx.x < (uint32_t)kTile && i0 + c < p)
-            stc(&yv[i0 + c], (part[c] + part[kTile + c]) + (part[2 * kTile + c] + part[3 * kTile + c]));
-        publish(&ff[i], 1u);
+        double r = -(b + ((part[lane] + part[kTile + lane]) + (part[2 * kTile + lane] + part[3 * kTile + lane])));
+        settle(r);
+        double w = 0.0;
+        dot_bcast(w, r, l);
+        w = over_groups(w);
+        if (grp == 0) stc(hw + i0 + 16 * q + c, w);
+        __syncthreads();  // part is free again
     }
     bool keep;
     const uint32_t slot = record_slot(a, k, &keep);
     bool nonfinite = false;
     const uint32_t nown = rank < nt ? (nt - 1 - rank) / g.size + 1 : 0u;
-    for (uint32_t o = nown; ok && o-- > 0;) {
-        const uint32_t i = rank + o * g.size, i0 = i * kTile;
-        if (threadIdx.x < (uint32_t)kTile) rv[c] = i0 + c < p ? ldc(&yv[i0 + c]) + ldc(&s_noise[i0 + c]) : 0.0;
-        __syncthreads();
-        for (uint32_t kk = nt - 1; ok && kk > i; --kk) {
-            if (!(ok = wait_row(&fb[kk]))) break;
-            // (U_i,kk beta_kk)_c: thread (q, c) takes row c's columns 16 q .. 16 q + 15
-            double acc = 0.0;
-#pragma unroll 4
-            for (int j = 0; j < 16; ++j) {
-                const uint32_t col = kk * kTile + 16 * q + j;
-                const double bv = col < p ? ldc(&a.beta[col]) : 0.0;
-                acc = fma(ldc(&a.A[(size_t)(i0 + c) * P + col]), bv, acc);
-            }
-            fold(acc);
-        }
-        if (!ok) break;
-        // beta_i = (L^-1_ii)^T r: thread (q, c) sums rows q, q + 4, ... of column c
-        double acc = 0.0;
-#pragma unroll 4
+    for (uint32_t o = nown; o-- > 0;) {
+        const uint32_t i = rank + o * g.size, i0 = i * kTile, j0 = i0 + lane;
+        const double ws = ldc(hw + j0) + (j0 < p ? ldc(&s_noise[j0]) : 0.0);
+        double l[16], t[16], acc[16];  // L^-1_ii: rows 16 grp .., column 16 q + c
+        const double* lp = a.Linv + (size_t)(i0 + 16 * grp) * P + i0 + 16 * q + c;
+#pragma unroll
+        for (int j = 0; j < 16; ++j) l[j] = ldc(lp + (size_t)j * P);
+        const double* row = a.A + (size_t)(i0 + 16 * q) * P + lane;  // U_ik: rows 16 q .., column `lane`
+#pragma unroll
         for (int j = 0; j < 16; ++j) {
-            const uint32_t r = q + 4 * j;
-            acc = fma(ldc(&a.Linv[(size_t)(i0 + r) * P + i0 + c]), rv[r], acc);
+            t[j] = i + 1 < nt ? ldc(row + (size_t)j * P + (nt - 1) * kTile) : 0.0;
+            acc[j] = 0.0;
         }
-        part[q * kTile + c] = acc;
+        for (uint32_t kk = nt - 1; kk > i; --kk) {
+            double nx[16];
+            if (kk - 1 > i) {
+#pragma unroll
+                for (int j = 0; j < 16; ++j) nx[j] = ldc(row + (size_t)j * P + (kk - 1) * kTile);
+            } else {
+#pragma unroll
+                for (int j = 0; j < 16; ++j) nx[j] = 0.0;
+            }
+            const double bv = take(hb + kk * kTile, lane, a.ctrl, g.timeout, min(kk - i, 8u));
+#pragma unroll
+            for (int j = 0; j < 16; ++j) {
+                acc[j] = fma(t[j], bv, acc[j]);
+                t[j] = nx[j];
+            }
+        }
+        // acc[j] summed over the lanes: each exchange halves the rows a lane keeps,
+        // so lane l ends with row l >> 2 of the wave's 16
+#pragma unroll
+        for (int st = 0; st < 4; ++st) {
+            const int off = 32 >> st, h = 8 >> st;
+            const bool up = (lane & off) != 0;
+#pragma unroll
+            for (int j = 0; j < h; ++j) {
+                const double send = up ? acc[j] : acc[j + h];
+                const double kept = up ? acc[j + h] : acc[j];
+                acc[j] = kept + __shfl_xor(send, off);
+            }
+        }
+        acc[0] += __shfl_xor(acc[0], 2);
+        acc[0] += __shfl_xor(acc[0], 1);
+        if ((lane & 3) == 0) part[16 * q + (lane >> 2)] = acc[0];
         __syncthreads();
-        if (threadIdx.x < (uint32_t)kTile && i0 + c < p) {
-            const uint32_t col = i0 + c;
-            const double bi = (part[c] + part[kTile + c]) + (part[2 * kTile + c] + part[3 * kTile + c]);
-            stc(&a.beta[col], bi);
+        double r = part[lane] - ws;  // minus the right-hand side
+        settle(r);
+        double bi = 0.0;
+        dot_bcast(bi, r, l);
+        bi = over_groups(bi);
+        const uint32_t col = i0 + 16 * q + c;
+        if (grp == 0) stc(hb + col, bi);
+        if (grp == 0 && col < p) {
+            a.beta[col] = bi;
             a.beta32[col] = (float)(bi * a.xscale[col]);
             if (!isfinite(bi)) nonfinite = true;
             if (keep) {
@@ -1087,11 +1141,11 @@ __device__ __forceinline__ void subst_solve(Args& a, Group& g, uint32_t rank, ui
                 if (a.ring_lam) a.ring_lam[(size_t)slot * p + col] = ldc(&a.lam_m2[col]);
             }
         }
-        publish(&fb[i], 1u);
+        __syncthreads();  // part is free again
     }
     if (nonfinite) atomicOr(&a.ctrl->err, kErrNonFinite);
     if (keep && rank == 0 && threadIdx.x == 0) a.ring_tau[slot] = current_tau(a);
-    // no block leaves before every flag it may wait on is up: the launch's
+    // no block leaves before every value it may wait on is there: the launch's
     // closing block clears them after this barrier
     group_sync(g);
 }
@@ -1286,10 +1340,13 @@ __device__ __forceinline__ void pside_role(Args& a, uint32_t rank, uint32_t k, d
         }
         if (a.x.p > (uint32_t)kSmallP && (a.mode & kModeBeta) && !(a.mode & kModePost)) {
             const uint32_t nt = padded(a.x.p) / kTile;
-            // tile versions, and the substitution's row flags after them
-            const uint32_t nver = 2 * nt * nt + (a.subst ? 2 * nt : 0u);
-            for (uint32_t e = threadIdx.x; e < nver; e += kThreads) a.ver[e] = 0u;
+            for (uint32_t e = threadIdx.x; e < 2 * nt * nt; e += kThreads) a.ver[e] = 0u;
             if (threadIdx.x == 0) a.ctrl->task_next = 0u;
+        }
+        if (a.subst && (a.mode & kModeBeta) && !(a.mode & kModePre)) {
+            const uint32_t P = padded(a.x.p);
+            for (uint32_t e = threadIdx.x; e < 2 * P; e += kThreads)
+                stc(handoff(a) + e, __longlong_as_double((long long)kNotReady));
         }
         if (a.mode & (kModeZ | kModeBsum)) {
             // every block of the group has read b's accumulator (before the
