@@ -180,6 +180,7 @@ struct SweepArgs {
     HSP_GLOBAL const uint32_t* row_id;  // original index of each stored row (rows reordered), or null
     HSP_GLOBAL PackQ* zq;  // the pack's shared z queue, or null (then gz blocks of its own)
     uint32_t subst;        // tile path: beta by blocked substitution (factorisation without L^-1)
+    uint32_t help;         // p-side blocks take z-pass units once the factorisation has none for them
 };
 
 // ---- the shared z queue of a pack -----------------------------------------------

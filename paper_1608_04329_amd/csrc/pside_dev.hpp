@@ -1150,35 +1150,43 @@ __device__ __forceinline__ void subst_solve(Args& a, Group& g, uint32_t rank, ui
     group_sync(g);
 }
 
-__device__ __forceinline__ void tile_path(Args& a, Group& g, uint32_t rank, uint32_t k, double* lds) {
-    const uint32_t p = a.x.p, P = padded(p);
+// The part of the tile path before b is needed: lambda, tau, nu, xi, the noise of
+// beta and the factorisation's tasks.  False if the factorisation failed.
+__device__ __forceinline__ bool tile_factor(Args& a, Group& g, uint32_t rank, uint32_t k, double* lds) {
+    const uint32_t p = a.x.p;
     Tile& S = *reinterpret_cast<Tile*>(lds);
     Tile& T = *reinterpret_cast<Tile*>(lds + kTile * kTileLd);
     double* flag = lds + 2 * kTile * kTileLd - 1;  // T's unused padding corner
     double* s_noise = a.vec + p;
-    bool ok = true;
-    if (!(a.mode & kModePost)) {
-        const double tau = hyper_lambda_tau(a, k, rank == 0, lds);
-        group_sync(g);  // lambda^-2 and the new tau^-2 in memory
-        if (rank == g.size - 1) {
-            if (a.mode & kModeNuXi) hyper_nu_xi(a, k);
-            if (a.mode & kModeBeta)
-                for (uint32_t i = threadIdx.x; i < p; i += kThreads) {
-                    const Words4 w = draw_words(a.seed, i, k, kTagBetaS, 0, a.chain);
-                    stc(&s_noise[i], box_muller_d(u01d(w.w0), u01d(w.w1)));
-                }
-        }
-        if (a.mode & kModeBeta) {
-            // Factorisation of [Q | I]: U in A (upper), L^-1 = U^-T in Linv
-            // (lower), as this block's list of tile tasks.
-            ok = run_tasks(a, g, rank, tau, S, T, flag);
-            group_sync(g);
-            ok = ok && !group_failed(g, flag);
-        }
-    } else {
-        // an earlier launch of this sweep drew lambda, tau, nu, xi and the
-        // noise of beta and factored Q; its failure flags are in memory
-        ok = !group_failed(g, flag);
+    // with kModePost an earlier launch of this sweep did all this
+    if (a.mode & kModePost) return true;
+    const double tau = hyper_lambda_tau(a, k, rank == 0, lds);
+    group_sync(g);  // lambda^-2 and the new tau^-2 in memory
+    if (rank == g.size - 1) {
+        if (a.mode & kModeNuXi) hyper_nu_xi(a, k);
+        if (a.mode & kModeBeta)
+            for (uint32_t i = threadIdx.x; i < p; i += kThreads) {
+                const Words4 w = draw_words(a.seed, i, k, kTagBetaS, 0, a.chain);
+                stc(&s_noise[i], box_muller_d(u01d(w.w0), u01d(w.w1)));
+            }
+    }
+    if (!(a.mode & kModeBeta)) return true;
+    // Factorisation of [Q | I]: U in A (upper), L^-1 = U^-T in Linv (lower), as
+    // this block's list of tile tasks.
+    return run_tasks(a, g, rank, tau, S, T, flag);
+}
+
+// The rest of the tile path, from the factorisation (ok: this block's part of
+// it succeeded) and b to beta.
+__device__ __forceinline__ void tile_beta(Args& a, Group& g, uint32_t rank, uint32_t k, double* lds, bool ok) {
+    const uint32_t p = a.x.p, P = padded(p);
+    double* flag = lds + 2 * kTile * kTileLd - 1;
+    double* s_noise = a.vec + p;
+    if (a.mode & kModePost) {
+        ok = !group_failed(g, flag);  // the earlier launch's failure flags are in memory
+    } else if (a.mode & kModeBeta) {
+        group_sync(g);
+        ok = ok && !group_failed(g, flag);
     }
     if (a.mode & kModePre) return;  // b is taken by a later launch of this sweep
 
@@ -1308,9 +1316,10 @@ __device__ __forceinline__ void tile_path(Args& a, Group& g, uint32_t rank, uint
     }
 }
 
-// The whole p-side role of block `rank` of the group.
-__device__ __forceinline__ void pside_role(Args& a, uint32_t rank, uint32_t k, double* lds) {
-    Group g;
+// The p-side role of block `rank` of the group, in two parts: all that comes
+// before b, and the rest.  Between them the block may take units of the z pass.
+// pside_begin returns false if the factorisation failed.
+__device__ __forceinline__ bool pside_begin(Args& a, Group& g, uint32_t rank, uint32_t k, double* lds) {
     g.trace = a.trace ? a.trace + (size_t)rank * kTraceSlots : nullptr;
     if (g.trace && threadIdx.x == 0) g.trace[0] = wall_clock64();
     g.ctrl = a.ctrl;
@@ -1323,11 +1332,13 @@ __device__ __forceinline__ void pside_role(Args& a, uint32_t rank, uint32_t k, d
     g.timeout = a.timeout_ticks;
     // the two-launch split is for the tile path; a launch never asks the
     // one-block path for half a sweep
-    if (a.x.p <= (uint32_t)kSmallP) {
-        if (!(a.mode & (kModePre | kModePost))) small_path(a, g, k, lds);
-    } else {
-        tile_path(a, g, rank, k, lds);
-    }
+    if (a.x.p > (uint32_t)kSmallP) return tile_factor(a, g, rank, k, lds);
+    if (!(a.mode & (kModePre | kModePost))) small_path(a, g, k, lds);
+    return true;
+}
+
+__device__ __forceinline__ void pside_end(Args& a, Group& g, uint32_t rank, uint32_t k, double* lds, bool ok) {
+    if (a.x.p > (uint32_t)kSmallP) tile_beta(a, g, rank, k, lds, ok);
     // the last barrier above was passed by every block of the group, and the
     // z-pass blocks have all finished if they ran: close the launch
     if (rank == 0) {

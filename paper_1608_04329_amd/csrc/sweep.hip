@@ -37,8 +37,28 @@ __device__ __forceinline__ void run_block(Args& a, double* lds) {
         if (b == a.idle) return;
         if (b > a.idle) --b;
     }
-    if (b < a.gp) pside_role(a, b, k, lds);
-    else zpass_role<XT, KC, R, WIDE>(a, b - a.gp, a.gz, k, lds);
+    const bool pside = b < a.gp;
+    if (!pside && b - a.gp >= a.gz) return;  // no z-pass work in this launch
+    Group g;
+    bool ok = true, z = !pside;
+    if (pside) {
+        ok = pside_begin(a, g, b, k, lds);
+        // a block whose factorisation work is done may take units of the z pass:
+        // the group's next barrier, which every reader of b passes, covers its
+        // additions, and the z-pass blocks' own count is not touched
+        z = a.help && b > 0 && (a.mode & kModeZ) && (a.mode & kModeBeta);
+        __syncthreads();
+    }
+    if (z) {
+        ZSums<XT, KC> sums;
+        const bool any = z_take<XT, KC, R, WIDE>(a, b - a.gp, a.gz, pside, k, lds, sums);
+        if (!pside) {
+            z_finish<XT, KC, WIDE>(a, b - a.gp, a.gz, lds, sums);
+            return;
+        }
+        if (any) z_flush<XT, KC, WIDE>(a, sums.b, sums.maxatt, sums.capped, lds);
+    }
+    pside_end(a, g, b, k, lds, ok);
 }
 
 // KC: 16-byte chunks per lane of a wave (of the whole row, or with WIDE of
@@ -170,6 +190,13 @@ void sweep_finish_args(SweepArgs* a, const SweepPlan& plan) {
         a->gz -= 1u;
         a->idle = plan.cus;
     }
+    // A group of more than a quarter of the device leaves the z pass too few blocks
+    // to end with it: its blocks (but not block 0, which finishes last) then take
+    // z-pass units when the factorisation has no task left for them.  N = 2e5,
+    // p = 4096 float32 (384 of 512 blocks): the z pass ends at 1622 instead of
+    // 2329 us, 2.51 -> 1.82 ms per sweep.  Smaller groups stay out: they would find
+    // little left, and looking costs a short sweep 2 % (N = 1e5, p = 100).
+    a->help = 4u * a->gp > (uint32_t)plan.capacity ? 1u : 0u;
     a->zgroups = (a->gz + kZGroup - 1) / kZGroup;
     a->z_static_pct = plan.static_pct;
     a->z_unit = plan.unit;

@@ -254,76 +254,99 @@ __device__ __forceinline__ void z_tile(Args& a, uint32_t t, uint32_t ksweep,
         }
 }
 
-// The z-pass role of the sweep kernel: block zrank of nz z-pass blocks.
-// Short rows (WIDE false, see wide_chunks): each wave holds whole rows,
-// KC chunks per lane, and takes tiles on its own.  Wider rows (WIDE): the
-// block's four waves split every row into quarters of KC chunks per lane
-// and take each tile together; their partial dot products meet in LDS and
-// are added in wave order, so every wave holds the same eta and draws the
-// same z, and each wave sums x_i^T z_i over its own quarter of the columns.
-template <int XT, int KC, int R, bool WIDE = false>
-__device__ __forceinline__ void zpass_role(Args& a, uint32_t zrank, uint32_t nz,
-                                           uint32_t ksweep, double* red) {
-    if (zrank >= nz) return;  // no z-pass work in this launch
+// A block's sums over the z-pass tiles it has worked on.
+template <int XT, int KC>
+struct ZSums {
+    double b[KC][XTraits<XT>::VEC];  // sums of x_ij z_i on this lane's columns
+    uint32_t maxatt;                 // most proposals of a row
+    bool capped;                     // a row reached the proposal cap
+};
+
+// The tiles of the z pass that this block takes.  Short rows (WIDE false, see
+// wide_chunks): each wave holds whole rows, KC chunks per lane, and takes tiles
+// on its own.  Wider rows (WIDE): the block's four waves split every row into
+// quarters of KC chunks per lane and take each tile together; their partial dot
+// products meet in LDS and are added in wave order, so every wave holds the same
+// eta and draws the same z, and each wave sums x_i^T z_i over its own quarter of
+// the columns.
+//
+// A share of the tiles is dealt out statically, interleaved over all waves (WIDE:
+// blocks) of the nz z-pass blocks; the rest go out in units of z_unit tiles to
+// whichever block asks next, so blocks on busier CUs do less of them.  Thread 0
+// reserves the next unit before the block works on the current one.  helper: a
+// block that is none of the nz takes units only.  One loop for both, so that
+// the tile's code is there once.  Returns whether the block got any tile.
+template <int XT, int KC, int R, bool WIDE>
+__device__ __forceinline__ bool z_take(Args& a, uint32_t zrank, uint32_t nz, bool helper, uint32_t ksweep, double* red,
+                                       ZSums<XT, KC>& z) {
     constexpr int VEC = XTraits<XT>::VEC;
     constexpr int CW = kWave * VEC;  // columns covered by one wave-wide 16-byte load
-
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = threadIdx.x / kWave;
     const uint32_t ld = a.x.ld;
-    const uint32_t N = a.x.N;
     const uint32_t c0 = WIDE ? (uint32_t)wave * KC * CW : 0u;  // first column of this wave's part
-
     float bl[KC][VEC];
-    double bacc[KC][VEC];
 #pragma unroll
     for (int kc = 0; kc < KC; ++kc)
 #pragma unroll
         for (int e = 0; e < VEC; ++e) {
             const uint32_t col = c0 + kc * CW + lane * VEC + e;
             bl[kc][e] = col < ld ? a.beta32[col] : 0.0f;
-            bacc[kc][e] = 0.0;
+            z.b[kc][e] = 0.0;
         }
-
-    const uint32_t n_tiles = (N + R - 1) / R;
-    // tiles are taken by waves, or for wide rows by whole blocks
-    const uint32_t W = WIDE ? nz : nz * kWPB;
-    uint32_t maxatt = 0;
-    bool capped = false;
-    uint32_t parity = 0;                // wide rows: LDS slot of the next tile's partial sums
-    double* eta_lds = red + 8;          // [2][kWPB][R], after the unit slot
-
-    auto tile = [&](uint32_t t) {
-        z_tile<XT, KC, R, WIDE>(a, t, ksweep, bl, bacc, maxatt, capped, parity, eta_lds);
-    };
-
-    // A share of the tiles is dealt out statically, interleaved over all
-    // waves; the rest go out in units of z_unit tiles to whichever block asks
-    // next, so blocks on busier CUs do less of them.  Thread 0 reserves the
-    // next unit before working on the current one.
-    const uint32_t unit = a.z_unit;
-    const uint32_t n_static = (uint32_t)((uint64_t)n_tiles * a.z_static_pct / 100 / W * W);
-    for (uint32_t t = WIDE ? zrank : zrank * kWPB + wave; t < n_static; t += W) tile(t);
-    if (n_static < n_tiles) {
-        const uint32_t n_units = (n_tiles - n_static + unit - 1) / unit;
-        double* slot = red;  // free until the reduction below
-        if (threadIdx.x == 0) *slot = (double)atomicAdd(&a.ctrl->z_next, 1u);
-        __syncthreads();
-        uint32_t u = (uint32_t)*slot;
-        __syncthreads();
-        while (u < n_units) {
-            uint32_t next = 0;
-            if (threadIdx.x == 0) next = atomicAdd(&a.ctrl->z_next, 1u);
-            for (uint32_t j = WIDE ? 0u : (uint32_t)wave; j < unit; j += WIDE ? 1u : (uint32_t)kWPB) {
-                const uint32_t t = n_static + u * unit + j;
-                if (t < n_tiles) tile(t);
+    z.maxatt = 0;
+    z.capped = false;
+    uint32_t parity = 0;        // wide rows: LDS slot of the next tile's partial sums
+    double* eta_lds = red + 8;  // [2][kWPB][R], after the unit slot
+    double* slot = red;
+    const uint32_t n_tiles = (a.x.N + R - 1) / R, unit = a.z_unit;
+    const uint32_t W = WIDE ? nz : nz * kWPB, step = WIDE ? 1u : (uint32_t)kWPB;
+    const uint32_t rounds = (uint32_t)((uint64_t)n_tiles * a.z_static_pct / 100 / W), n_static = rounds * W;
+    const uint32_t n_units = (n_tiles - n_static + unit - 1) / unit;
+    uint32_t left = helper ? 0u : rounds;  // static tiles still to come
+    uint32_t t = WIDE ? zrank : zrank * kWPB + wave, j = unit, u = 0, next = 0;
+    bool any = left > 0, first = true;
+    for (;;) {
+        uint32_t now;
+        if (left > 0) {
+            now = t;
+            t += W;
+            --left;
+        } else {
+            if (j >= unit) {  // the next unit
+                if (threadIdx.x == 0) *slot = (double)(first ? atomicAdd(&a.ctrl->z_next, 1u) : next);
+                __syncthreads();
+                u = (uint32_t)*slot;
+                __syncthreads();
+                if (u >= n_units) break;
+                any = true;
+                first = false;
+                if (threadIdx.x == 0) next = atomicAdd(&a.ctrl->z_next, 1u);
+                j = WIDE ? 0u : (uint32_t)wave;
+                if (j >= unit) continue;
             }
-            if (threadIdx.x == 0) *slot = (double)next;
-            __syncthreads();
-            u = (uint32_t)*slot;
-            __syncthreads();
+            now = n_static + u * unit + j;
+            j += step;
+            if (now >= n_tiles) continue;
         }
+        z_tile<XT, KC, R, WIDE>(a, now, ksweep, bl, z.b, z.maxatt, z.capped, parity, eta_lds);
     }
+    return any;
+}
+
+// Block zrank of the nz z-pass blocks has done its tiles: its proposal
+// statistics, and its sums into b's accumulator.
+template <int XT, int KC, bool WIDE>
+__device__ __forceinline__ void z_finish(Args& a, uint32_t zrank, uint32_t nz, double* red, ZSums<XT, KC>& z) {
+    constexpr int VEC = XTraits<XT>::VEC;
+    constexpr int CW = kWave * VEC;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = threadIdx.x / kWave;
+    const uint32_t ld = a.x.ld;
+    const uint32_t c0 = WIDE ? (uint32_t)wave * KC * CW : 0u;
+    auto& bacc = z.b;
+    const uint32_t maxatt = z.maxatt;
+    const bool capped = z.capped;
 
     // wave statistics
     uint32_t m = maxatt;
@@ -413,19 +436,28 @@ __device__ __forceinline__ void zpass_role(Args& a, uint32_t zrank, uint32_t nz,
 }
 
 
-// A queue worker leaves chain a: the float64 sums of x_ij z_i over the units
-// it finished there (each wave's, added in wave order) go into the chain's b
-// accumulator, then its proposal statistics; once those additions are
-// complete, the unit count goes into the chain's z_count.
-template <int XT, int KC>
-__device__ __forceinline__ void zq_flush(Args& a, double (&bacc)[KC][XTraits<XT>::VEC], uint32_t& maxatt,
-                                         bool& capped, uint32_t units, double* red) {
+// A block leaves chain a: the float64 sums of x_ij z_i over the units it
+// finished there (each wave's, added in wave order, or for wide rows each wave's
+// own columns) go into the chain's b accumulator, then its proposal statistics.
+template <int XT, int KC, bool WIDE>
+__device__ __forceinline__ void z_flush(Args& a, double (&bacc)[KC][XTraits<XT>::VEC], uint32_t& maxatt,
+                                        bool& capped, double* red) {
     constexpr int VEC = XTraits<XT>::VEC;
     constexpr int CW = kWave * VEC;
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = threadIdx.x / kWave;
     const uint32_t ld = a.x.ld;
-    for (uint32_t seg = 0; seg < ld; seg += kRedCols) {
+    if constexpr (WIDE) {
+#pragma unroll
+        for (int kc = 0; kc < KC; ++kc)
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) {
+                const uint32_t col = ((uint32_t)wave * KC + kc) * CW + lane * VEC + e;
+                if (col < ld)
+                    __hip_atomic_fetch_add(&a.bsum[col], bacc[kc][e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+    }
+    for (uint32_t seg = 0; !WIDE && seg < ld; seg += kRedCols) {
 #pragma unroll
         for (int kc = 0; kc < KC; ++kc)
 #pragma unroll
@@ -456,9 +488,6 @@ __device__ __forceinline__ void zq_flush(Args& a, double (&bacc)[KC][XTraits<XT>
     }
     maxatt = 0;
     capped = false;
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-    if (threadIdx.x == 0) atomicAdd(&a.ctrl->z_count, (unsigned long long)units);
 }
 
 // A worker block of a pack's shared z queue (rows of one wave each): the
@@ -516,7 +545,11 @@ __device__ __forceinline__ void zqueue_role(const SweepArgs* const* tab, uint32_
                 u = (uint32_t)red[0];
                 __syncthreads();
             }
-            zq_flush<XT, KC>(a, bacc, maxatt, capped, finished, red);
+            z_flush<XT, KC, false>(a, bacc, maxatt, capped, red);
+            // once those additions are complete, the chain's p-side may count them
+            __builtin_amdgcn_s_waitcnt(0);
+            __syncthreads();
+            if (threadIdx.x == 0) atomicAdd(&a.ctrl->z_count, (unsigned long long)finished);
         }
         // the chain with most units left, the first of equals; a claim that
         // comes too late only sends the block back here
