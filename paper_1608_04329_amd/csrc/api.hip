@@ -110,6 +110,7 @@ struct hsp_state {
     float* zdbg = nullptr;
     int32_t* adbg = nullptr;
     double *ring_beta = nullptr, *ring_tau = nullptr, *ring_lam = nullptr;
+    double* fetch = nullptr;   // kFetchDoubles: small hsp_draws, gathered for one copy
     SweepPlan plan{};
     uint64_t timeout_ticks = 0;
     uint64_t sweeps_done = 0;  // host mirror of ctrl->sweep
@@ -229,22 +230,26 @@ hipError_t enqueue_sweep(hsp_state* s, hipStream_t st) {
     return sweep_launch(h, s->dtab, s->plan, st);
 }
 
-hsp_status check_device_flags(hsp_state* s) {
-    Ctrl c;
-    HIP_TRY(hipMemcpy(&c, s->ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost));
-    if (c.err & kErrNotPD) {
+hsp_status flag_status(hsp_state* s, uint32_t err, int32_t chol_info, uint32_t sweep) {
+    if (err & kErrNotPD) {
         char buf[160];
         std::snprintf(buf, sizeof buf,
                       "X^T X + tau^-2 Lambda^-2 is not positive definite (pivot %d) at sweep %u",
-                      c.chol_info, c.sweep + 1);
+                      chol_info, sweep + 1);
         return fail(s, HSP_ENOTPD, buf);
     }
-    if (c.err & kErrTnCap)
+    if (err & kErrTnCap)
         return fail(s, HSP_ERANGE, "a truncated-normal row reached the proposal cap (non-finite X beta)");
-    if (c.err & kErrNonFinite) return fail(s, HSP_ERANGE, "a draw of beta, lambda or tau was not finite");
-    if (c.err & kErrTimeout)
+    if (err & kErrNonFinite) return fail(s, HSP_ERANGE, "a draw of beta, lambda or tau was not finite");
+    if (err & kErrTimeout)
         return fail(s, HSP_EHIP, "a bounded wait inside the sweep kernel timed out");
     return HSP_OK;
+}
+
+hsp_status check_device_flags(hsp_state* s) {
+    Ctrl c;
+    HIP_TRY(hipMemcpy(&c, s->ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost));
+    return flag_status(s, c.err, c.chol_info, c.sweep);
 }
 
 hsp_status sync_state(hsp_state* s) {
@@ -266,7 +271,7 @@ void free_state(hsp_state* s) {
     }
     void* bufs[] = {s->Xbuf, s->xexp, s->xscale, s->y, s->ctrl, s->beta, s->lam, s->nu, s->tau, s->xi, s->b, s->G, s->Gp,
                     s->A, s->Linv, s->vec, s->partial, s->beta32, s->zdbg, s->adbg,
-                    s->ring_beta, s->ring_tau, s->ring_lam, s->trace, s->bsum,
+                    s->ring_beta, s->ring_tau, s->ring_lam, s->fetch, s->trace, s->bsum,
                     s->zgrp_count, s->dargs, s->dtab, s->tasks, s->task_off, s->ver, s->row_id};
     for (void* p : bufs)
         if (p) (void)hipFree(p);
@@ -1892,16 +1897,38 @@ hsp_status hsp_draws(hsp_state* s, double* beta, double* tau_m2, double* lam_m2,
                      int64_t count, int64_t* n_out) {
     if (!s) return HSP_EINVAL;
     if (s->poisoned) return HSP_EPOISONED;
-    hsp_status st = sync_state(s);
-    if (st) return st;
     const int64_t recorded = (int64_t)((s->sweeps_done - s->draw_base) / (uint64_t)s->opt.thin);
-    if (n_out) *n_out = recorded;
-    if (count == 0) return HSP_OK;
-    if (first < 0 || count < 0 || first + count > recorded || first < recorded - s->opt.max_draws)
-        return fail(s, HSP_EINVAL, "requested draws are not stored (range or overwritten)");
-    if (lam_m2 && !s->ring_lam) return fail(s, HSP_EINVAL, "lambda was not recorded");
     const int64_t cap = s->opt.max_draws;
     const size_t p = s->x.p;
+    const bool stored = count > 0 && first >= 0 && first <= recorded - count && first >= recorded - cap;
+    const size_t per = (beta ? p : 0) + (tau_m2 ? 1 : 0) + (lam_m2 ? p : 0);
+    if (stored && (!lam_m2 || s->ring_lam) && (size_t)count <= kFetchDoubles / (per + 1)) {
+        // a few draws: one kernel gathers them behind the failure flags, one copy
+        // waits for it and brings all (each copy costs the host 12-16 us; as a
+        // synchronisation, the flags and two or three copies: 48 us for 8 draws of
+        // p = 10, now 21)
+        if (!s->fetch) HIP_TRY(dalloc(&s->fetch, kFetchDoubles));
+        std::vector<double> host(kFetchHead + (size_t)count * per);
+        HIP_TRY(fetch_draws_launch(s->ctrl, beta ? s->ring_beta : nullptr, tau_m2 ? s->ring_tau : nullptr,
+                                   lam_m2 ? s->ring_lam : nullptr, (uint32_t)p, (uint32_t)(first % cap), (uint32_t)cap,
+                                   (uint32_t)count, s->fetch, s->stream));
+        HIP_TRY(hipMemcpyAsync(host.data(), s->fetch, host.size() * 8, hipMemcpyDeviceToHost, s->stream));
+        HIP_TRY(hipStreamSynchronize(s->stream));
+        hsp_status st = flag_status(s, (uint32_t)host[0], (int32_t)host[1], (uint32_t)host[2]);
+        if (st) return st;
+        if (n_out) *n_out = recorded;
+        const double* src = host.data() + kFetchHead;
+        if (beta) std::memcpy(beta, src, count * p * 8), src += count * p;
+        if (tau_m2) std::memcpy(tau_m2, src, count * 8), src += count;
+        if (lam_m2) std::memcpy(lam_m2, src, count * p * 8);
+        return HSP_OK;
+    }
+    hsp_status st = sync_state(s);
+    if (st) return st;
+    if (n_out) *n_out = recorded;
+    if (count == 0) return HSP_OK;
+    if (!stored) return fail(s, HSP_EINVAL, "requested draws are not stored (range or overwritten)");
+    if (lam_m2 && !s->ring_lam) return fail(s, HSP_EINVAL, "lambda was not recorded");
     for (int64_t d = first; d < first + count;) {
         const int64_t slot = d % cap;
         const int64_t run = std::min(first + count - d, cap - slot);

@@ -490,6 +490,23 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(XLayout x, const uint3
     }
 }
 
+__global__ __launch_bounds__(256) void fetch_draws_kernel(const Ctrl* __restrict__ ctrl, const double* __restrict__ rb,
+                                                          const double* __restrict__ rt, const double* __restrict__ rl,
+                                                          uint32_t p, uint32_t first, uint32_t cap, uint32_t count,
+                                                          double* __restrict__ out) {
+    const uint32_t i = blockIdx.x * 256u + threadIdx.x, nb = rb ? count * p : 0u, nt = rt ? count : 0u;
+    if (i == 0) {
+        out[0] = (double)ctrl->err;
+        out[1] = (double)ctrl->chol_info;
+        out[2] = (double)ctrl->sweep;
+    }
+    if (i >= nb + nt + (rl ? count * p : 0u)) return;
+    const bool tau = i >= nb && i < nb + nt;
+    const uint32_t e = i < nb ? i : tau ? (i - nb) * p : i - nb - nt;  // draw e / p, coordinate e % p
+    const size_t slot = (first + e / p) % cap;
+    out[kFetchHead + i] = tau ? rt[slot] : (i < nb ? rb : rl)[slot * p + e % p];
+}
+
 // Read ceiling: stream `bytes` (a multiple of 16) with eight 16-byte
 // non-temporal loads in flight per lane, grid-stride, the same kind of load
 // as the z pass, and nothing else.
@@ -512,6 +529,15 @@ __global__ __launch_bounds__(256) void stream_read_kernel(const RdVec* __restric
         s += __uint_as_float(v.x ^ v.y ^ v.z ^ v.w);
     }
     if (s == -1.0f) sink[0] = s;  // never true for the sums of finite data; keeps the loads
+}
+
+hipError_t fetch_draws_launch(const Ctrl* ctrl, const double* ring_beta, const double* ring_tau, const double* ring_lam,
+                              uint32_t p, uint32_t first, uint32_t capacity, uint32_t count, double* out,
+                              hipStream_t st) {
+    const uint32_t n = (ring_beta ? count * p : 0u) + (ring_tau ? count : 0u) + (ring_lam ? count * p : 0u);
+    hipLaunchKernelGGL(fetch_draws_kernel, dim3(n / 256 + 1), dim3(256), 0, st, ctrl, ring_beta, ring_tau, ring_lam, p,
+                       first, capacity, count, out);
+    return hipGetLastError();
 }
 
 hipError_t stream_read_launch(const void* x, size_t bytes, int num_cus, float* sink, hipStream_t st) {

@@ -376,6 +376,16 @@ hipError_t row_key_launch(const XLayout& x, const float* beta32, const uint8_t* 
 hipError_t gather_rows_launch(const XLayout& x, const uint32_t* perm, void* Xo, const uint8_t* y, uint8_t* yo,
                               const uint32_t* id, uint32_t* ido, hipStream_t st);
 
+// The failure flags, the failed pivot and the sweep count (as doubles; whole
+// numbers below 2^53) into out[0 .. 2], then from out[kFetchHead] `count` draws
+// of the rings from slot first on (wrapping at capacity): beta, tau^-2, lambda^-2,
+// each skipped if its ring is null.  Up to kFetchDoubles doubles in all, beyond
+// which the copies outweigh the calls.
+constexpr size_t kFetchHead = 4, kFetchDoubles = 8192;
+hipError_t fetch_draws_launch(const Ctrl* ctrl, const double* ring_beta, const double* ring_tau, const double* ring_lam,
+                              uint32_t p, uint32_t first, uint32_t capacity, uint32_t count, double* out,
+                              hipStream_t st);
+
 // Stream `bytes` of x with plain 16-byte loads only (the read ceiling).
 hipError_t stream_read_launch(const void* x, size_t bytes, int num_cus, float* sink, hipStream_t st);
 
