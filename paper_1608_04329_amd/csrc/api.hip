@@ -110,7 +110,7 @@ struct hsp_state {
     float* zdbg = nullptr;
     int32_t* adbg = nullptr;
     double *ring_beta = nullptr, *ring_tau = nullptr, *ring_lam = nullptr;
-    double* fetch = nullptr;   // kFetchDoubles: small hsp_draws, gathered for one copy
+    double* fetch = nullptr;   // kFetchDoubles of pinned host memory that small hsp_draws are gathered into
     SweepPlan plan{};
     uint64_t timeout_ticks = 0;
     uint64_t sweeps_done = 0;  // host mirror of ctrl->sweep
@@ -271,10 +271,11 @@ void free_state(hsp_state* s) {
     }
     void* bufs[] = {s->Xbuf, s->xexp, s->xscale, s->y, s->ctrl, s->beta, s->lam, s->nu, s->tau, s->xi, s->b, s->G, s->Gp,
                     s->A, s->Linv, s->vec, s->partial, s->beta32, s->zdbg, s->adbg,
-                    s->ring_beta, s->ring_tau, s->ring_lam, s->fetch, s->trace, s->bsum,
+                    s->ring_beta, s->ring_tau, s->ring_lam, s->trace, s->bsum,
                     s->zgrp_count, s->dargs, s->dtab, s->tasks, s->task_off, s->ver, s->row_id};
     for (void* p : bufs)
         if (p) (void)hipFree(p);
+    if (s->fetch) (void)hipHostFree(s->fetch);
     if (s->streamed) {
         // s->Xbuf is null for a streamed state: X lives in Xhost and the stages
         if (s->Xhost) (void)hipHostFree(s->Xhost);
@@ -1902,22 +1903,23 @@ hsp_status hsp_draws(hsp_state* s, double* beta, double* tau_m2, double* lam_m2,
     const size_t p = s->x.p;
     const bool stored = count > 0 && first >= 0 && first <= recorded - count && first >= recorded - cap;
     const size_t per = (beta ? p : 0) + (tau_m2 ? 1 : 0) + (lam_m2 ? p : 0);
-    if (stored && (!lam_m2 || s->ring_lam) && (size_t)count <= kFetchDoubles / (per + 1)) {
-        // a few draws: one kernel gathers them behind the failure flags, one copy
-        // waits for it and brings all (each copy costs the host 12-16 us; as a
-        // synchronisation, the flags and two or three copies: 48 us for 8 draws of
-        // p = 10, now 21)
-        if (!s->fetch) HIP_TRY(dalloc(&s->fetch, kFetchDoubles));
-        std::vector<double> host(kFetchHead + (size_t)count * per);
+    if (stored && (!lam_m2 || s->ring_lam) && (size_t)count * per <= kFetchDoubles - kFetchHead) {
+        // a few draws: one kernel writes them, behind the failure flags, straight
+        // into pinned host memory (launch and wait: 11-12 us up to 64 KB; each
+        // copy into pageable memory takes 12-180 us)
+        if (!s->fetch)
+            HIP_TRY(hipHostMalloc(reinterpret_cast<void**>(&s->fetch), kFetchDoubles * 8, hipHostMallocDefault));
+        void* dev = nullptr;
+        HIP_TRY(hipHostGetDevicePointer(&dev, s->fetch, 0));
         HIP_TRY(fetch_draws_launch(s->ctrl, beta ? s->ring_beta : nullptr, tau_m2 ? s->ring_tau : nullptr,
                                    lam_m2 ? s->ring_lam : nullptr, (uint32_t)p, (uint32_t)(first % cap), (uint32_t)cap,
-                                   (uint32_t)count, s->fetch, s->stream));
-        HIP_TRY(hipMemcpyAsync(host.data(), s->fetch, host.size() * 8, hipMemcpyDeviceToHost, s->stream));
+                                   (uint32_t)count, static_cast<double*>(dev), s->stream));
         HIP_TRY(hipStreamSynchronize(s->stream));
+        const double* host = s->fetch;
         hsp_status st = flag_status(s, (uint32_t)host[0], (int32_t)host[1], (uint32_t)host[2]);
         if (st) return st;
         if (n_out) *n_out = recorded;
-        const double* src = host.data() + kFetchHead;
+        const double* src = host + kFetchHead;
         if (beta) std::memcpy(beta, src, count * p * 8), src += count * p;
         if (tau_m2) std::memcpy(tau_m2, src, count * 8), src += count;
         if (lam_m2) std::memcpy(lam_m2, src, count * p * 8);

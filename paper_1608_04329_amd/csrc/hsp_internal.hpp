@@ -380,7 +380,7 @@ hipError_t gather_rows_launch(const XLayout& x, const uint32_t* perm, void* Xo, 
 // numbers below 2^53) into out[0 .. 2], then from out[kFetchHead] `count` draws
 // of the rings from slot first on (wrapping at capacity): beta, tau^-2, lambda^-2,
 // each skipped if its ring is null.  Up to kFetchDoubles doubles in all, beyond
-// which the copies outweigh the calls.
+// which plain copies take the draws.
 constexpr size_t kFetchHead = 4, kFetchDoubles = 8192;
 hipError_t fetch_draws_launch(const Ctrl* ctrl, const double* ring_beta, const double* ring_tau, const double* ring_lam,
                               uint32_t p, uint32_t first, uint32_t capacity, uint32_t count, double* out,
