@@ -757,7 +757,7 @@ hsp_status stream_args(hsp_state* s, uint32_t mode) {
         h.idle = 0;
         const uint32_t tiles = (rows + s->plan.rows - 1) / s->plan.rows;
         h.gz = std::max<uint32_t>(1, std::min<uint32_t>(s->plan.gz, (tiles + 3) / 4));
-        h.zgroups = (h.gz + kZGroup - 1) / kZGroup;
+        h.zgroups = z_groups(h.gz);
         s->sd_host[c] = h;
     }
     const uint32_t pmode = (mode & ~kModeZ) | ((mode & kModeZ) ? kModeBsum : 0u);
@@ -1319,7 +1319,7 @@ hsp_status plan_packs(hsp_batch* b) {
             h.gz = pk.gz[j];
             h.z_static_pct = kZStaticPctDefault;
             h.z_unit = kZUnitDefault;
-            h.zgroups = (h.gz + kZGroup - 1) / kZGroup;
+            h.zgroups = z_groups(h.gz);
             if (pk.queue) {
                 // the p-side waits for the chain's units instead of its groups
                 const uint32_t tiles = (s->x.N + rows_for(pk.xtype, pk.chunks) - 1) / rows_for(pk.xtype, pk.chunks);

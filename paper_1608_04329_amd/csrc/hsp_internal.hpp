@@ -46,6 +46,12 @@ constexpr int kSmallP = 16;            // p up to this runs the one-block p-side
 #endif
 constexpr int kMaxGroup = HSP_MAX_GROUP;  // most blocks of the p-side group
 constexpr int kZGroup = 16;            // z-pass blocks whose partials one block sums
+// Arrivals that complete a z pass of gz blocks: one per group of kZGroup, or one
+// per block where a single group would do (those blocks add their sums themselves,
+// without the partials' way through memory).
+__host__ __device__ constexpr uint32_t z_groups(uint32_t gz) {
+    return gz <= (uint32_t)kZGroup ? gz : (gz + kZGroup - 1) / kZGroup;
+}
 // The z pass for rows of kc 16-byte chunks per lane of a wave (xtype 0:
 // float32, 4 elements per chunk; 1: bfloat16, 8): whether each wave holds
 // whole rows (up to 1536 float32 or 1024 bfloat16 elements) or the row is
@@ -165,7 +171,7 @@ struct SweepArgs {
     uint32_t mode;           // kMode* bits
     uint32_t gp;             // blocks of the p-side group (first in the grid)
     uint32_t gz;             // z-pass blocks (after the group)
-    uint32_t zgroups;        // ceil(gz / kZGroup)
+    uint32_t zgroups;        // z_groups(gz): arrivals that complete the z pass
     uint32_t block0;         // first grid block of this chain (several chains share a pack launch)
     uint32_t idle;           // a grid block that leaves at once (0: none), see sweep_finish_args
     uint64_t timeout_ticks;  // bound of every wait, in s_memrealtime ticks

@@ -11,9 +11,9 @@
 // Cholesky factorisation of Q depend only on the previous sweep, so the group
 // runs them while the z pass streams X; beta waits for the z pass.
 //
-// beta for p <= 16 (one block): Q packed in LDS, Q = U^T U by a right-looking
-// Cholesky, then s ~ N(0, I), U v = s, U^T w = b, U mu = w, beta = mu + v
-// (Section 5, beta steps ii-viii).
+// beta for p <= 16 (one block): [Q | I] in the registers of one wave, factored
+// by the row operations of one 16-row panel while the z pass runs, then the same
+// two products as below on 16 lanes.
 //
 // beta for p > 16 (gp blocks, 64 x 64 tiles): a right-looking blocked
 // Cholesky that applies the same row operations to an identity block, so it
@@ -151,6 +151,56 @@ __device__ __forceinline__ void group_sync(Group& g) {
     __syncthreads();
 }
 
+// The first half of a group barrier: what this block stored is complete and it
+// has arrived; it does not wait for the others.
+__device__ __forceinline__ void group_arrive(Group& g) {
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    if (threadIdx.x == 0) atomicAdd(&g.ctrl->bar_count, 1ull);
+    g.n++;
+    stamp(g);
+}
+
+// The second half: every block of the group has arrived as often as this one.
+// The block's threads meet at the end.
+__device__ __forceinline__ void group_wait(Group& g) {
+    if (threadIdx.x == 0 && g.size > 1)
+        wait_count(&g.ctrl->bar_count, g.base + (unsigned long long)g.n * g.size, g.ctrl, g.timeout);
+    __syncthreads();
+}
+
+// Arrive, then wait for the group and, with a target, for the z pass (z_count
+// >= ztarget), both polled in the same loads; false if the group is failing.
+// The failure flags count from the poll after the one that saw the group
+// complete: a block sets them before it arrives.
+__device__ __forceinline__ bool group_sync_z(Group& g, unsigned long long ztarget, double* lds_flag) {
+    group_arrive(g);
+    if (threadIdx.x == 0) {
+        const unsigned long long target = g.base + (unsigned long long)g.n * g.size;
+        const uint64_t t0 = wall_clock64();
+        uint32_t nap = 1, err = 0;
+        bool here = g.size == 1;
+        for (;;) {
+            const unsigned long long bars = __hip_atomic_load(&g.ctrl->bar_count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const unsigned long long zs = __hip_atomic_load(&g.ctrl->z_count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            err = __hip_atomic_load(&g.ctrl->err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if ((here && zs >= ztarget) || (err & kErrTimeout)) break;
+            const bool arrived = bars >= target;
+            if (wall_clock64() - t0 > g.timeout) {
+                atomicOr(&g.ctrl->err, kErrTimeout);
+                err = kErrTimeout;
+                break;
+            }
+            if (!(arrived && !here)) backoff(nap, here ? 32 : 8);
+            here = here || arrived;
+        }
+        lds_flag[0] = (err & (kErrNotPD | kErrTimeout)) ? 1.0 : 0.0;
+        if (g.trace && ztarget) g.trace[kTraceSlots - 1] = wall_clock64();
+    }
+    __syncthreads();
+    return lds_flag[0] == 0.0;
+}
+
 // Block-wide float64 sum in a fixed order (identical result in every block).
 __device__ __forceinline__ double block_sum(double v, double* red) {
 #pragma unroll
@@ -170,45 +220,24 @@ __device__ __forceinline__ uint32_t record_slot(Args& a, uint32_t k, bool* keep)
     return *keep ? (since / a.thin - 1u) % a.capacity : 0u;
 }
 
+// LDS offsets (doubles) of what hyper_lambda_tau leaves in red: on the one-block
+// path lambda^-2 (16).
+constexpr int kRedGamma = 9, kRedLambda = 16;
+
 // ---- lambda^-2 and tau^-2 (every block of the group computes them) ---------------
 // Returns tau^-2 (new if kModeTau).  Block `writer` stores lambda^-2 and tau^-2.
+// The gamma variate behind tau^-2 does not depend on the data: the last wave draws
+// it before its share of the lambda^-2, beside the other waves.  The caller's next
+// use of red comes after a block barrier.
 __device__ double hyper_lambda_tau(Args& a, uint32_t k, bool writer, double* red) {
     const uint32_t p = a.x.p;
-    const double tau_old = *a.tau_m2;
-    double acc = 0.0;
-    uint32_t clamps = 0;
-    bool bad = false;
-    for (uint32_t j = threadIdx.x; j < p; j += kThreads) {
-        const double bj = a.beta[j];
-        double lam;
-        if (a.mode & kModeLambda) {
-            double rate = a.nu_m1[j] + tau_old * bj * bj / 2.0;
-            if (!(rate >= DBL_MIN)) {
-                rate = DBL_MIN;
-                ++clamps;
-            }
-            const Words4 w = draw_words(a.seed, j, k, kTagLambda, 0, a.chain);
-            lam = -log(u01d(w.w0)) / rate;
-            if (!isfinite(lam)) bad = true;
-            if (writer) stc(&a.lam_m2[j], lam);
-        } else {
-            lam = a.lam_m2[j];
-        }
-        acc += lam * bj * bj;
-    }
-    if (writer) {
-        if (clamps) atomicAdd(&a.ctrl->clamps, (unsigned long long)clamps);
-        if (bad) atomicOr(&a.ctrl->err, kErrNonFinite);
-    }
-    if (!(a.mode & kModeTau)) return tau_old;
-    const double sum = block_sum(acc, red);
-    // Cheng's GB: proposal m = 64 * round + lane, uniforms of Philox round m/2
-    // (words 0-1 for even m, 2-3 for odd m); the lowest accepted m wins, which
-    // is the first acceptance of the sequential algorithm.  (Section 5 uses 32
-    // threads and a serial scan for the same purpose.)
-    if (threadIdx.x < kWave) {
-        const int lane = threadIdx.x;
-        const double rate = *a.xi_m1 + sum / 2.0;
+    const double tau_old = *a.tau_m2, xi = *a.xi_m1;
+    if ((a.mode & kModeTau) && threadIdx.x >= kThreads - kWave) {
+        // Cheng's GB: proposal m = 64 * round + lane, uniforms of Philox round m/2
+        // (words 0-1 for even m, 2-3 for odd m); the lowest accepted m wins, which
+        // is the first acceptance of the sequential algorithm.  (Section 5 uses 32
+        // threads and a serial scan for the same purpose.)
+        const int lane = threadIdx.x & (kWave - 1);
         const double sh = ((double)p + 1.0) / 2.0;
         const double A = 1.0 / sqrt(2.0 * sh - 1.0);
         const double B = sh - log(4.0);
@@ -231,17 +260,43 @@ __device__ double hyper_lambda_tau(Args& a, uint32_t k, bool writer, double* red
                 break;
             }
         }
-        if (lane == 0) red[8] = g / rate;
+        if (lane == 0) red[kRedGamma] = g;
     }
-    __syncthreads();
-    const double tau = red[8];
+    double acc = 0.0;
+    uint32_t clamps = 0;
+    bool bad = false;
+    for (uint32_t j = threadIdx.x; j < p; j += kThreads) {
+        const double bj = a.beta[j];
+        double lam;
+        if (a.mode & kModeLambda) {
+            double rate = a.nu_m1[j] + tau_old * bj * bj / 2.0;
+            if (!(rate >= DBL_MIN)) {
+                rate = DBL_MIN;
+                ++clamps;
+            }
+            const Words4 w = draw_words(a.seed, j, k, kTagLambda, 0, a.chain);
+            lam = -log(u01d(w.w0)) / rate;
+            if (!isfinite(lam)) bad = true;
+            if (writer) stc(&a.lam_m2[j], lam);
+        } else {
+            lam = a.lam_m2[j];
+        }
+        if (p <= (uint32_t)kSmallP) red[kRedLambda + j] = lam;
+        acc += lam * bj * bj;
+    }
+    if (writer) {
+        if (clamps) atomicAdd(&a.ctrl->clamps, (unsigned long long)clamps);
+        if (bad) atomicOr(&a.ctrl->err, kErrNonFinite);
+    }
+    if (!(a.mode & kModeTau)) return tau_old;
+    const double sum = block_sum(acc, red);
+    const double tau = red[kRedGamma] / (xi + sum / 2.0);
     // the other blocks may still be reading the old value: the new one goes to
     // a scratch slot and is published when the launch closes
     if (writer && threadIdx.x == 0) {
         stc(&a.vec[2 * p], tau);
         if (!isfinite(tau) || !(tau > 0.0)) atomicOr(&a.ctrl->err, kErrNonFinite);
     }
-    __syncthreads();
     return tau;
 }
 
@@ -263,153 +318,6 @@ __device__ void hyper_nu_xi(Args& a, uint32_t k) {
     if (threadIdx.x == 0) {
         const Words4 w = draw_words(a.seed, 0, k, kTagXi, 0, a.chain);
         *a.xi_m1 = -log(u01d(w.w0)) / (1.0 + current_tau(a));
-    }
-}
-
-// ---- one-block path, p <= 16 -----------------------------------------------------
-__device__ __forceinline__ uint32_t pk(uint32_t p, uint32_t i, uint32_t j) {
-    // packed upper triangle, row-major: row i starts at i p - i (i - 1) / 2
-    return i * p - (i * (i - 1u)) / 2u + (j - i);
-}
-
-__device__ double lane_elem(const double (&r)[2], uint32_t i) {
-    const double v0 = __shfl(r[0], (int)(i & 63u));
-    const double v1 = __shfl(r[1], (int)(i & 63u));
-    return i < 64u ? v0 : v1;
-}
-
-// One wave: U^T x = r (forward) or U x = r (backward), U packed in LDS;
-// lane l holds entries l and l + 64.
-__device__ void wave_solve(const double* U, uint32_t p, double (&r)[2], bool forward) {
-    const int lane = threadIdx.x & 63;
-    if (forward) {
-        for (uint32_t i = 0; i < p; ++i) {
-            const double xi = lane_elem(r, i) / U[pk(p, i, i)];
-#pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                const uint32_t j = q * 64 + lane;
-                if (j == i) r[q] = xi;
-                else if (j > i && j < p) r[q] -= U[pk(p, i, j)] * xi;
-            }
-        }
-    } else {
-        for (int ii = (int)p - 1; ii >= 0; --ii) {
-            const uint32_t i = (uint32_t)ii;
-            const double xi = lane_elem(r, i) / U[pk(p, i, i)];
-#pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                const uint32_t j = q * 64 + lane;
-                if (j == i) r[q] = xi;
-                else if (j < i) r[q] -= U[pk(p, j, i)] * xi;
-            }
-        }
-    }
-}
-
-// LDS offset (doubles) of b on the one-block path, past the packed factor.
-constexpr uint32_t kSmallBOff = 512;
-static_assert(kSmallP * (kSmallP + 1) / 2 <= (int)kSmallBOff && kSmallBOff + kSmallP <= (uint32_t)kLdsDoubles,
-              "one-block path LDS layout");
-
-__device__ __forceinline__ void small_path(Args& a, Group& g, uint32_t k, double* lds) {
-    const uint32_t p = a.x.p;
-    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-    double tau = hyper_lambda_tau(a, k, true, lds);
-    group_sync(g);  // lambda, tau in memory
-    if (a.mode & kModeNuXi) hyper_nu_xi(a, k);
-    bool bad = false;
-    if (a.mode & kModeBeta) {
-        double* U = lds;  // p (p + 1) / 2 doubles
-        for (uint32_t i = ty; i < p; i += 16)
-            for (uint32_t j = i + tx; j < p; j += 16)
-                U[pk(p, i, j)] = a.G[(size_t)i * p + j] + (i == j ? tau * a.lam_m2[i] : 0.0);
-        __syncthreads();
-        // right-looking, row scaling deferred: step c subtracts
-        // A[c][i] A[c][j] / A[c][c] from the trailing upper triangle
-        for (uint32_t c = 0; c < p; ++c) {
-            const double d = U[pk(p, c, c)];
-            if (!(d > 0.0)) {
-                bad = true;
-                break;
-            }
-            const double inv = 1.0 / d;
-            for (uint32_t i = c + 1 + ty; i < p; i += 16) {
-                const double f = U[pk(p, c, i)] * inv;
-                for (uint32_t j = i + tx; j < p; j += 16) U[pk(p, i, j)] -= f * U[pk(p, c, j)];
-            }
-            __syncthreads();
-        }
-        if (!bad) {
-            for (uint32_t i = ty; i < p; i += 16) {
-                const double rs = 1.0 / sqrt(U[pk(p, i, i)]);
-                for (uint32_t j = i + 1 + tx; j < p; j += 16) U[pk(p, i, j)] *= rs;
-            }
-            __syncthreads();
-            for (uint32_t i = threadIdx.x; i < p; i += kThreads) U[pk(p, i, i)] = sqrt(U[pk(p, i, i)]);
-            __syncthreads();
-        } else if (threadIdx.x == 0) {
-            atomicOr(&a.ctrl->err, kErrNotPD);
-            for (uint32_t c = 0; c < p; ++c)
-                if (!(U[pk(p, c, c)] > 0.0)) {
-                    atomicCAS(&a.ctrl->chol_info, 0, (int)(c + 1));
-                    break;
-                }
-        }
-    }
-    if (a.mode & (kModeZ | kModeBsum)) {
-        if ((a.mode & kModeZ) && threadIdx.x == 0) {
-            wait_count(&a.ctrl->z_count, g.zbase + a.zgroups, a.ctrl, a.timeout_ticks, 64);
-        }
-        __syncthreads();
-        // b as the z groups (of this launch, or of an earlier multi-chain
-        // pass) accumulated it, in the units of the stored X, unscaled
-        // exactly; wave 0 takes it from LDS below
-        for (uint32_t j = threadIdx.x; j < p; j += kThreads) {
-            const double s = ldc(&a.bsum[j]) * a.xscale[j];
-            a.b[j] = s;
-            lds[kSmallBOff + j] = s;
-        }
-        __syncthreads();
-    }
-    bool keep;
-    const uint32_t slot = record_slot(a, k, &keep);
-    if ((a.mode & kModeBeta) && !bad && threadIdx.x < kWave) {
-        const double* U = lds;
-        const int lane = threadIdx.x;
-        double v[2], w[2];
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const uint32_t j = q * 64 + lane;
-            v[q] = 0.0;
-            w[q] = 0.0;
-            if (j < p) {
-                const Words4 wd = draw_words(a.seed, j, k, kTagBetaS, 0, a.chain);
-                v[q] = box_muller_d(u01d(wd.w0), u01d(wd.w1));
-                w[q] = (a.mode & (kModeZ | kModeBsum)) ? lds[kSmallBOff + j] : a.b[j];
-            }
-        }
-        wave_solve(U, p, v, false);  // U v = s
-        wave_solve(U, p, w, true);   // U^T w = b
-        wave_solve(U, p, w, false);  // U mu = w
-        bool nonfinite = false;
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const uint32_t j = q * 64 + lane;
-            if (j < p) {
-                const double bj = w[q] + v[q];
-                a.beta[j] = bj;
-                a.beta32[j] = (float)(bj * a.xscale[j]);
-                if (!isfinite(bj)) nonfinite = true;
-                if (keep) a.ring_beta[(size_t)slot * p + j] = bj;
-            }
-        }
-        if (__ballot(nonfinite) && lane == 0) atomicOr(&a.ctrl->err, kErrNonFinite);
-    }
-    if (keep) {
-        __syncthreads();
-        if (a.ring_lam)
-            for (uint32_t j = threadIdx.x; j < p; j += kThreads) a.ring_lam[(size_t)slot * p + j] = ldc(&a.lam_m2[j]);
-        if (threadIdx.x == 0) a.ring_tau[slot] = current_tau(a);
     }
 }
 
@@ -606,6 +514,15 @@ __device__ __forceinline__ void panel_pivots(double (&d)[16], double (&a)[16]) {
         settle(d[C]);
         panel_rows<C, C + 1>(d, a);
         panel_pivots<C + 1>(d, a);
+    }
+}
+
+// acc += sum_j x_j y[j], x_j being lane j of x's row of 16 lanes.
+template <int J = 0>
+__device__ __forceinline__ void dot_bcast(double& acc, double minus_x, const double (&y)[16]) {
+    if constexpr (J < 16) {
+        fmsub_bcast<J>(acc, minus_x, y[J]);
+        dot_bcast<J + 1>(acc, minus_x, y);
     }
 }
 
@@ -1001,15 +918,6 @@ __device__ __forceinline__ double take(const double* hand, int idx, Ctrl* ctrl, 
     }
 }
 
-// acc += sum_j x_j y[j], x_j being lane j of x's row of 16 lanes.
-template <int J = 0>
-__device__ __forceinline__ void dot_bcast(double& acc, double minus_x, const double (&y)[16]) {
-    if constexpr (J < 16) {
-        fmsub_bcast<J>(acc, minus_x, y[J]);
-        dot_bcast<J + 1>(acc, minus_x, y);
-    }
-}
-
 // beta = U^-1 (U^-T b + s) by blocked substitution (where the factorisation
 // leaves L^-1 out beyond its diagonal tiles, half of its flops).  Block r of the
 // group owns tile rows r, r + gp, ...  Forward, its rows in increasing order:
@@ -1150,6 +1058,109 @@ __device__ __forceinline__ void subst_solve(Args& a, Group& g, uint32_t rank, ui
     group_sync(g);
 }
 
+// ---- one-block path, p <= 16 -----------------------------------------------------
+// LDS (doubles, after hyper_lambda_tau's): the noise of beta (16), U^-T (16 rows of
+// 17) and the failed pivot (0: none).
+constexpr int kSmallNoise = 32, kSmallT = 48, kSmallFail = kSmallT + 16 * 17, kSmallLds = 384;
+static_assert(kSmallFail < kSmallLds, "one-block path LDS layout");
+
+// While the z pass runs, wave 0 factors [Q | I] (padded to 16 with the identity)
+// as one panel, wave 1 draws nu and xi, wave 2 the noise s; then wave 0 takes b and
+// does y = U^-T b + s and beta = U^-1 y on its lanes, one of y's and beta's entries
+// per lane of a row of 16, with the other operand broadcast from the row.  Bound by
+// latencies; after b arrives it takes two 16-term sums (three triangular solves
+// with a division per row took ~4 us).
+__device__ __forceinline__ void small_path(Args& a, Group& g, uint32_t k, double* lds) {
+    const uint32_t p = a.x.p;
+    const int lane = threadIdx.x & 63, c = lane & 15;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const bool beta = (a.mode & kModeBeta) != 0, in = (uint32_t)c < p;
+    const uint32_t cj = min((uint32_t)c, p - 1u);
+    double d[16], t[16];
+    if (wave == 0 && beta) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) d[i] = a.G[(size_t)min((uint32_t)i, p - 1u) * p + cj];
+    }
+    const double scale = a.xscale[cj];
+    const double tau = hyper_lambda_tau(a, k, true, lds);
+    __syncthreads();
+    stamp(g);
+    if (wave == 1 && (a.mode & kModeNuXi)) {
+        if ((uint32_t)lane < p) {
+            const Words4 w = draw_words(a.seed, lane, k, kTagNu, 0, a.chain);
+            a.nu_m1[lane] = -log(u01d(w.w0)) / (1.0 + lds[kRedLambda + lane]);
+        } else if (lane == kSmallP) {
+            const Words4 w = draw_words(a.seed, 0, k, kTagXi, 0, a.chain);
+            *a.xi_m1 = -log(u01d(w.w0)) / (1.0 + tau);
+        }
+    }
+    if (wave == 2 && beta && lane < kSmallP) {
+        const Words4 w = draw_words(a.seed, lane, k, kTagBetaS, 0, a.chain);
+        lds[kSmallNoise + lane] = in ? box_muller_d(u01d(w.w0), u01d(w.w1)) : 0.0;
+    }
+    if (wave == 0 && beta) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const double q = i == c ? fma(tau, lds[kRedLambda + cj], d[i]) : d[i];
+            d[i] = in && (uint32_t)i < p ? q : (i == c ? 1.0 : 0.0);
+            t[i] = lane == i ? 1.0 : 0.0;
+        }
+        panel_pivots<0>(d, t);  // lane j < 16 holds column j of U^-T
+        double u = d[0];        // U's diagonal, entry c in lane c
+#pragma unroll
+        for (int i = 1; i < 16; ++i) u = c == i ? d[i] : u;
+        const unsigned long long fail = __ballot(lane < 16 && !(u > 0.0));
+        if (lane == 0) lds[kSmallFail] = fail ? (double)__ffsll((long long)fail) : 0.0;
+        if (lane < 16) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) lds[kSmallT + i * 17 + lane] = t[i];
+        }
+    }
+    __syncthreads();
+    const bool bad = beta && lds[kSmallFail] != 0.0;
+    if (wave != 0) return;
+    const bool from_sum = (a.mode & (kModeZ | kModeBsum)) != 0;
+    double b = 0.0;
+    double row[16];  // row c of U^-T
+    if (beta) {
+#pragma unroll
+        for (int j = 0; j < 16; ++j) row[j] = lds[kSmallT + c * 17 + j];
+    }
+    if (from_sum) {
+        if ((a.mode & kModeZ) && lane == 0) wait_count(&a.ctrl->z_count, g.zbase + a.zgroups, a.ctrl, a.timeout_ticks, 8);
+        // b as the z blocks (of this launch, or of an earlier pass) accumulated it,
+        // in the units of the stored X, unscaled exactly
+        b = ldc(&a.bsum[cj]) * scale;
+        if (lane < 16 && in) a.b[c] = b;
+    } else if (beta) {
+        b = a.b[cj];
+    }
+    bool keep;
+    const uint32_t slot = record_slot(a, k, &keep);
+    if (beta && !bad) {
+        double mb = in ? -b : 0.0, y = lds[kSmallNoise + c], bj = 0.0;
+        settle(mb);
+        dot_bcast(y, mb, row);
+        double my = -y;
+        settle(my);
+        dot_bcast(bj, my, t);
+        if (lane < 16 && in) {
+            a.beta[c] = bj;
+            a.beta32[c] = (float)(bj * scale);
+            if (keep) a.ring_beta[(size_t)slot * p + c] = bj;
+        }
+        if (__ballot(lane < 16 && in && !isfinite(bj)) && lane == 0) atomicOr(&a.ctrl->err, kErrNonFinite);
+    }
+    if (bad && lane == 0) {
+        atomicOr(&a.ctrl->err, kErrNotPD);
+        atomicCAS(&a.ctrl->chol_info, 0, (int)lds[kSmallFail]);
+    }
+    if (keep) {
+        if (a.ring_lam && lane < 16 && in) a.ring_lam[(size_t)slot * p + c] = lds[kRedLambda + c];
+        if (lane == 0) a.ring_tau[slot] = tau;
+    }
+}
+
 // The part of the tile path before b is needed: lambda, tau, nu, xi, the noise of
 // beta and the factorisation's tasks.  False if the factorisation failed.
 __device__ __forceinline__ bool tile_factor(Args& a, Group& g, uint32_t rank, uint32_t k, double* lds) {
@@ -1161,7 +1172,12 @@ __device__ __forceinline__ bool tile_factor(Args& a, Group& g, uint32_t rank, ui
     // with kModePost an earlier launch of this sweep did all this
     if (a.mode & kModePost) return true;
     const double tau = hyper_lambda_tau(a, k, rank == 0, lds);
-    group_sync(g);  // lambda^-2 and the new tau^-2 in memory
+    // No block waits here for block 0's lambda^-2 in memory: whoever reads it in
+    // the factorisation has waited for a tile that follows from block 0's first,
+    // stored later.  nu and xi wait until every block has read the old ones.
+    // (A launch without the factorisation has no later barrier: it waits.)
+    group_arrive(g);
+    if (!(a.mode & kModeBeta) || rank == g.size - 1) group_wait(g);
     if (rank == g.size - 1) {
         if (a.mode & kModeNuXi) hyper_nu_xi(a, k);
         if (a.mode & kModeBeta)
@@ -1182,21 +1198,17 @@ __device__ __forceinline__ void tile_beta(Args& a, Group& g, uint32_t rank, uint
     const uint32_t p = a.x.p, P = padded(p);
     double* flag = lds + 2 * kTile * kTileLd - 1;
     double* s_noise = a.vec + p;
-    if (a.mode & kModePost) {
-        ok = !group_failed(g, flag);  // the earlier launch's failure flags are in memory
-    } else if (a.mode & kModeBeta) {
-        group_sync(g);
-        ok = ok && !group_failed(g, flag);
+    const unsigned long long ztarget = (a.mode & kModeZ) ? g.zbase + a.zgroups : 0ull;
+    if ((a.mode & kModeBeta) && !(a.mode & kModePost)) {
+        ok = group_sync_z(g, ztarget, flag) && ok;
+    } else {
+        // (with kModePost the earlier launch's failure flags are in memory)
+        if (a.mode & kModePost) ok = !group_failed(g, flag);
+        if (ztarget && threadIdx.x == 0) wait_count(&a.ctrl->z_count, ztarget, a.ctrl, a.timeout_ticks, 64);
+        __syncthreads();
     }
     if (a.mode & kModePre) return;  // b is taken by a later launch of this sweep
 
-    if (a.mode & kModeZ) {
-        if (threadIdx.x == 0) {
-            wait_count(&a.ctrl->z_count, g.zbase + a.zgroups, a.ctrl, a.timeout_ticks, 64);
-        }
-        if (g.trace && threadIdx.x == 0) g.trace[kTraceSlots - 1] = wall_clock64();
-        __syncthreads();
-    }
     // b = X^T z into LDS (zero on the padding), as the z groups accumulated
     // it; block 0 also stores it.  A vector too long for the LDS (big) is
     // read from memory where it is used instead.
@@ -1318,7 +1330,9 @@ __device__ __forceinline__ void tile_beta(Args& a, Group& g, uint32_t rank, uint
 
 // The p-side role of block `rank` of the group, in two parts: all that comes
 // before b, and the rest.  Between them the block may take units of the z pass.
-// pside_begin returns false if the factorisation failed.
+// pside_begin returns false if the factorisation failed.  SMALL: a kernel for
+// p <= 16 alone, without the tile path.
+template <bool SMALL>
 __device__ __forceinline__ bool pside_begin(Args& a, Group& g, uint32_t rank, uint32_t k, double* lds) {
     g.trace = a.trace ? a.trace + (size_t)rank * kTraceSlots : nullptr;
     if (g.trace && threadIdx.x == 0) g.trace[0] = wall_clock64();
@@ -1332,13 +1346,18 @@ __device__ __forceinline__ bool pside_begin(Args& a, Group& g, uint32_t rank, ui
     g.timeout = a.timeout_ticks;
     // the two-launch split is for the tile path; a launch never asks the
     // one-block path for half a sweep
-    if (a.x.p > (uint32_t)kSmallP) return tile_factor(a, g, rank, k, lds);
+    if constexpr (!SMALL) {
+        if (a.x.p > (uint32_t)kSmallP) return tile_factor(a, g, rank, k, lds);
+    }
     if (!(a.mode & (kModePre | kModePost))) small_path(a, g, k, lds);
     return true;
 }
 
+template <bool SMALL>
 __device__ __forceinline__ void pside_end(Args& a, Group& g, uint32_t rank, uint32_t k, double* lds, bool ok) {
-    if (a.x.p > (uint32_t)kSmallP) tile_beta(a, g, rank, k, lds, ok);
+    if constexpr (!SMALL) {
+        if (a.x.p > (uint32_t)kSmallP) tile_beta(a, g, rank, k, lds, ok);
+    }
     // the last barrier above was passed by every block of the group, and the
     // z-pass blocks have all finished if they ran: close the launch
     if (rank == 0) {
@@ -1365,7 +1384,6 @@ __device__ __forceinline__ void pside_end(Args& a, Group& g, uint32_t rank, uint
             if (threadIdx.x == 0) a.ctrl->z_next = 0u;
             for (uint32_t j = threadIdx.x; j < a.x.ld; j += kThreads) stc(&a.bsum[j], 0.0);
         }
-        __threadfence();
     }
 }
 

@@ -29,8 +29,9 @@ namespace {
 // to chain chain_of_block[b] (chain 0 for all when the map is null) and runs
 // that chain's role at position b - block0 of its blocks, or, marked with
 // kWorkerBit, is a worker of the pack's shared z queue.
-template <int XT, int KC, int R, bool WIDE>
+template <int XT, int KC, int R, bool WIDE, bool SMALL = false>
 __device__ __forceinline__ void run_block(Args& a, double* lds) {
+    constexpr int RC = SMALL ? 64 : kRedCols;  // columns of an LDS reduction segment
     uint32_t b = blockIdx.x - a.block0;
     const uint32_t k = a.ctrl->sweep + 1u;
     if (a.idle) {
@@ -42,7 +43,7 @@ __device__ __forceinline__ void run_block(Args& a, double* lds) {
     Group g;
     bool ok = true, z = !pside;
     if (pside) {
-        ok = pside_begin(a, g, b, k, lds);
+        ok = pside_begin<SMALL>(a, g, b, k, lds);
         // a block whose factorisation work is done may take units of the z pass:
         // the group's next barrier, which every reader of b passes, covers its
         // additions, and the z-pass blocks' own count is not touched
@@ -53,12 +54,12 @@ __device__ __forceinline__ void run_block(Args& a, double* lds) {
         ZSums<XT, KC> sums;
         const bool any = z_take<XT, KC, R, WIDE>(a, b - a.gp, a.gz, pside, k, lds, sums);
         if (!pside) {
-            z_finish<XT, KC, WIDE>(a, b - a.gp, a.gz, lds, sums);
+            z_finish<XT, KC, WIDE, RC>(a, b - a.gp, a.gz, lds, sums, any);
             return;
         }
-        if (any) z_flush<XT, KC, WIDE>(a, sums.b, sums.maxatt, sums.capped, lds);
+        if (any) z_flush<XT, KC, WIDE, RC>(a, sums.b, sums.maxatt, sums.capped, lds);
     }
-    pside_end(a, g, b, k, lds, ok);
+    pside_end<SMALL>(a, g, b, k, lds, ok);
 }
 
 // KC: 16-byte chunks per lane of a wave (of the whole row, or with WIDE of
@@ -78,6 +79,16 @@ __global__ __launch_bounds__(kThreads, 2) void sweep_kernel(const SweepArgs* con
 }
 
 
+
+// A lone chain with p <= 16 (rows of one chunk): without the tile path, its LDS
+// and its registers, so that a sweep of tens of microseconds starts and fetches
+// its code sooner.
+template <int XT>
+__global__ __launch_bounds__(kThreads, 2) void small_sweep_kernel(const SweepArgs* const* __restrict__ args,
+                                                                  const uint16_t* __restrict__) {
+    __shared__ double lds[kSmallLds];
+    run_block<XT, 1, rows_for(XT, 1), false, true>(*(Args*)args[0], lds);
+}
 
 // The multi-chain z pass for chains sharing one bfloat16 design (KS
 // 32-column steps per wave); no block waits for another.
@@ -121,6 +132,12 @@ KernelFn kernel_for(int xtype, int chunks) {
     return pick_wide<1>(kcw, std::make_integer_sequence<int, kMaxP / (kWave * 8 * 4)>{});
 }
 
+// The kernel of a lone chain's launches.
+KernelFn lone_kernel(const XLayout& x, int chunks) {
+    if (x.p > (uint32_t)kSmallP) return kernel_for(x.xtype, chunks);
+    return x.xtype == 0 ? &small_sweep_kernel<0> : &small_sweep_kernel<1>;
+}
+
 }  // namespace
 
 uint32_t max_group(const XLayout& x, int capacity) {
@@ -152,7 +169,7 @@ hipError_t sweep_plan(const XLayout& x, int num_cus, SweepPlan* plan, uint32_t g
     plan->chunks = (int)((x.ld + kWave * vec - 1) / (kWave * vec));
     plan->rows = rows_for(x.xtype, plan->chunks);
     const bool wide = wide_chunks(x.xtype, plan->chunks);
-    KernelFn f = kernel_for(x.xtype, plan->chunks);
+    KernelFn f = lone_kernel(x, plan->chunks);
     if (!f) return hipErrorInvalidValue;
     int per_cu = 0;
     hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(f),
@@ -197,14 +214,14 @@ void sweep_finish_args(SweepArgs* a, const SweepPlan& plan) {
     // 2329 us, 2.51 -> 1.82 ms per sweep.  Smaller groups stay out: they would find
     // little left, and looking costs a short sweep 2 % (N = 1e5, p = 100).
     a->help = 4u * a->gp > (uint32_t)plan.capacity ? 1u : 0u;
-    a->zgroups = (a->gz + kZGroup - 1) / kZGroup;
+    a->zgroups = z_groups(a->gz);
     a->z_static_pct = plan.static_pct;
     a->z_unit = plan.unit;
 }
 
 hipError_t sweep_launch(const SweepArgs& host, const SweepArgs* const* table, const SweepPlan& plan,
                         hipStream_t st) {
-    KernelFn f = kernel_for(host.x.xtype, plan.chunks);
+    KernelFn f = lone_kernel(host.x, plan.chunks);
     if (!f) return hipErrorInvalidValue;
     const uint16_t* none = nullptr;
     void* args[] = {&table, &none};

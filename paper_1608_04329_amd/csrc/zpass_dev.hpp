@@ -31,7 +31,7 @@
 namespace hsp {
 
 constexpr int kWPB = kThreads / kWave;  // waves per block
-constexpr int kRedCols = kLdsDoubles / kWPB;  // columns per LDS reduction segment
+constexpr int kRedCols = kLdsDoubles / kWPB;  // columns per LDS reduction segment (of a whole block's LDS)
 
 template <int XT>
 struct XTraits;
@@ -301,11 +301,14 @@ __device__ __forceinline__ bool z_take(Args& a, uint32_t zrank, uint32_t nz, boo
     double* slot = red;
     const uint32_t n_tiles = (a.x.N + R - 1) / R, unit = a.z_unit;
     const uint32_t W = WIDE ? nz : nz * kWPB, step = WIDE ? 1u : (uint32_t)kWPB;
-    const uint32_t rounds = (uint32_t)((uint64_t)n_tiles * a.z_static_pct / 100 / W), n_static = rounds * W;
+    // (at most one tile per taker: all static, and nothing to claim)
+    const bool one = n_tiles <= W;
+    const uint32_t rounds = one ? 1u : (uint32_t)((uint64_t)n_tiles * a.z_static_pct / 100 / W);
+    const uint32_t n_static = one ? n_tiles : rounds * W;
     const uint32_t n_units = (n_tiles - n_static + unit - 1) / unit;
-    uint32_t left = helper ? 0u : rounds;  // static tiles still to come
     uint32_t t = WIDE ? zrank : zrank * kWPB + wave, j = unit, u = 0, next = 0;
-    bool any = left > 0, first = true;
+    uint32_t left = helper || t >= n_static ? 0u : rounds;  // static tiles still to come
+    bool any = !helper && n_static > 0, first = true;
     for (;;) {
         uint32_t now;
         if (left > 0) {
@@ -313,6 +316,7 @@ __device__ __forceinline__ bool z_take(Args& a, uint32_t zrank, uint32_t nz, boo
             t += W;
             --left;
         } else {
+            if (n_units == 0) break;
             if (j >= unit) {  // the next unit
                 if (threadIdx.x == 0) *slot = (double)(first ? atomicAdd(&a.ctrl->z_next, 1u) : next);
                 __syncthreads();
@@ -334,10 +338,64 @@ __device__ __forceinline__ bool z_take(Args& a, uint32_t zrank, uint32_t nz, boo
     return any;
 }
 
+// A block leaves chain a: the float64 sums of x_ij z_i over the units it
+// finished there (each wave's, added in wave order, or for wide rows each wave's
+// own columns) go into the chain's b accumulator, then its proposal statistics.
+template <int XT, int KC, bool WIDE, int RC = kRedCols>
+__device__ __forceinline__ void z_flush(Args& a, double (&bacc)[KC][XTraits<XT>::VEC], uint32_t& maxatt,
+                                        bool& capped, double* red) {
+    constexpr int VEC = XTraits<XT>::VEC;
+    constexpr int CW = kWave * VEC;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = threadIdx.x / kWave;
+    const uint32_t ld = a.x.ld;
+    if constexpr (WIDE) {
+#pragma unroll
+        for (int kc = 0; kc < KC; ++kc)
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) {
+                const uint32_t col = ((uint32_t)wave * KC + kc) * CW + lane * VEC + e;
+                if (col < ld)
+                    __hip_atomic_fetch_add(&a.bsum[col], bacc[kc][e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+    }
+    for (uint32_t seg = 0; !WIDE && seg < ld; seg += RC) {
+#pragma unroll
+        for (int kc = 0; kc < KC; ++kc)
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) {
+                const uint32_t col = kc * CW + lane * VEC + e;
+                if (col >= seg && col < seg + RC && col < ld) red[wave * RC + (col - seg)] = bacc[kc][e];
+            }
+        __syncthreads();
+        for (uint32_t c = threadIdx.x; c < RC && seg + c < ld; c += kThreads) {
+            double v = red[c];
+#pragma unroll
+            for (int w = 1; w < kWPB; ++w) v += red[w * RC + c];
+            __hip_atomic_fetch_add(&a.bsum[seg + c], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int kc = 0; kc < KC; ++kc)
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) bacc[kc][e] = 0.0;
+    uint32_t m = maxatt;
+#pragma unroll
+    for (int off = kWave / 2; off >= 1; off >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, off));
+    const bool anycap = __ballot(capped) != 0ull;
+    if (lane == 0) {
+        if (m) atomicMax(&a.ctrl->max_attempts, m);
+        if (anycap) atomicOr(&a.ctrl->err, kErrTnCap);
+    }
+    maxatt = 0;
+    capped = false;
+}
+
 // Block zrank of the nz z-pass blocks has done its tiles: its proposal
 // statistics, and its sums into b's accumulator.
-template <int XT, int KC, bool WIDE>
-__device__ __forceinline__ void z_finish(Args& a, uint32_t zrank, uint32_t nz, double* red, ZSums<XT, KC>& z) {
+template <int XT, int KC, bool WIDE, int RC>
+__device__ __forceinline__ void z_finish(Args& a, uint32_t zrank, uint32_t nz, double* red, ZSums<XT, KC>& z, bool any) {
     constexpr int VEC = XTraits<XT>::VEC;
     constexpr int CW = kWave * VEC;
     const int lane = threadIdx.x & (kWave - 1);
@@ -345,6 +403,24 @@ __device__ __forceinline__ void z_finish(Args& a, uint32_t zrank, uint32_t nz, d
     const uint32_t ld = a.x.ld;
     const uint32_t c0 = WIDE ? (uint32_t)wave * KC * CW : 0u;
     auto& bacc = z.b;
+    // the launch's last block to arrive resets the shared unit counter if there is
+    // no p-side group to do so (a chunk of rows): every block has then left its
+    // claim loop
+    auto arrived = [&] {
+        atomicAdd(&a.ctrl->z_count, 1ull);
+        if (a.gp == 0 && atomicAdd(&a.ctrl->z_done, 1u) == a.zgroups - 1) {
+            __hip_atomic_store(&a.ctrl->z_done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(&a.ctrl->z_next, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    };
+    if (nz <= (uint32_t)kZGroup) {
+        // few blocks: each adds its sums itself (z_groups counts blocks)
+        if (any) z_flush<XT, KC, WIDE, RC>(a, bacc, z.maxatt, z.capped, red);
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+        if (threadIdx.x == 0) arrived();
+        return;
+    }
     const uint32_t maxatt = z.maxatt;
     const bool capped = z.capped;
 
@@ -369,20 +445,20 @@ __device__ __forceinline__ void z_finish(Args& a, uint32_t zrank, uint32_t nz, d
                 if (col < ld) stc(&a.partial[(size_t)zrank * ld + col], bacc[kc][e]);
             }
     }
-    for (uint32_t seg = 0; !WIDE && seg < ld; seg += kRedCols) {
+    for (uint32_t seg = 0; !WIDE && seg < ld; seg += RC) {
 #pragma unroll
         for (int kc = 0; kc < KC; ++kc)
 #pragma unroll
             for (int e = 0; e < VEC; ++e) {
                 const uint32_t col = kc * CW + lane * VEC + e;
-                if (col >= seg && col < seg + kRedCols && col < ld)
-                    red[wave * kRedCols + (col - seg)] = bacc[kc][e];
+                if (col >= seg && col < seg + RC && col < ld)
+                    red[wave * RC + (col - seg)] = bacc[kc][e];
             }
         __syncthreads();
-        for (uint32_t c = threadIdx.x; c < kRedCols && seg + c < ld; c += kThreads) {
+        for (uint32_t c = threadIdx.x; c < RC && seg + c < ld; c += kThreads) {
             double v = red[c];
 #pragma unroll
-            for (int w = 1; w < kWPB; ++w) v += red[w * kRedCols + c];
+            for (int w = 1; w < kWPB; ++w) v += red[w * RC + c];
             stc(&a.partial[(size_t)zrank * ld + seg + c], v);
         }
         __syncthreads();
@@ -423,72 +499,11 @@ __device__ __forceinline__ void z_finish(Args& a, uint32_t zrank, uint32_t nz, d
         if (threadIdx.x == 0) {
             // every block of the group has arrived
             __hip_atomic_store(&a.zgrp_count[grp], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            atomicAdd(&a.ctrl->z_count, 1ull);
-            // a launch without a p-side group (a chunk of rows) resets the
-            // shared unit counter itself once every group has finished, i.e.
-            // every block has left its claim loop
-            if (a.gp == 0 && atomicAdd(&a.ctrl->z_done, 1u) == a.zgroups - 1) {
-                __hip_atomic_store(&a.ctrl->z_done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                __hip_atomic_store(&a.ctrl->z_next, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
+            arrived();
         }
     }
 }
 
-
-// A block leaves chain a: the float64 sums of x_ij z_i over the units it
-// finished there (each wave's, added in wave order, or for wide rows each wave's
-// own columns) go into the chain's b accumulator, then its proposal statistics.
-template <int XT, int KC, bool WIDE>
-__device__ __forceinline__ void z_flush(Args& a, double (&bacc)[KC][XTraits<XT>::VEC], uint32_t& maxatt,
-                                        bool& capped, double* red) {
-    constexpr int VEC = XTraits<XT>::VEC;
-    constexpr int CW = kWave * VEC;
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wave = threadIdx.x / kWave;
-    const uint32_t ld = a.x.ld;
-    if constexpr (WIDE) {
-#pragma unroll
-        for (int kc = 0; kc < KC; ++kc)
-#pragma unroll
-            for (int e = 0; e < VEC; ++e) {
-                const uint32_t col = ((uint32_t)wave * KC + kc) * CW + lane * VEC + e;
-                if (col < ld)
-                    __hip_atomic_fetch_add(&a.bsum[col], bacc[kc][e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-    }
-    for (uint32_t seg = 0; !WIDE && seg < ld; seg += kRedCols) {
-#pragma unroll
-        for (int kc = 0; kc < KC; ++kc)
-#pragma unroll
-            for (int e = 0; e < VEC; ++e) {
-                const uint32_t col = kc * CW + lane * VEC + e;
-                if (col >= seg && col < seg + kRedCols && col < ld) red[wave * kRedCols + (col - seg)] = bacc[kc][e];
-            }
-        __syncthreads();
-        for (uint32_t c = threadIdx.x; c < kRedCols && seg + c < ld; c += kThreads) {
-            double v = red[c];
-#pragma unroll
-            for (int w = 1; w < kWPB; ++w) v += red[w * kRedCols + c];
-            __hip_atomic_fetch_add(&a.bsum[seg + c], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int kc = 0; kc < KC; ++kc)
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) bacc[kc][e] = 0.0;
-    uint32_t m = maxatt;
-#pragma unroll
-    for (int off = kWave / 2; off >= 1; off >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, off));
-    const bool anycap = __ballot(capped) != 0ull;
-    if (lane == 0) {
-        if (m) atomicMax(&a.ctrl->max_attempts, m);
-        if (anycap) atomicOr(&a.ctrl->err, kErrTnCap);
-    }
-    maxatt = 0;
-    capped = false;
-}
 
 // A worker block of a pack's shared z queue (rows of one wave each): the
 // units of its home chain, then of whichever chain has most units left, until
