@@ -329,7 +329,7 @@ __device__ void mc_role(McView& m, uint32_t rank, double* lds) {
     const unsigned long long capmask = __ballot(capped);
     const bool anycap = ((capmask >> n) | (capmask >> (n + 16)) | (capmask >> (n + 32)) | (capmask >> (n + 48))) & 1ull;
     if (live && q == 0) {
-        if (mx) atomicMax(&ctrl->max_attempts, mx);
+        if (mx > ctrl->max_attempts) atomicMax(&ctrl->max_attempts, mx);
         if (anycap) atomicOr(&ctrl->err, kErrTnCap);
     }
 }

@@ -188,6 +188,10 @@ hipError_t sweep_plan(const XLayout& x, int num_cus, SweepPlan* plan, uint32_t g
     if (gz > room) gz = room;
     if (gz < 1) gz = 1;
     plan->gz = (uint32_t)gz;
+    // a short pass (fewer than four tiles per taker) goes out one tile per wave at
+    // a time: with units of 8 tiles N = 1e5, p = 100 had 391 units for 509 blocks
+    const uint64_t takers = wide ? gz : gz * kWPB;
+    if (tiles < 4 * takers) plan->unit = wide ? 1u : (uint32_t)kWPB;
     return hipSuccess;
 }
 

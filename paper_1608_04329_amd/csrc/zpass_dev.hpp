@@ -77,6 +77,39 @@ __device__ __forceinline__ float xelem(const uint4& v, int e) {
     }
 }
 
+__device__ __forceinline__ float dpp_quad(float v, int xor_lane) {  // lane ^ 1 or lane ^ 2
+    const int i = __float_as_int(v);
+    return __int_as_float(xor_lane == 1 ? __builtin_amdgcn_update_dpp(0, i, 0xB1, 0xf, 0xf, true)    // quad_perm 1,0,3,2
+                                        : __builtin_amdgcn_update_dpp(0, i, 0x4E, 0xf, 0xf, true));  // quad_perm 2,3,0,1
+}
+
+// One step of the halving exchange between lanes l and l ^ off (a power of two,
+// known at compile time): a lane whose bit `off` is clear keeps lo and receives its
+// partner's lo, one whose bit is set keeps hi and receives hi; the sum of the two.
+// (lo == hi: a plain pairwise sum.)  Across half-waves and across rows of 16 lanes a
+// lane swap does keep and exchange in one instruction; within a row, cross-lane
+// operands; none goes through LDS.
+__device__ __forceinline__ float exchange_add(float lo, float hi, int off) {
+    typedef unsigned int U32x2 __attribute__((ext_vector_type(2)));
+    if (off == 32) {
+        const U32x2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(lo), __float_as_uint(hi), false, false);
+        return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    }
+    if (off == 16) {
+        const U32x2 r = __builtin_amdgcn_permlane16_swap(__float_as_uint(lo), __float_as_uint(hi), false, false);
+        return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    }
+    const bool up = (threadIdx.x & off) != 0;
+    const float send = up ? lo : hi, keep = up ? hi : lo;
+    if (off == 8)  // rotate the row by 8
+        return keep + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(send), 0x128, 0xf, 0xf, true));
+    if (off == 4) {  // mirror half-rows (l ^ 7), then quads (l ^ 3)
+        const int m = __builtin_amdgcn_update_dpp(0, __float_as_int(send), 0x141, 0xf, 0xf, true);
+        return keep + __int_as_float(__builtin_amdgcn_update_dpp(0, m, 0x1B, 0xf, 0xf, true));
+    }
+    return keep + dpp_quad(send, off);
+}
+
 // One proposal from the uniforms (ua, ub): both candidates, one selected.
 __device__ __forceinline__ void tn_candidate(float mu, bool gauss, float theta, float inv_theta,
                                              float ua, float ub, float& t, bool& acc) {
@@ -118,6 +151,17 @@ __device__ __forceinline__ void z_tile(Args& a, uint32_t t, uint32_t ksweep,
     uint32_t coff[KC];
 #pragma unroll
     for (int kc = 0; kc < KC; ++kc) coff[kc] = min(c0 + kc * CW + lane * VEC, ld - VEC) * EB;
+    // Lane r < R will draw z for row row0 + r: position first_row + row0 + r of
+    // the stored X and y (X may arrive in row chunks), whose original row index
+    // (the rows may have been reordered) sets its Philox counters and its place
+    // in the debug outputs.  Its outcome is loaded ahead of X's rows: loaded where
+    // it is used, every tile waited for one more memory latency.
+    const uint32_t row = row0 + (uint32_t)lane;
+    const bool active = lane < R && row < N;
+    const uint32_t pos = a.first_row + min(row0 + min((uint32_t)lane, (uint32_t)R - 1u), N - 1u);
+    uint32_t grow = pos;
+    if (a.row_id) grow = a.row_id[pos];
+    const uint32_t yv = a.y[pos];
     uint4 xr[R][KC];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
@@ -162,15 +206,10 @@ __device__ __forceinline__ void z_tile(Args& a, uint32_t t, uint32_t ksweep,
         const int off = kWave >> (st + 1);
         const int h = R >> (st + 1);  // rows kept after this step (0: one row left)
         if (h >= 1) {
-            const bool up = (lane & off) != 0;
 #pragma unroll
-            for (int j = 0; j < h; ++j) {
-                const float send = up ? s[j] : s[j + h];
-                const float keep = up ? s[j + h] : s[j];
-                s[j] = keep + __shfl_xor(send, off);
-            }
+            for (int j = 0; j < h; ++j) s[j] = exchange_add(s[j], s[j + h], off);
         } else {
-            s[0] += __shfl_xor(s[0], off);
+            s[0] = exchange_add(s[0], s[0], off);
         }
     }
     float eta;
@@ -191,15 +230,7 @@ __device__ __forceinline__ void z_tile(Args& a, uint32_t t, uint32_t ksweep,
         eta = __shfl(s[0], lane << (6 - LR));  // row `lane`'s sum, for lanes below R
     }
 
-    // lane r < R draws z for row row0 + r: position first_row + row0 + r of
-    // the stored X and y (X may arrive in row chunks), whose original row
-    // index (the rows may have been reordered) sets its Philox counters
-    // and its place in the debug outputs
-    const uint32_t row = row0 + (uint32_t)lane;
-    const bool active = lane < R && row < N;
-    const uint32_t pos = a.first_row + row;
-    const uint32_t grow = active ? (a.row_id ? a.row_id[pos] : pos) : 0u;
-    const float ys = (active && a.y[pos]) ? 1.0f : -1.0f;
+    const float ys = yv ? 1.0f : -1.0f;
     const float mu = ys * eta;
     const bool gauss = mu > 0.47f;
     const float den = sqrtf(fmaf(mu, mu, 4.0f)) - mu;  // 2 theta
@@ -318,14 +349,16 @@ __device__ __forceinline__ bool z_take(Args& a, uint32_t zrank, uint32_t nz, boo
         } else {
             if (n_units == 0) break;
             if (j >= unit) {  // the next unit
-                if (threadIdx.x == 0) *slot = (double)(first ? atomicAdd(&a.ctrl->z_next, 1u) : next);
+                // (z-pass block r's first unit is r, without asking; claims follow
+                // from nz on)
+                if (threadIdx.x == 0) *slot = (double)(!first ? next : helper ? nz + atomicAdd(&a.ctrl->z_next, 1u) : zrank);
                 __syncthreads();
                 u = (uint32_t)*slot;
                 __syncthreads();
                 if (u >= n_units) break;
                 any = true;
                 first = false;
-                if (threadIdx.x == 0) next = atomicAdd(&a.ctrl->z_next, 1u);
+                if (threadIdx.x == 0) next = nz + atomicAdd(&a.ctrl->z_next, 1u);
                 j = WIDE ? 0u : (uint32_t)wave;
                 if (j >= unit) continue;
             }
@@ -385,7 +418,7 @@ __device__ __forceinline__ void z_flush(Args& a, double (&bacc)[KC][XTraits<XT>:
     for (int off = kWave / 2; off >= 1; off >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, off));
     const bool anycap = __ballot(capped) != 0ull;
     if (lane == 0) {
-        if (m) atomicMax(&a.ctrl->max_attempts, m);
+        if (m > a.ctrl->max_attempts) atomicMax(&a.ctrl->max_attempts, m);
         if (anycap) atomicOr(&a.ctrl->err, kErrTnCap);
     }
     maxatt = 0;
@@ -430,7 +463,7 @@ __device__ __forceinline__ void z_finish(Args& a, uint32_t zrank, uint32_t nz, d
     for (int off = kWave / 2; off >= 1; off >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, off));
     const bool anycap = __ballot(capped) != 0ull;
     if (lane == 0) {
-        if (m) atomicMax(&a.ctrl->max_attempts, m);
+        if (m > a.ctrl->max_attempts) atomicMax(&a.ctrl->max_attempts, m);
         if (anycap) atomicOr(&a.ctrl->err, kErrTnCap);
     }
 
