@@ -52,7 +52,7 @@ __device__ __forceinline__ void run_block(Args& a, double* lds) {
     }
     if (z) {
         ZSums<XT, KC> sums;
-        const bool any = z_take<XT, KC, R, WIDE>(a, b - a.gp, a.gz, pside, k, lds, sums);
+        const bool any = z_take<XT, KC, R, WIDE, SMALL ? kWave / R : 1>(a, b - a.gp, a.gz, pside, k, lds, sums);
         if (!pside) {
             z_finish<XT, KC, WIDE, RC>(a, b - a.gp, a.gz, lds, sums, any);
             return;

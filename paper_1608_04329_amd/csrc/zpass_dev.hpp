@@ -5,8 +5,7 @@
 // Rows are full-conditionally independent (Eq. 8), so every row is drawn in
 // parallel.  A wave owns a tile of R consecutive rows held in registers: each
 // lane loads 16-byte vectors of every row (coalesced across the wave), the
-// wave reduces the R dot products, lanes 0..R-1 draw one truncated normal
-// each, and the same registers then feed x_i^T z_i.  X is read from HBM
+// wave reduces the R dot products, its lanes draw the R truncated normals, and the same registers then feed x_i^T z_i.  X is read from HBM
 // exactly once per sweep; eta and z never touch memory.
 //
 // Truncated normal, divergence-free: with y* = 2y - 1 and mu* = y* eta the
@@ -122,11 +121,17 @@ __device__ __forceinline__ void tn_candidate(float mu, bool gauss, float theta, 
     acc = gauss ? (tg > 0.0f) : (ub < rho);
 }
 
+// G lanes per row (1 or 64 / R) try G Philox rounds, of two proposals each, at a
+// time.  More than one only where a tile's latency is all there is (the kernel of
+// short chains: N = 1000, p = 10 98 -> 90 us per 8 sweeps): a pass that streams X
+// hides the extra turns and lost 1-2 % to the selection among lanes (rare events,
+// p = 141: 554 -> 568 us per 4 sweeps).
+//
 // One tile of R rows of chain a (rows t R ..): eta = x_i beta (with wide
 // rows, the block's four quarters added through LDS), the truncated-normal
 // draws, and the tile's grid-rounded sums of x_ij z_i added into bacc.  bl
 // holds beta (column-scaled, float32) on this lane's columns.
-template <int XT, int KC, int R, bool WIDE>
+template <int XT, int KC, int R, bool WIDE, int G = 1>
 __device__ __forceinline__ void z_tile(Args& a, uint32_t t, uint32_t ksweep,
                                        const float (&bl)[KC][XTraits<XT>::VEC],
                                        double (&bacc)[KC][XTraits<XT>::VEC], uint32_t& maxatt, bool& capped,
@@ -151,14 +156,16 @@ __device__ __forceinline__ void z_tile(Args& a, uint32_t t, uint32_t ksweep,
     uint32_t coff[KC];
 #pragma unroll
     for (int kc = 0; kc < KC; ++kc) coff[kc] = min(c0 + kc * CW + lane * VEC, ld - VEC) * EB;
-    // Lane r < R will draw z for row row0 + r: position first_row + row0 + r of
-    // the stored X and y (X may arrive in row chunks), whose original row index
-    // (the rows may have been reordered) sets its Philox counters and its place
-    // in the debug outputs.  Its outcome is loaded ahead of X's rows: loaded where
-    // it is used, every tile waited for one more memory latency.
-    const uint32_t row = row0 + (uint32_t)lane;
-    const bool active = lane < R && row < N;
-    const uint32_t pos = a.first_row + min(row0 + min((uint32_t)lane, (uint32_t)R - 1u), N - 1u);
+    // Lane r < R (with G > 1 lanes r, r + R, ...) will draw z for row row0 + r:
+    // position first_row + row0 + r of the stored X and y (X may arrive in row
+    // chunks), whose original row index (the rows may have been reordered) sets
+    // its Philox counters and its place in the debug outputs.  Its outcome is
+    // loaded ahead of X's rows: loaded where it is used, every tile waited for one
+    // more memory latency.
+    const uint32_t li = G > 1 ? (uint32_t)lane & (R - 1) : (uint32_t)lane;  // row of the tile
+    const uint32_t row = row0 + li;
+    const bool active = li < (uint32_t)R && row < N;
+    const uint32_t pos = a.first_row + min(row0 + min(li, (uint32_t)R - 1u), N - 1u);
     uint32_t grow = pos;
     if (a.row_id) grow = a.row_id[pos];
     const uint32_t yv = a.y[pos];
@@ -190,6 +197,7 @@ __device__ __forceinline__ void z_tile(Args& a, uint32_t t, uint32_t ksweep,
     // instead of 6 R.  Once one row is left the steps are plain pairwise sums.
     // Lane l ends with the whole sum of row l >> (6 - log2 R).
     static_assert(R >= 1 && R <= kWave && (R & (R - 1)) == 0, "rows per tile: a power of two");
+    static_assert(G == 1 || (G == kWave / R && R < kWave && kMaxRounds % G == 0), "lanes per row");
     constexpr int LR = R >= 32 ? 5 : R >= 16 ? 4 : R >= 8 ? 3 : R >= 4 ? 2 : R >= 2 ? 1 : 0;
     float s[R];
 #pragma unroll
@@ -227,7 +235,7 @@ __device__ __forceinline__ void z_tile(Args& a, uint32_t t, uint32_t ksweep,
         eta = v;
         parity ^= 1u;
     } else {
-        eta = __shfl(s[0], lane << (6 - LR));  // row `lane`'s sum, for lanes below R
+        eta = __shfl(s[0], (int)li << (6 - LR));  // row li's sum, for li below R
     }
 
     const float ys = yv ? 1.0f : -1.0f;
@@ -239,29 +247,58 @@ __device__ __forceinline__ void z_tile(Args& a, uint32_t t, uint32_t ksweep,
     float zval = 0.0f;
     int32_t att = -1;
     bool done = !active;
-    for (uint32_t round = 0; __ballot(!done) != 0ull; ++round) {
-        if (!done) {
-            const Words4 w = draw_words(a.seed, grow, ksweep, kTagZ, round, a.chain);
+    if constexpr (G == 1) {
+        for (uint32_t round = 0; __ballot(!done) != 0ull; ++round) {
+            if (!done) {
+                const Words4 w = draw_words(a.seed, grow, ksweep, kTagZ, round, a.chain);
+                float t0, t1;
+                bool a0, a1;
+                tn_candidate(mu, gauss, theta, inv_theta, u01f(w.w0), u01f(w.w1), t0, a0);
+                tn_candidate(mu, gauss, theta, inv_theta, u01f(w.w2), u01f(w.w3), t1, a1);
+                if (a0) {
+                    zval = ys * t0;
+                    att = (int32_t)(2 * round);
+                    done = true;
+                } else if (a1) {
+                    zval = ys * t1;
+                    att = (int32_t)(2 * round + 1);
+                    done = true;
+                } else if (round + 1 >= kMaxRounds) {
+                    zval = __builtin_nanf("");
+                    done = true;
+                    capped = true;
+                }
+            }
+        }
+    } else {
+        // the row's first acceptance in the order of the rounds counts, as if one
+        // lane had tried them one after another
+        constexpr unsigned long long kRowLanes = ~0ull / ((1ull << R) - 1ull);  // bits 0, R, 2 R, ...
+        for (uint32_t round = 0; __ballot(!done) != 0ull; round += G) {
+            const uint32_t mine = round + (uint32_t)lane / R;
+            const Words4 w = draw_words(a.seed, grow, ksweep, kTagZ, mine, a.chain);
             float t0, t1;
             bool a0, a1;
             tn_candidate(mu, gauss, theta, inv_theta, u01f(w.w0), u01f(w.w1), t0, a0);
             tn_candidate(mu, gauss, theta, inv_theta, u01f(w.w2), u01f(w.w3), t1, a1);
-            if (a0) {
-                zval = ys * t0;
-                att = (int32_t)(2 * round);
-                done = true;
-            } else if (a1) {
-                zval = ys * t1;
-                att = (int32_t)(2 * round + 1);
-                done = true;
-            } else if (round + 1 >= kMaxRounds) {
-                zval = __builtin_nanf("");
-                done = true;
-                capped = true;
+            const unsigned long long hit = (__ballot(!done && (a0 || a1)) >> li) & kRowLanes;
+            const int from = hit ? (int)li + (int)__ffsll((long long)hit) - 1 : lane;
+            const float tz = __shfl(ys * (a0 ? t0 : t1), from);
+            const int32_t ta = __shfl((int32_t)(2 * mine) + (a0 ? 0 : 1), from);
+            if (!done) {
+                if (hit) {
+                    zval = tz;
+                    att = ta;
+                    done = true;
+                } else if (round + G >= kMaxRounds) {
+                    zval = __builtin_nanf("");
+                    done = true;
+                    capped = true;
+                }
             }
         }
     }
-    if (active && (!WIDE || wave == 0)) {
+    if (active && (G == 1 || lane < R) && (!WIDE || wave == 0)) {
         maxatt = max(maxatt, (uint32_t)(att + 1));
         if (a.zdbg) {
             a.zdbg[grow] = zval;
@@ -307,7 +344,7 @@ struct ZSums {
 // reserves the next unit before the block works on the current one.  helper: a
 // block that is none of the nz takes units only.  One loop for both, so that
 // the tile's code is there once.  Returns whether the block got any tile.
-template <int XT, int KC, int R, bool WIDE>
+template <int XT, int KC, int R, bool WIDE, int G>
 __device__ __forceinline__ bool z_take(Args& a, uint32_t zrank, uint32_t nz, bool helper, uint32_t ksweep, double* red,
                                        ZSums<XT, KC>& z) {
     constexpr int VEC = XTraits<XT>::VEC;
@@ -366,7 +403,7 @@ __device__ __forceinline__ bool z_take(Args& a, uint32_t zrank, uint32_t nz, boo
             j += step;
             if (now >= n_tiles) continue;
         }
-        z_tile<XT, KC, R, WIDE>(a, now, ksweep, bl, z.b, z.maxatt, z.capped, parity, eta_lds);
+        z_tile<XT, KC, R, WIDE, G>(a, now, ksweep, bl, z.b, z.maxatt, z.capped, parity, eta_lds);
     }
     return any;
 }
