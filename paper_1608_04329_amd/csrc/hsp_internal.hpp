@@ -92,6 +92,7 @@ struct Ctrl {
     unsigned long long z_epoch;    // z_count when the current launch started
     alignas(128) uint32_t err;     // kErr* bits
     alignas(128) unsigned long long bar_count;  // arrivals at p-side group barriers (monotonic)
+    alignas(128) unsigned long long hyper_count;  // group blocks past lambda and tau (zero between launches)
     alignas(128) unsigned long long z_count;    // z-pass groups finished (monotonic)
     alignas(128) uint32_t task_next;  // next factorisation task of the shared queue (zero between launches)
     alignas(128) uint32_t z_next;     // next z-pass unit of the shared remainder (zero between launches)
@@ -276,8 +277,11 @@ constexpr int kSubstP = 1536;
 __host__ __device__ constexpr uint32_t handoff_offset(uint32_t p) { return (2u * p + 8u + 15u) / 16u * 16u; }
 constexpr unsigned long long kNotReady = 0x7FF85EED5EED5EEDull;
 constexpr bool with_inverse(uint32_t nt) { return nt * (uint32_t)kTile <= (uint32_t)kSubstP; }
+// What a chain with a pass of its own does: L^-1 only from kFewTiles tiles on.
+constexpr uint32_t kFewTiles = 5;
+constexpr bool chain_inverse(uint32_t nt) { return nt >= kFewTiles && with_inverse(nt); }
 // inverse: whether the L^-1 tasks are part of the graph (a lone chain:
-// with_inverse(nt); the chains of a multi-chain pass, whose factorisation
+// chain_inverse(nt); the chains of a multi-chain pass, whose factorisation
 // does not hide under a pass of their own, leave them out)
 void chol_schedule(uint32_t nt, uint32_t gp, std::vector<uint32_t>* tasks,
                    std::vector<uint32_t>* off, bool inverse);

@@ -47,18 +47,6 @@ struct Group {
     uint64_t timeout;
 };
 
-// Block-uniform read of the failure flags that stop the group's work.
-__device__ __forceinline__ bool group_failed(const Group& g, double* lds_flag) {
-    __syncthreads();
-    if (threadIdx.x == 0)
-        lds_flag[0] = (__hip_atomic_load(&g.ctrl->err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) &
-                       (kErrNotPD | kErrTimeout)) ? 1.0 : 0.0;
-    __syncthreads();
-    const bool f = lds_flag[0] != 0.0;
-    __syncthreads();
-    return f;
-}
-
 // Sleep about 64 * n cycles between polls.  Polls are coherent loads that
 // bypass the L2 and all land on one memory channel: a tight loop from many
 // blocks slows the z pass's stream, so every wait backs off exponentially.
@@ -151,54 +139,51 @@ __device__ __forceinline__ void group_sync(Group& g) {
     __syncthreads();
 }
 
-// The first half of a group barrier: what this block stored is complete and it
-// has arrived; it does not wait for the others.
-__device__ __forceinline__ void group_arrive(Group& g) {
+// This block has drawn lambda and tau, and what it stored of them is complete; it
+// does not wait for the others.  (A count of its own: on bar_count, a block that
+// has run ahead to the next barrier would be taken for one still to come.)
+__device__ __forceinline__ void hyper_arrive(Group& g) {
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
-    if (threadIdx.x == 0) atomicAdd(&g.ctrl->bar_count, 1ull);
-    g.n++;
+    if (threadIdx.x == 0) atomicAdd(&g.ctrl->hyper_count, 1ull);
     stamp(g);
 }
 
-// The second half: every block of the group has arrived as often as this one.
-// The block's threads meet at the end.
-__device__ __forceinline__ void group_wait(Group& g) {
-    if (threadIdx.x == 0 && g.size > 1)
-        wait_count(&g.ctrl->bar_count, g.base + (unsigned long long)g.n * g.size, g.ctrl, g.timeout);
+// Every block of the group has arrived there.
+__device__ __forceinline__ void hyper_wait(Group& g) {
+    if (threadIdx.x == 0 && g.size > 1) wait_count(&g.ctrl->hyper_count, g.size, g.ctrl, g.timeout);
     __syncthreads();
 }
 
 // Arrive, then wait for the group and, with a target, for the z pass (z_count
-// >= ztarget), both polled in the same loads; false if the group is failing.
-// The failure flags count from the poll after the one that saw the group
-// complete: a block sets them before it arrives.
-__device__ __forceinline__ bool group_sync_z(Group& g, unsigned long long ztarget, double* lds_flag) {
-    group_arrive(g);
+// >= ztarget), both polled in the same loads; the last to arrive knows it from
+// its own arrival.  The failure flags are read by the caller, later: a block sets
+// them before it arrives.
+__device__ __forceinline__ void group_sync_z(Group& g, unsigned long long ztarget) {
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    g.n++;
     if (threadIdx.x == 0) {
         const unsigned long long target = g.base + (unsigned long long)g.n * g.size;
+        bool here = atomicAdd(&g.ctrl->bar_count, 1ull) + 1 >= target;
+        stamp(g);
         const uint64_t t0 = wall_clock64();
-        uint32_t nap = 1, err = 0;
-        bool here = g.size == 1;
-        for (;;) {
+        uint32_t nap = 1;
+        while (!here || ztarget) {
             const unsigned long long bars = __hip_atomic_load(&g.ctrl->bar_count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             const unsigned long long zs = __hip_atomic_load(&g.ctrl->z_count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            err = __hip_atomic_load(&g.ctrl->err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const uint32_t err = __hip_atomic_load(&g.ctrl->err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            here = here || bars >= target;
             if ((here && zs >= ztarget) || (err & kErrTimeout)) break;
-            const bool arrived = bars >= target;
             if (wall_clock64() - t0 > g.timeout) {
                 atomicOr(&g.ctrl->err, kErrTimeout);
-                err = kErrTimeout;
                 break;
             }
-            if (!(arrived && !here)) backoff(nap, here ? 32 : 8);
-            here = here || arrived;
+            backoff(nap, here ? 16 : 8);
         }
-        lds_flag[0] = (err & (kErrNotPD | kErrTimeout)) ? 1.0 : 0.0;
         if (g.trace && ztarget) g.trace[kTraceSlots - 1] = wall_clock64();
     }
     __syncthreads();
-    return lds_flag[0] == 0.0;
 }
 
 // Block-wide float64 sum in a fixed order (identical result in every block).
@@ -949,6 +934,7 @@ __device__ __forceinline__ void subst_solve(Args& a, Group& g, uint32_t rank, ui
     for (uint32_t i = rank; i < nt; i += g.size) {
         const uint32_t i0 = i * kTile, j0 = i0 + lane;
         const double b = j0 < p ? (from_sum ? ldc(&a.bsum[j0]) * a.xscale[j0] : a.b[j0]) : 0.0;
+        if (from_sum && q == 0 && j0 < p) a.b[j0] = b;
         double l[16], t[16];  // L^-1_ii: row 16 q + c, columns 16 grp ..
         const double* lp = a.Linv + (size_t)(i0 + 16 * q + c) * P + i0 + 16 * grp;
 #pragma unroll
@@ -1175,9 +1161,13 @@ __device__ __forceinline__ bool tile_factor(Args& a, Group& g, uint32_t rank, ui
     // No block waits here for block 0's lambda^-2 in memory: whoever reads it in
     // the factorisation has waited for a tile that follows from block 0's first,
     // stored later.  nu and xi wait until every block has read the old ones.
-    // (A launch without the factorisation has no later barrier: it waits.)
-    group_arrive(g);
-    if (!(a.mode & kModeBeta) || rank == g.size - 1) group_wait(g);
+    // (A launch without the factorisation has no later barrier: all wait.)
+    if (a.mode & kModeBeta) {
+        hyper_arrive(g);
+        if (rank == g.size - 1) hyper_wait(g);
+    } else {
+        group_sync(g);
+    }
     if (rank == g.size - 1) {
         if (a.mode & kModeNuXi) hyper_nu_xi(a, k);
         if (a.mode & kModeBeta)
@@ -1200,10 +1190,8 @@ __device__ __forceinline__ void tile_beta(Args& a, Group& g, uint32_t rank, uint
     double* s_noise = a.vec + p;
     const unsigned long long ztarget = (a.mode & kModeZ) ? g.zbase + a.zgroups : 0ull;
     if ((a.mode & kModeBeta) && !(a.mode & kModePost)) {
-        ok = group_sync_z(g, ztarget, flag) && ok;
+        group_sync_z(g, ztarget);
     } else {
-        // (with kModePost the earlier launch's failure flags are in memory)
-        if (a.mode & kModePost) ok = !group_failed(g, flag);
         if (ztarget && threadIdx.x == 0) wait_count(&a.ctrl->z_count, ztarget, a.ctrl, a.timeout_ticks, 64);
         __syncthreads();
     }
@@ -1219,16 +1207,23 @@ __device__ __forceinline__ void tile_beta(Args& a, Group& g, uint32_t rank, uint
         return from_sum ? ldc(&a.bsum[j]) * a.xscale[j] : a.b[j];  // unscaled exactly
     };
     double* bl = lds;
-    for (uint32_t j = threadIdx.x; j < P; j += kThreads) {
+    // (the failure flags of this launch's factorisation, or with kModePost of the
+    // earlier one's, come with b)
+    uint32_t err = 0;
+    if (threadIdx.x == 0) err = __hip_atomic_load(&g.ctrl->err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const bool by_rows = (a.mode & kModeBeta) && a.subst;  // the owner of a row takes its b
+    for (uint32_t j = threadIdx.x; !by_rows && j < P; j += kThreads) {
         const double s = b_at(j);
         if (from_sum && rank == 0 && j < p) a.b[j] = s;
         if (!big) bl[j] = s;
     }
+    if (threadIdx.x == 0) *flag = (err & (kErrNotPD | kErrTimeout)) ? 1.0 : 0.0;
     __syncthreads();
+    ok = ok && *flag == 0.0;
 
-    if ((a.mode & kModeBeta) && ok && a.subst) {
+    if (by_rows && ok) {
         subst_solve(a, g, rank, k, lds, from_sum);
-    } else if ((a.mode & kModeBeta) && ok) {
+    } else if ((a.mode & kModeBeta) && !by_rows && ok) {
         const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
         // y = L^-1 b + s, four rows per wave at a time.  L^-1 is zero above the
         // diagonal and the identity on the padding, and b is zero there, so
@@ -1371,7 +1366,10 @@ __device__ __forceinline__ void pside_end(Args& a, Group& g, uint32_t rank, uint
         if (a.x.p > (uint32_t)kSmallP && (a.mode & kModeBeta) && !(a.mode & kModePost)) {
             const uint32_t nt = padded(a.x.p) / kTile;
             for (uint32_t e = threadIdx.x; e < 2 * nt * nt; e += kThreads) a.ver[e] = 0u;
-            if (threadIdx.x == 0) a.ctrl->task_next = 0u;
+            if (threadIdx.x == 0) {
+                a.ctrl->task_next = 0u;
+                a.ctrl->hyper_count = 0ull;
+            }
         }
         if (a.subst && (a.mode & kModeBeta) && !(a.mode & kModePre)) {
             const uint32_t P = padded(a.x.p);
