@@ -36,8 +36,8 @@ hsp_status hsp_get_phase_trace(hsp_state* s, uint64_t* out, int64_t* group_block
  * with the same row operations applied to an identity block, is split into
  * tile tasks that the p-side blocks of the sweep kernel run.  nt =
  * ceil(p / 64) tiles per side, gp blocks; inverse: 1 with the L^-1 tasks,
- * 0 without them (beta then by blocked substitution), -1 as a lone chain of
- * that size has it (with them up to 24 tiles).
+ * 0 without them (beta then by blocked substitution), -1 with them up to 24
+ * tiles (a lone chain also leaves them out below 7 tiles).
  * Task code: type (bits 0-1: 0 factor a diagonal tile, 1 triangular solve of
  * a tile of the block row, 2 tile update, 3 the next diagonal tile's solve,
  * update and factorisation in one block) | part (bit 2: 0 U, 1 L^-1) | step

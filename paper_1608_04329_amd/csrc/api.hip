@@ -210,7 +210,7 @@ SweepArgs sweep_args(hsp_state* s, uint32_t mode) {
     a.trace = dev_ptr(s->trace);
     a.gp = a.gz = a.zgroups = a.block0 = a.idle = 0;
     const uint32_t nt = (s->x.p + kTile - 1) / kTile;
-    a.subst = s->x.p > (uint32_t)kSmallP && !with_inverse(nt) ? 1u : 0u;
+    a.subst = s->x.p > (uint32_t)kSmallP && !chain_inverse(nt) ? 1u : 0u;
     return a;
 }
 
@@ -325,7 +325,7 @@ hsp_status chain_impl(hsp_state* s);
 hsp_status upload_schedule(hsp_state* s) {
     const uint32_t nt = (s->x.p + kTile - 1) / kTile;
     std::vector<uint32_t> tasks, off;
-    chol_schedule(nt, s->plan.gp, &tasks, &off, with_inverse(nt));
+    chol_schedule(nt, s->plan.gp, &tasks, &off, chain_inverse(nt));
     if (s->tasks) (void)hipFree(s->tasks);
     if (s->task_off) (void)hipFree(s->task_off);
     s->tasks = s->task_off = nullptr;
@@ -1086,7 +1086,7 @@ uint32_t count_tasks(uint32_t nt) {
     uint32_t n = 0;
     for (uint32_t k = 0; k < nt; ++k) {
         const uint32_t m = nt - k - 1;
-        n += 1 + m + k + m * (m + 1) / 2 + m * (k + 1);
+        n += 1 + m + m * (m + 1) / 2 + (chain_inverse(nt) ? k + m * (k + 1) : 0);
     }
     return n;
 }

@@ -267,10 +267,10 @@ __host__ __device__ constexpr uint32_t task_code(uint32_t type, uint32_t part, u
 // (beta as two parallel triangular products) or leaves it out beyond the
 // diagonal tiles (beta by blocked substitution).  L^-1 is half of the
 // factorisation's flops; up to p = kSubstP the factorisation hides under the
-// z pass and the products make the shorter tail, beyond it the substitution's
-// latency costs less (measured: N = 1e6, p = 1500: 1.10 ms per sweep with L^-1
-// against 1.23 ms; N = 5e5, p = 2048: 1.66 against 1.29 ms; N = 2e5, p = 4096:
-// 11.5 against 6.5 ms).
+// z pass and the products make the shorter tail (but see kFewTiles), beyond it the
+// substitution's latency costs less (measured, with row steps of 5 us where they
+// now take 1.45: N = 1e6, p = 1500: 1.10 ms per sweep with L^-1 against 1.23;
+// N = 5e5, p = 2048: 1.66 against 1.29; N = 2e5, p = 4096: 11.5 against 6.5).
 constexpr int kSubstP = 1536;
 // The substitution's hand-off values (2 P doubles, P = p rounded up to 64) in a
 // chain's scratch vector, and what they hold until they are stored.
@@ -278,7 +278,13 @@ __host__ __device__ constexpr uint32_t handoff_offset(uint32_t p) { return (2u *
 constexpr unsigned long long kNotReady = 0x7FF85EED5EED5EEDull;
 constexpr bool with_inverse(uint32_t nt) { return nt * (uint32_t)kTile <= (uint32_t)kSubstP; }
 // What a chain with a pass of its own does: L^-1 only from kFewTiles tiles on.
-constexpr uint32_t kFewTiles = 5;
+// Below, the last rows of L^-1 come after the chain's end and the two products take
+// a group barrier each, while the substitution's few steps start at once.  Inverse
+// against substitution, us per sweep, N = 1e5 float32: p = 40 32.7 / 29.4, 100
+// 50.7 / 41.8, 160 64.7 / 57.6, 300 91.2 / 89.0, 360 106.1 / 103.8, 420 119.5 /
+// 120.7, 700 183.2 / 191.1; where the pass over X is the longer (N = 1.3e6, p = 141
+// and 250; N = 1e6 bfloat16, p = 300) the substitution is 0.4-0.7 % behind.
+constexpr uint32_t kFewTiles = 7;
 constexpr bool chain_inverse(uint32_t nt) { return nt >= kFewTiles && with_inverse(nt); }
 // inverse: whether the L^-1 tasks are part of the graph (a lone chain:
 // chain_inverse(nt); the chains of a multi-chain pass, whose factorisation

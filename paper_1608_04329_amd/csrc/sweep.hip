@@ -142,13 +142,15 @@ KernelFn lone_kernel(const XLayout& x, int chunks) {
 
 uint32_t max_group(const XLayout& x, int capacity) {
     const uint32_t nt = (x.p + kTile - 1) / kTile;
-    uint32_t gp = x.p <= (uint32_t)kSmallP ? 1u : nt * (nt + 1) / 2;
+    // (few tiles: block 0's chain has most of the tasks, and the substitution a
+    // block per row)
+    uint32_t gp = x.p <= (uint32_t)kSmallP ? 1u : nt < kFewTiles ? std::max(nt, nt * (nt - 1) / 2) : nt * (nt + 1) / 2;
     // the factorisation's tile tasks (each ~6 us on one block) against the
     // pass over X (~6 TB/s) on the other three quarters of the device
     double tasks = 0.0;
     for (uint32_t k = 0; x.p > (uint32_t)kSmallP && k < nt; ++k) {
         const double m = nt - k - 1;
-        tasks += 1.0 + m + m * (m + 1.0) / 2.0 + (with_inverse(nt) ? k + m * (k + 1.0) : 0.0);
+        tasks += 1.0 + m + m * (m + 1.0) / 2.0 + (chain_inverse(nt) ? k + m * (k + 1.0) : 0.0);
     }
     const double z_us = (double)x.N * x.ld * (x.xtype == 0 ? 4 : 2) / 6.0e6;
     const bool factor_bound = tasks * 6.0 / (kMaxGroup - 1) > z_us;
