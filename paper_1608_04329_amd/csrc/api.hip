@@ -106,6 +106,8 @@ struct hsp_state {
     double *vec = nullptr, *partial = nullptr, *bsum = nullptr;
     uint32_t* zgrp_count = nullptr;
     uint32_t *tasks = nullptr, *task_off = nullptr, *ver = nullptr;  // tile path schedule
+    uint32_t* runs = nullptr;  // its items without L^-1
+    uint32_t nruns = 0;
     float* beta32 = nullptr;
     float* zdbg = nullptr;
     int32_t* adbg = nullptr;
@@ -194,6 +196,8 @@ SweepArgs sweep_args(hsp_state* s, uint32_t mode) {
     a.Linv = dev_ptr(s->Linv);
     a.tasks = dev_ptr(s->tasks);
     a.task_off = dev_ptr(s->task_off);
+    a.runs = dev_ptr(static_cast<const uint32_t*>(s->runs));
+    a.nruns = s->nruns;
     a.ver = dev_ptr(s->ver);
     a.row_id = dev_ptr(static_cast<const uint32_t*>(s->row_id));
     a.vec = dev_ptr(s->vec);
@@ -272,7 +276,7 @@ void free_state(hsp_state* s) {
     void* bufs[] = {s->Xbuf, s->xexp, s->xscale, s->y, s->ctrl, s->beta, s->lam, s->nu, s->tau, s->xi, s->b, s->G, s->Gp,
                     s->A, s->Linv, s->vec, s->partial, s->beta32, s->zdbg, s->adbg,
                     s->ring_beta, s->ring_tau, s->ring_lam, s->trace, s->bsum,
-                    s->zgrp_count, s->dargs, s->dtab, s->tasks, s->task_off, s->ver, s->row_id};
+                    s->zgrp_count, s->dargs, s->dtab, s->tasks, s->task_off, s->runs, s->ver, s->row_id};
     for (void* p : bufs)
         if (p) (void)hipFree(p);
     if (s->fetch) (void)hipHostFree(s->fetch);
@@ -324,15 +328,22 @@ hsp_status chain_impl(hsp_state* s);
 // The factorisation's task lists for the plan's group size (tile path).
 hsp_status upload_schedule(hsp_state* s) {
     const uint32_t nt = (s->x.p + kTile - 1) / kTile;
-    std::vector<uint32_t> tasks, off;
-    chol_schedule(nt, s->plan.gp, &tasks, &off, chain_inverse(nt));
+    std::vector<uint32_t> tasks, off, runs;
+    const bool inverse = chain_inverse(nt);
+    chol_schedule(nt, s->plan.gp, &tasks, &off, inverse, &runs);
     if (s->tasks) (void)hipFree(s->tasks);
     if (s->task_off) (void)hipFree(s->task_off);
-    s->tasks = s->task_off = nullptr;
+    if (s->runs) (void)hipFree(s->runs);
+    s->tasks = s->task_off = s->runs = nullptr;
     HIP_TRY(dalloc(&s->tasks, tasks.size()));
     HIP_TRY(dalloc(&s->task_off, off.size()));
     HIP_TRY(hipMemcpy(s->tasks, tasks.data(), tasks.size() * 4, hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(s->task_off, off.data(), off.size() * 4, hipMemcpyHostToDevice));
+    if (!inverse) {
+        HIP_TRY(dalloc(&s->runs, runs.size()));
+        HIP_TRY(hipMemcpy(s->runs, runs.data(), runs.size() * 4, hipMemcpyHostToDevice));
+        s->nruns = (uint32_t)runs.size() - 1;
+    }
     return HSP_OK;
 }
 
@@ -1337,13 +1348,22 @@ hsp_status plan_packs(hsp_batch* b) {
             if ((pk.mc || pk.pre || pk.split) && s->x.p > (uint32_t)kSmallP) h.subst = 1u;
             if (s->x.p > (uint32_t)kSmallP && !pk.split) {
                 const uint32_t nt = (s->x.p + kTile - 1) / kTile;
-                std::vector<uint32_t> tasks, off;
-                chol_schedule(nt, h.gp, &tasks, &off, h.subst == 0u);
-                uint32_t *dt = nullptr, *doff = nullptr;
+                std::vector<uint32_t> tasks, off, runs;
+                chol_schedule(nt, h.gp, &tasks, &off, h.subst == 0u, &runs);
+                uint32_t *dt = nullptr, *doff = nullptr, *druns = nullptr;
                 if (dalloc(&dt, tasks.size()) || dalloc(&doff, off.size()))
                     return batch_fail(b, HSP_ENOMEM, "pack allocation failed");
                 pk.sched.push_back(dt);
                 pk.sched.push_back(doff);
+                h.runs = nullptr;
+                if (h.subst) {
+                    if (dalloc(&druns, runs.size())) return batch_fail(b, HSP_ENOMEM, "pack allocation failed");
+                    pk.sched.push_back(druns);
+                    if (hipMemcpy(druns, runs.data(), runs.size() * 4, hipMemcpyHostToDevice))
+                        return batch_fail(b, HSP_EHIP, "pack schedule upload");
+                    h.runs = dev_ptr(static_cast<const uint32_t*>(druns));
+                    h.nruns = (uint32_t)runs.size() - 1;
+                }
                 if (hipMemcpy(dt, tasks.data(), tasks.size() * 4, hipMemcpyHostToDevice) ||
                     hipMemcpy(doff, off.data(), off.size() * 4, hipMemcpyHostToDevice))
                     return batch_fail(b, HSP_EHIP, "pack schedule upload");

@@ -179,6 +179,8 @@ struct SweepArgs {
     HSP_GLOBAL uint64_t* trace;         // optional: kTraceSlots timestamps per group block
     HSP_GLOBAL const uint32_t* tasks;   // tile path: every group block's task list, concatenated
     HSP_GLOBAL const uint32_t* task_off;  // gp + 1 offsets into tasks
+    HSP_GLOBAL const uint32_t* runs;    // without L^-1: starts of the queue's items in tasks, and the end
+    uint32_t nruns;                     // items of the queue
     HSP_GLOBAL uint32_t* ver;           // tile path: 2 x nt x nt tile version counters (zero between launches)
     uint32_t z_static_pct;   // z pass: share of the row tiles dealt out statically (0..100)
     uint32_t z_unit;         // z pass: tiles per claimed unit of the rest (1..kZUnitMax)
@@ -289,8 +291,12 @@ constexpr bool chain_inverse(uint32_t nt) { return nt >= kFewTiles && with_inver
 // inverse: whether the L^-1 tasks are part of the graph (a lone chain:
 // chain_inverse(nt); the chains of a multi-chain pass, whose factorisation
 // does not hide under a pass of their own, leave them out)
+// runs (may be null): where the queue's items (with one block its list's) start in
+// tasks, and the end: an item is one task, or a run of updates of one tile, up to
+// kRunLen steps, that one block sums up before it stores the tile.
+constexpr uint32_t kRunLen = 4, kRunLag = 2;
 void chol_schedule(uint32_t nt, uint32_t gp, std::vector<uint32_t>* tasks,
-                   std::vector<uint32_t>* off, bool inverse);
+                   std::vector<uint32_t>* off, bool inverse, std::vector<uint32_t>* runs = nullptr);
 
 struct SweepPlan {
     uint32_t gp;

@@ -338,24 +338,37 @@ __device__ __forceinline__ void load_tile(Tile& T, const double* M, uint32_t P, 
     for (int q = 0; q < 16; ++q) T[rb + 4 * q][c] = v[q];
 }
 
+// Two tiles on their way from memory to LDS (load_tile's layout).
+struct TilePair {
+    double v[16], w[16];
+};
+__device__ __forceinline__ void fetch_tiles(TilePair& o, const double* MS, uint32_t rs, uint32_t cs, const double* MT,
+                                            uint32_t rt, uint32_t ct, uint32_t P) {
+    const int c = threadIdx.x & (kTile - 1), rb = threadIdx.x >> 6;
+    const double* s0 = MS + (size_t)(rs + rb) * P + cs + c;
+    const double* t0 = MT + (size_t)(rt + rb) * P + ct + c;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+        o.v[q] = ldc(s0 + (size_t)(4 * q) * P);
+        o.w[q] = ldc(t0 + (size_t)(4 * q) * P);
+    }
+}
+__device__ __forceinline__ void put_tiles(const TilePair& o, Tile& S, Tile& T) {
+    const int c = threadIdx.x & (kTile - 1), rb = threadIdx.x >> 6;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+        S[rb + 4 * q][c] = o.v[q];
+        T[rb + 4 * q][c] = o.w[q];
+    }
+}
+
 // load_tile for two tiles with every global load issued before any LDS store.
 __device__ __forceinline__ void load_tiles(Tile& S, const double* MS, uint32_t rs, uint32_t cs,
                                            Tile& T, const double* MT, uint32_t rt, uint32_t ct,
                                            uint32_t P) {
-    const int c = threadIdx.x & (kTile - 1), rb = threadIdx.x >> 6;
-    const double* s0 = MS + (size_t)(rs + rb) * P + cs + c;
-    const double* t0 = MT + (size_t)(rt + rb) * P + ct + c;
-    double v[16], w[16];
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-        v[q] = ldc(s0 + (size_t)(4 * q) * P);
-        w[q] = ldc(t0 + (size_t)(4 * q) * P);
-    }
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-        S[rb + 4 * q][c] = v[q];
-        T[rb + 4 * q][c] = w[q];
-    }
+    TilePair x;
+    fetch_tiles(x, MS, rs, cs, MT, rt, ct, P);
+    put_tiles(x, S, T);
 }
 
 // ---- 64 x 64 x 64 tile products on the FP64 matrix cores ----------------------
@@ -369,15 +382,18 @@ struct MAcc {
     Acc4 v[2][2];
 };
 
-// acc = S^T T
-__device__ __forceinline__ void gemm_tn(const Tile& S, const Tile& T, MAcc& acc) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int i0 = 32 * (wave >> 1), j0 = 32 * (wave & 1);
-    const int kr = lane >> 4, cc = lane & 15;
+__device__ __forceinline__ void zero_acc(MAcc& acc) {
 #pragma unroll
     for (int bi = 0; bi < 2; ++bi)
 #pragma unroll
         for (int bj = 0; bj < 2; ++bj) acc.v[bi][bj] = Acc4{0.0, 0.0, 0.0, 0.0};
+}
+
+// acc += S^T T
+__device__ __forceinline__ void gemm_tn(const Tile& S, const Tile& T, MAcc& acc) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int i0 = 32 * (wave >> 1), j0 = 32 * (wave & 1);
+    const int kr = lane >> 4, cc = lane & 15;
 #pragma unroll 4
     for (int q0 = 0; q0 < kTile; q0 += 4) {
         const double a0 = S[q0 + kr][i0 + cc], a1 = S[q0 + kr][i0 + 16 + cc];
@@ -691,6 +707,31 @@ __device__ __forceinline__ void syrk_block(const Tile& U, Tile& D, int I, int J,
     for (int r = 0; r < 4; ++r) D[16 * I + kr + 4 * r][16 * J + cc] = fma(-1.0, acc[r], old[r]);
 }
 
+// Wave 0: wait for the inputs of a run of n updates of tile (i, j) from step k on:
+// U_k'i and U_k'j final for each step k', and the tile updated up to k; false if
+// the group is failing or the wait timed out.
+__device__ __forceinline__ bool wait_run(const uint32_t* vU, uint32_t nt, uint32_t k, uint32_t n, uint32_t i, uint32_t j,
+                                         Ctrl* ctrl, uint64_t timeout) {
+    const uint32_t l = threadIdx.x & 63u, s = l < n ? l : l - n;
+    const bool tile = l >= 2 * n;  // (lanes past 2 n all look at the tile itself)
+    const uint32_t* v = tile ? vU + i * nt + j : vU + (k + s) * nt + (l < n ? i : j);
+    const uint32_t need = tile ? k : k + s + 1;
+    uint64_t t0 = 0;
+    uint32_t nap = 1;
+    for (int it = 0;; ++it) {
+        const uint32_t got = __hip_atomic_load(const_cast<uint32_t*>(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (__ballot(got < need) == 0ull) return true;
+        if (it == 0) t0 = wall_clock64();
+        if (__hip_atomic_load(&ctrl->err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & (kErrTimeout | kErrNotPD))
+            return false;
+        if (wall_clock64() - t0 > timeout) {
+            if (l == 0) atomicOr(&ctrl->err, kErrTimeout);
+            return false;
+        }
+        backoff(nap, 8);
+    }
+}
+
 // Run block `rank`'s list of factorisation tasks.  Tile versions: U tile
 // (i, j), i <= j, has had v of its i updates (plus 1 once final); L^-1 tile
 // (i, j), j <= i, v of its i - j updates (plus 1 once final).  Each task waits
@@ -710,20 +751,36 @@ __device__ __forceinline__ bool run_tasks(Args& a, Group& g, uint32_t rank, doub
     // starts one.  The claimed index travels to the block through LDS.
     const bool queue = g.size > 1 && rank > 0;
     const uint32_t n0 = queue ? a.task_off[1] : 0u, n1 = queue ? a.task_off[2] : a.task_off[1];
+    // With runs (no L^-1) the queue's items, and a lone block's, are numbered by
+    // a.runs; an item is claimed when the block is free, a reservation would hold
+    // up the tasks next to the chain for as long as a run takes.
+    const bool by_runs = a.runs && (queue || g.size == 1);
+    uint32_t x = 0;
     uint32_t n = n0;
     if (queue) {
         if (threadIdx.x == 0) *next_lds = (double)atomicAdd(&a.ctrl->task_next, 1u);
         __syncthreads();
-        n = n0 + (uint32_t)*next_lds;
+        x = (uint32_t)*next_lds;
+        n = n0 + x;
         __syncthreads();
     }
-    while (n < n1) {
+    while (by_runs ? x < a.nruns : n < n1) {
+        uint32_t len = 1;
+        if (by_runs) {
+            n = a.runs[x];
+            len = a.runs[x + 1] - n;
+        }
         const uint32_t code = a.tasks[n];
         const uint32_t type = code & 3u, part = (code >> 2) & 1u, kb = (code >> 3) & kTaskField,
                        ib = (code >> 11) & kTaskField, jb = (code >> 19) & kTaskField;
         uint32_t reserved = 0;
-        if (threadIdx.x == 0) {
-            if (queue) reserved = atomicAdd(&a.ctrl->task_next, 1u);
+        if (len > 1) {
+            if (threadIdx.x < (uint32_t)kWave) {
+                const bool w = wait_run(vU, nt, kb, len, ib, jb, a.ctrl, g.timeout);
+                if (threadIdx.x == 0) *flag = w ? 0.0 : 1.0;
+            }
+        } else if (threadIdx.x == 0) {
+            if (queue && !by_runs) reserved = atomicAdd(&a.ctrl->task_next, 1u);
             uint32_t* v[3] = {nullptr, nullptr, nullptr};
             uint32_t need[3] = {0u, 0u, 0u};
             int nv;
@@ -851,6 +908,37 @@ __device__ __forceinline__ bool run_tasks(Args& a, Group& g, uint32_t rank, doub
             put_col(part == 0 ? a.A : a.Linv, P, k0, j0, x);
             out = part == 0 ? &vU[kb * nt + jb] : &vL[kb * nt + jb];
             val = part == 0 ? kb + 1 : kb - jb + 1;
+        } else if (len > 1) {
+            // A_ij -= sum over the run's steps of U_ki^T U_kj: the tile is read and
+            // stored once, and each step's tiles are on their way during the
+            // products of the step before.  (One task per step, each with its own
+            // wait, three loads and a store, kept the FP64 matrix cores 40 % busy:
+            // p = 7003, 8.5 us per task on each of two blocks per unit.)
+            MTile old;
+            load_tile_m(old, kb == 0 ? a.Gp : a.A, P, ib * kTile, jb * kTile, kb == 0 && ib == jb, tau, a.lam_m2, p);
+            TilePair next;
+            fetch_tiles(next, a.A, k0, ib * kTile, a.A, k0, jb * kTile, P);
+            put_tiles(next, S, T);
+            __syncthreads();
+            stamp(g);
+            MAcc acc;
+            zero_acc(acc);
+            for (uint32_t s = 0; s < len; ++s) {
+                const bool more = s + 1 < len;
+                const uint32_t ks = (kb + s + 1) * kTile;
+                if (more) fetch_tiles(next, a.A, ks, ib * kTile, a.A, ks, jb * kTile, P);
+                // claim the next item while the last products run
+                if (!more && queue && threadIdx.x == 0) reserved = atomicAdd(&a.ctrl->task_next, 1u);
+                gemm_tn(S, T, acc);
+                if (more) {
+                    __syncthreads();  // every wave has read S and T
+                    put_tiles(next, S, T);
+                    __syncthreads();
+                }
+            }
+            put_tile_m(a.A, P, ib * kTile, jb * kTile, acc, -1.0, old);
+            out = &vU[ib * nt + jb];
+            val = kb + len;
         } else {
             // A_ij -= U_ki^T U_kj  or  L^-1_ij -= U_ki^T L^-1_kj; the three
             // tiles' loads are in flight together
@@ -864,15 +952,20 @@ __device__ __forceinline__ bool run_tasks(Args& a, Group& g, uint32_t rank, doub
             __syncthreads();
             stamp(g);
             MAcc acc;
+            zero_acc(acc);
             gemm_tn(S, T, acc);
             put_tile_m(part == 0 ? a.A : a.Linv, P, ib * kTile, jb * kTile, acc, -1.0, old);
             out = part == 0 ? &vU[ib * nt + jb] : &vL[ib * nt + jb];
             val = part == 0 ? kb + 1 : kb - jb + 1;
         }
-        if (threadIdx.x == 0 && queue) *next_lds = (double)reserved;
+        if (threadIdx.x == 0 && queue) {
+            if (by_runs && len == 1) reserved = atomicAdd(&a.ctrl->task_next, 1u);
+            *next_lds = (double)reserved;
+        }
         publish(out, val, out2, 1u);
         stamp(g);
-        n = queue ? n0 + (uint32_t)*next_lds : n + 1;
+        x = queue ? (uint32_t)*next_lds : x + 1;
+        n = queue ? n0 + x : n + 1;
         __syncthreads();
     }
     return true;

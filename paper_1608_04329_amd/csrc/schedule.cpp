@@ -26,7 +26,9 @@
 // durations decide who runs what.  A task starts in the simulation only after
 // its inputs finished, so the order is topological: the earliest unfinished
 // task always has its inputs and has been claimed by a block that is free to
-// run it, and the group cannot deadlock.
+// run it, and the group cannot deadlock.  Without L^-1 a tile's updates come in
+// runs (update_run): one item of the queue, which starts in the simulation when
+// the inputs of all its updates are there.
 #include <algorithm>
 #include <cstdint>
 #include <queue>
@@ -46,14 +48,25 @@ struct Task {
     std::vector<uint32_t> succ;
     uint32_t ndep = 0;
     double prio = 0.0;  // longest path from the start of this task to the end
+    uint32_t n = 1;     // updates of one tile in a row (a run), steps k, k + 1, ...
 };
 
 }  // namespace
 
+// The run of updates of a tile of row i that update k belongs to: without L^-1,
+// chunks of kRunLen steps up to the row's last kRunLag updates, which are single
+// (the last ones are on the way to the chain).  A function of k and i alone, so
+// that a tile is summed alike whatever the group's size.
+static void update_run(uint32_t k, uint32_t i, bool inverse, uint32_t* first, uint32_t* n) {
+    const uint32_t m = !inverse && i > kRunLag ? i - kRunLag : 0;
+    *first = k < m ? k / kRunLen * kRunLen : k;
+    *n = k < m ? std::min(*first + kRunLen, m) - *first : 1;
+}
+
 void chol_schedule(uint32_t nt, uint32_t gp, std::vector<uint32_t>* tasks,
-                   std::vector<uint32_t>* off, bool inverse) {
+                   std::vector<uint32_t>* off, bool inverse, std::vector<uint32_t>* runs) {
     // rough costs in units of one tile task
-    const double c_potrf = 3.5, c_panel = 4.5, c_trsm = 1.0, c_gemm = 1.0;
+    const double c_potrf = 1.5, c_panel = 2.0, c_trsm = 1.0, c_gemm = 1.0, c_run0 = 0.7, c_run = 0.4;
     const bool chain = gp > 1;  // block 0 owns the critical chain
     const bool inv = inverse;  // the L^-1 tasks (TRSM_L, GEMM_L) are part of the graph
     std::vector<Task> t;
@@ -65,8 +78,8 @@ void chol_schedule(uint32_t nt, uint32_t gp, std::vector<uint32_t>* tasks,
     std::vector<int64_t> gemm_u((size_t)nt * nt * nt, -1), gemm_l((size_t)nt * nt * nt, -1);
     std::vector<bool> on_chain;
     std::vector<std::pair<int64_t, int64_t>> panel_first;  // (first half, second half)
-    auto add = [&t, &on_chain](uint32_t code, double cost, bool ch) {
-        t.push_back(Task{code, cost, {}, 0, 0.0});
+    auto add = [&t, &on_chain](uint32_t code, double cost, bool ch, uint32_t n = 1) {
+        t.push_back(Task{code, cost, {}, 0, 0.0, n});
         on_chain.push_back(ch);
         return (int64_t)t.size() - 1;
     };
@@ -88,8 +101,13 @@ void chol_schedule(uint32_t nt, uint32_t gp, std::vector<uint32_t>* tasks,
         for (uint32_t j = 0; inv && j < k; ++j) trsm_l[k * nt + j] = add(task_code(kTaskTrsm, 1, k, k, j), c_trsm, false);
         for (uint32_t i = k + 1; i < nt; ++i) {
             for (uint32_t j = i; j < nt; ++j)
-                if (!(chain && i == k + 1 && j == k + 1))
-                    gemm_u[idx3(k, i, j)] = add(task_code(kTaskGemm, 0, k, i, j), c_gemm, false);
+                if (!(chain && i == k + 1 && j == k + 1)) {
+                    uint32_t first, n;
+                    update_run(k, i, inv, &first, &n);
+                    gemm_u[idx3(k, i, j)] = k > first ? gemm_u[idx3(first, i, j)]
+                                                      : add(task_code(kTaskGemm, 0, k, i, j),
+                                                            n > 1 ? c_run0 + c_run * n : c_gemm, false, n);
+                }
             for (uint32_t j = 0; inv && j <= k; ++j)
                 gemm_l[idx3(k, i, j)] = add(task_code(kTaskGemm, 1, k, i, j), c_gemm, false);
         }
@@ -140,18 +158,22 @@ void chol_schedule(uint32_t nt, uint32_t gp, std::vector<uint32_t>* tasks,
         t[e.first].succ.push_back((uint32_t)e.second);
         t[e.second].ndep++;
     }
-    // priorities: longest path to the end (tasks are not created in topological
-    // order any more, so iterate to a fixed point over the edge list)
-    for (auto& x : t) x.prio = x.cost;
-    for (bool changed = true; changed;) {
-        changed = false;
-        for (auto it = edges.rbegin(); it != edges.rend(); ++it) {
-            const double v = t[it->first].cost + t[it->second].prio;
-            if (v > t[it->first].prio) {
-                t[it->first].prio = v;
-                changed = true;
-            }
-        }
+    // priorities: longest path to the end, in reverse topological order (tasks
+    // are not created in one)
+    std::vector<uint32_t> topo, open(t.size());
+    topo.reserve(t.size());
+    for (uint32_t n = 0; n < t.size(); ++n) {
+        open[n] = t[n].ndep;
+        if (!open[n]) topo.push_back(n);
+    }
+    for (size_t x = 0; x < topo.size(); ++x)
+        for (uint32_t s2 : t[topo[x]].succ)
+            if (--open[s2] == 0) topo.push_back(s2);
+    for (size_t x = topo.size(); x-- > 0;) {
+        Task& q = t[topo[x]];
+        double best = 0.0;
+        for (uint32_t s2 : q.succ) best = std::max(best, t[s2].prio);
+        q.prio = q.cost + best;
     }
     // list scheduling: chain tasks on block 0, the rest on blocks 1.. (or all on
     // block 0 when the group has one block)
@@ -183,7 +205,7 @@ void chol_schedule(uint32_t nt, uint32_t gp, std::vector<uint32_t>* tasks,
     } else {
         workers[1].push(Worker{0.0, 0});
     }
-    std::vector<std::vector<uint32_t>> lists(gp);
+    std::vector<std::vector<uint32_t>> lists(gp);    // tasks by block
     std::vector<std::pair<double, uint32_t>> order;  // (simulated start, task)
     // Event simulation on one clock that never goes back: at each instant,
     // every free block of a class takes the highest-priority task that is
@@ -204,7 +226,7 @@ void chol_schedule(uint32_t nt, uint32_t gp, std::vector<uint32_t>* tasks,
                 ready[c].pop();
                 const double fin = clock + t[id].cost;
                 if (t[id].code != kNoTask) {
-                    lists[w.b].push_back(t[id].code);
+                    lists[w.b].push_back(id);
                     order.push_back({clock, id});
                 }
                 ++done;
@@ -233,20 +255,23 @@ void chol_schedule(uint32_t nt, uint32_t gp, std::vector<uint32_t>* tasks,
     // blocks take tasks from, one at a time, as they become free.
     tasks->clear();
     off->assign(1, 0u);
-    if (!chain) {
-        tasks->insert(tasks->end(), lists[0].begin(), lists[0].end());
+    if (runs) runs->clear();
+    auto put = [&](uint32_t id, bool item) {
+        if (runs && item) runs->push_back((uint32_t)tasks->size());
+        for (uint32_t q = 0; q < t[id].n; ++q) tasks->push_back(t[id].code + (q << 3));  // step k + q
+    };
+    for (uint32_t id : lists[0]) put(id, !chain);
+    off->push_back((uint32_t)tasks->size());
+    if (chain) {
+        std::stable_sort(order.begin(), order.end(),
+                         [](const std::pair<double, uint32_t>& x, const std::pair<double, uint32_t>& y) {
+                             return x.first < y.first;
+                         });
+        for (auto& o : order)
+            if (!on_chain[o.second]) put(o.second, true);
         off->push_back((uint32_t)tasks->size());
-        return;
     }
-    tasks->insert(tasks->end(), lists[0].begin(), lists[0].end());
-    off->push_back((uint32_t)tasks->size());
-    std::stable_sort(order.begin(), order.end(),
-                     [](const std::pair<double, uint32_t>& x, const std::pair<double, uint32_t>& y) {
-                         return x.first < y.first;
-                     });
-    for (auto& o : order)
-        if (!on_chain[o.second]) tasks->push_back(t[o.second].code);
-    off->push_back((uint32_t)tasks->size());
+    if (runs) runs->push_back((uint32_t)tasks->size());
 }
 
 }  // namespace hsp
