@@ -293,8 +293,13 @@ constexpr bool chain_inverse(uint32_t nt) { return nt >= kFewTiles && with_inver
 // does not hide under a pass of their own, leave them out)
 // runs (may be null): where the queue's items (with one block its list's) start in
 // tasks, and the end: an item is one task, or a run of updates of one tile, up to
-// kRunLen steps, that one block sums up before it stores the tile.
-constexpr uint32_t kRunLen = 4, kRunLag = 2;
+// kRunLen steps, that one block sums up before it stores the tile.  Runs of 4, of 8
+// and of 16 up to half of the updates still to come, ms per sweep: p = 2000, N = 2e4
+// float32 0.54 / 0.53 / 0.53, p = 4096, N = 2e5 float32 1.39 / 1.37 / 1.36, p = 7003,
+// N = 6e4 bfloat16 3.63 / 3.47 / 3.41, p = 10000, N = 5e4 bfloat16 9.00 / 8.35 / 8.06
+// (runs of 8 up to the last two updates, which hold up the chain: 0.58, 1.38, 3.56,
+// 8.55).
+constexpr uint32_t kRunLen = 16;
 void chol_schedule(uint32_t nt, uint32_t gp, std::vector<uint32_t>* tasks,
                    std::vector<uint32_t>* off, bool inverse, std::vector<uint32_t>* runs = nullptr);
 

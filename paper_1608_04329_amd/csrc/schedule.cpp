@@ -54,13 +54,14 @@ struct Task {
 }  // namespace
 
 // The run of updates of a tile of row i that update k belongs to: without L^-1,
-// chunks of kRunLen steps up to the row's last kRunLag updates, which are single
-// (the last ones are on the way to the chain).  A function of k and i alone, so
-// that a tile is summed alike whatever the group's size.
+// half of the updates still to come, at most kRunLen (the last ones, on the way to
+// the chain, are single).  A function of k and i alone, so that a tile is summed
+// alike whatever the group's size.
 static void update_run(uint32_t k, uint32_t i, bool inverse, uint32_t* first, uint32_t* n) {
-    const uint32_t m = !inverse && i > kRunLag ? i - kRunLag : 0;
-    *first = k < m ? k / kRunLen * kRunLen : k;
-    *n = k < m ? std::min(*first + kRunLen, m) - *first : 1;
+    uint32_t f = inverse ? k : 0, len = 1;
+    while (!inverse && f + (len = std::max(1u, std::min(kRunLen, (i - f) / 2))) <= k) f += len;
+    *first = f;
+    *n = len;
 }
 
 void chol_schedule(uint32_t nt, uint32_t gp, std::vector<uint32_t>* tasks,

@@ -158,10 +158,23 @@ uint32_t max_group(const XLayout& x, int capacity) {
         // the factorisation hides under the z pass: a quarter of the device at most
         if (gp > (uint32_t)kMaxGroup) gp = kMaxGroup;
         if (gp > (uint32_t)capacity / 4) gp = capacity / 4 > 0 ? capacity / 4 : 1;
-    } else {
+    } else if (with_inverse(nt)) {
         // the factorisation outweighs the pass over X: three quarters
         const uint32_t cap = (uint32_t)capacity * 3 / 4;
         if (gp > cap) gp = cap > 0 ? cap : 1;
+    } else {
+        // Without L^-1 the updates run at ~4.2 us a task and block, and block 0's
+        // chain at ~17 us a step: more than tasks / (2 nt) blocks would only wait for
+        // the chain.  The pass over X keeps its share of the time, which is the
+        // chain's or that of all the work on all blocks, and a sixteenth.  us per sweep at 128 / 192 / 256 / 320 / 384 / 448 / 480 blocks:
+        // p = 2000, N = 2e4 float32 525 / 528 / 536 / - / 576 (96: 522, 64: 607);
+        // p = 3000, N = 1e4 float32 902 / 783 / 796 / - / 891; p = 4096, N = 2e5
+        // float32 1870 / 1448 / 1390 / 1503 / 1589 / 2097; p = 7003, N = 6e4 bfloat16
+        // - / - / 4186 / 3980 / 3773 / 3620 / 3645; p = 10000, N = 5e4 bfloat16
+        // - / - / 11284 / - / 9818 / 9313 / 9047.
+        const double share = 1.0 - z_us / std::max(17.0 * nt, z_us + tasks * 4.2 / capacity);
+        const uint32_t want = std::max((uint32_t)kMaxGroup, (uint32_t)std::min(tasks / (2.0 * nt), share * capacity));
+        gp = std::max(1u, std::min({gp, want, (uint32_t)capacity * 15 / 16}));
     }
     return gp;
 }

@@ -1,10 +1,11 @@
 """The ways beta is solved, at the sizes where one takes over from another: one
 block (p <= 16), substitution with few tiles (up to six 64-wide tiles), L^-1 and
-two products from seven.  One sweep of a lone chain, and three more of which the
-last is compared, against one float64 oracle sweep each from the chain's own
-state.  Bars: lambda, tau, nu, xi are float64 from the same state (1e-10 leaves
-room for sums in another order); a relative change of 1e-5 of X^T z (float32
-sums), propagated through Q^-1, bounds beta."""
+two products from seven, substitution again beyond 24 (the updates in runs).
+One sweep of a lone chain, and three more of which the last is compared, against
+one float64 oracle sweep each from the chain's own state.  Bars: lambda, tau,
+nu, xi are float64 from the same state (1e-10 leaves room for sums in another
+order); a relative change of 1e-5 of X^T z (float32 sums), propagated through
+Q^-1, bounds beta."""
 import numpy as np
 import pytest
 
@@ -14,7 +15,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("N,p", [(700, 2), (1000, 3), (2000, 15), (5003, 16), (900, 17), (1501, 64), (1501, 65),
-                                 (2003, 128), (2003, 193), (1700, 384), (1700, 385), (1900, 448)])
+                                 (2003, 128), (2003, 193), (1700, 384), (1700, 385), (1900, 448), (2300, 1537),
+                                 (2300, 2113)])
 def test_one_sweep_matches_the_oracle(orc, N, p):
     torch, hsp = need_gpu()
     d = dataset(N, p, 900 + p)
