@@ -97,8 +97,8 @@ typedef struct {
                                and stream it through the GPU in row chunks every
                                sweep (designs larger than device memory); 0 (default):
                                X resident in device memory */
-    int64_t stream_rows;    /* with x_stream: rows per chunk (rounded to the row
-                               splits of the one-time X^T X); 0 (default): about
+    int64_t stream_rows;    /* with x_stream: rows per chunk (rounded down to a
+                               multiple of 64, at least 64); 0 (default): about
                                256 MB of X per chunk */
 } hsp_options;
 
@@ -129,9 +129,8 @@ void hsp_default_options(hsp_options* opt);
  * With x_stream, the library's copy of X lives in pinned host memory and
  * every sweep streams it through two device chunk buffers (copies on a
  * stream of their own, overlapped with the z pass of the previous chunk);
- * the chain draws bit for bit what a resident chain draws whenever the row
- * splits of X^T X are the same (always when about 256 MB of X holds one
- * split).  Throughput is then bound by the host-to-device link.
+ * the chain draws bit for bit what a resident chain draws.  Throughput is then
+ * bound by the host-to-device link.
  * Errors: HSP_EINVAL if N < 2, p < 2, N >= 2^32, p > hsp_max_p(), a y_i is
  * not 0/1 or an X entry is not finite; HSP_ENOMEM; HSP_EHIP.
  */
@@ -150,8 +149,9 @@ int64_t hsp_max_p(void);
  * products are summed on the FP64 matrix cores in a fixed order (the same G,
  * bit for bit, on every call).  G: device buffer of p x p doubles, row-major,
  * written whole (symmetric).  Allocates a device workspace of 32 KB x (64-wide
- * tile pairs of G) x (row splits) for p <= 128, else 128 KB x (128-wide tile
- * pairs) x (row splits), and frees it before returning; runs on hip_stream (NULL: the null stream) and waits for it.
+ * tile pairs of G) x (row splits) for p <= 128, else at most 128 KB x (128-wide
+ * tile pairs) x (row splits), and frees it before returning; runs on hip_stream
+ * (NULL: the null stream) and waits for it.
  * Errors: HSP_EINVAL (NULL pointers, N < 1, p < 1, ld < p, N or ld >= 2^32,
  * unknown x_type); HSP_ENOMEM; HSP_EHIP.
  */

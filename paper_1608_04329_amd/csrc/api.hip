@@ -616,8 +616,9 @@ hsp_status create_impl(hsp_state* s, const float* X, const uint8_t* y, int64_t N
     if (p > kSmallP) HIP_TRY(dalloc(&s->Gp, P * P));
     {
         double* work = nullptr;
-        HIP_TRY(dalloc(&work, gram_work_doubles(s->x, s->num_cus)));
-        hipError_t e = gram_launch(s->x, s->xexp, s->G, work, s->num_cus, s->stream);
+        const GramGeometry gg = gram_geometry(s->x, s->num_cus);
+        HIP_TRY(dalloc(&work, gram_work_doubles(gg)));
+        hipError_t e = gram_launch(s->x, gg, s->xexp, s->G, work, gram_work_doubles(gg), s->stream);
         if (!e && s->Gp) e = pad_gram_launch(s->G, (uint32_t)p, (uint32_t)P, s->Gp, s->stream);
         if (!e) e = hipStreamSynchronize(s->stream);
         (void)hipFree(work);
@@ -627,11 +628,11 @@ hsp_status create_impl(hsp_state* s, const float* X, const uint8_t* y, int64_t N
 }
 
 // X kept in pinned host memory and streamed through the GPU (x_stream).
-// Creation makes two passes over X in chunks of whole Gram row splits, with
-// the same kernels as the resident path: the column maxima, then each chunk
-// scaled (and rounded to bfloat16) into the library layout, validated, its
-// Gram partial tiles formed, and copied out to the pinned buffer.  G is then
-// summed over the splits in order, as for a resident X.
+// Creation makes two passes over X in chunks of rows, with the same kernels as
+// the resident path: the column maxima, then each chunk scaled (and rounded to
+// bfloat16) into the library layout, validated, its part of the Gram partial
+// tiles formed, and copied out to the pinned buffer.  G is then summed over the
+// splits in order, as for a resident X.
 hsp_status create_stream_impl(hsp_state* s, const float* X, const uint8_t* y, int64_t N, int64_t p) {
     hsp_status st0 = setup_impl(s);
     if (st0) return st0;
@@ -649,10 +650,8 @@ hsp_status create_stream_impl(hsp_state* s, const float* X, const uint8_t* y, in
     full.N = (uint32_t)N;
     full.p = (uint32_t)p;
     full.ld = ld;
-    const GramGeometry gg = gram_geometry(full, s->num_cus, budget);
-    const uint64_t per = std::max<uint64_t>(1, budget / gg.rows_per_split);
-    s->chunk_rows = (uint32_t)std::min<uint64_t>((uint64_t)gg.rows_per_split * per,
-                                                 ((uint64_t)N + 63) / 64 * 64);
+    const GramGeometry gg = gram_geometry(full, s->num_cus);
+    s->chunk_rows = (uint32_t)std::min<uint64_t>(budget, ((uint64_t)N + 63) / 64 * 64);
     s->nchunks = (uint32_t)(((uint64_t)N + s->chunk_rows - 1) / s->chunk_rows);
     HIP_TRY(hipHostMalloc(&s->Xhost, (size_t)N * row_bytes, hipHostMallocDefault));
     for (int i = 0; i < 2; ++i) HIP_TRY(dalloc(reinterpret_cast<char**>(&s->stage[i]), (size_t)s->chunk_rows * row_bytes));
@@ -710,7 +709,7 @@ hsp_status create_stream_impl(hsp_state* s, const float* X, const uint8_t* y, in
         const size_t r0 = (size_t)c * s->chunk_rows;
         if (!e) e = pack_x_launch(src, cl, s->xexp, s->stream);
         if (!e) e = validate_launch(cl, s->y + r0, s->ctrl, s->stream);
-        if (!e) e = gram_chunk_launch(cl, gg, (uint32_t)(r0 / gg.rows_per_split), work, s->stream);
+        if (!e) e = gram_chunk_launch(cl, gg, r0, (uint64_t)N, work, s->stream);
         if (!e) e = hipMemcpyAsync(static_cast<char*>(s->Xhost) + r0 * row_bytes, s->stage[0], rows * row_bytes,
                                    hipMemcpyDeviceToHost, s->stream);
         if (!e) e = hipStreamSynchronize(s->stream);  // the stage and raw buffers are reused
@@ -2163,8 +2162,9 @@ hsp_status hsp_gram(const void* X, int32_t x_type, int64_t N, int64_t p, int64_t
     if (hsp_status st = gram_device(&num_cus)) return st;
     const hipStream_t st = static_cast<hipStream_t>(hip_stream);
     double* work = nullptr;
-    HIP_TRY(dalloc(&work, gram_work_doubles(x, num_cus)));
-    hipError_t e = gram_launch(x, nullptr, G, work, num_cus, st);
+    const GramGeometry gg = gram_geometry(x, num_cus);
+    HIP_TRY(dalloc(&work, gram_work_doubles(gg)));
+    hipError_t e = gram_launch(x, gg, nullptr, G, work, gram_work_doubles(gg), st);
     if (!e) e = hipStreamSynchronize(st);
     (void)hipFree(work);
     HIP_TRY(e);
@@ -2178,7 +2178,8 @@ hsp_status hsp_gram_noalloc(const void* X, int32_t x_type, int64_t N, int64_t p,
     if (const char* msg = gram_args(X, x_type, N, p, ld, G, &x)) return fail(nullptr, HSP_EINVAL, msg);
     int num_cus = 0;
     if (hsp_status st = gram_device(&num_cus)) return st;
-    const size_t need = gram_pair_doubles(x, num_cus);
+    const GramGeometry gg = gram_geometry(x, num_cus);
+    const size_t need = gram_pair_doubles(gg);
     if (need > kGramScratchDoubles)
         return fail(nullptr, HSP_EINVAL,
                     "hsp_gram_noalloc: one tile pair needs " + std::to_string(need * 8) +
@@ -2187,7 +2188,7 @@ hsp_status hsp_gram_noalloc(const void* X, int32_t x_type, int64_t N, int64_t p,
     double* work = nullptr;
     HIP_TRY(gram_scratch(&work));
     const hipStream_t st = static_cast<hipStream_t>(hip_stream);
-    HIP_TRY(gram_launch_chunked(x, nullptr, G, work, kGramScratchDoubles, num_cus, st));
+    HIP_TRY(gram_launch(x, gg, nullptr, G, work, kGramScratchDoubles, st));
     HIP_TRY(hipStreamSynchronize(st));
     return HSP_OK;
 }

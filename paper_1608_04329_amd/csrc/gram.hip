@@ -86,9 +86,9 @@ __global__ void validate_kernel(XLayout x, const uint8_t* __restrict__ y, Ctrl* 
 // Bound by the matrix cores: one operation takes 64 cycles of a SIMD, and with
 // NB = 4 a wave reads and widens 8 fragments per 16 operations (NB = 2: 4 per
 // 4), so LDS, conversions and the loads of X mostly hide behind them.  N = 1e6,
-// p = 1000 float32: 18.2 ms (59 TFLOP/s of the blocks computed; a large library
+// p = 1000 float32: 16.9 ms (64 TFLOP/s of the blocks computed; a large library
 // product reaches 73), against 80 ms with 64-wide tiles staged as float64 by
-// 4-byte loads; N = 3e5, p = 777 bfloat16: 14.3 -> 4.25 ms.
+// 4-byte loads; N = 3e5, p = 777 bfloat16: 14.3 -> 3.4 ms.
 constexpr int kGramK = 32;  // rows of X per stage
 typedef double GAcc __attribute__((ext_vector_type(4)));
 
@@ -96,13 +96,6 @@ typedef double GAcc __attribute__((ext_vector_type(4)));
 // read touches lie in different quarters of the 64 banks.
 template <int NB>
 constexpr int gram_stride() { return 32 * NB + 16; }
-
-__device__ __forceinline__ void pair_of(uint32_t pair, uint32_t nt, uint32_t& ti, uint32_t& tj) {
-    uint32_t r = 0, idx = pair;
-    while (idx >= nt - r) { idx -= nt - r; ++r; }
-    ti = r;
-    tj = r + idx;
-}
 
 // VN consecutive columns from col of one row, as 16 bytes of X.  ALIGNED (rows
 // start on 16-byte boundaries): one load with no branch; columns past p are
@@ -152,26 +145,89 @@ __device__ __forceinline__ void gram_products(const float* __restrict__ S, const
     }
 }
 
-// Pairs [pair0, pair0 + npc) over the row splits of x, which are the splits
-// split0, split0 + 1, ... of the whole design (x may be a chunk of its rows);
-// work holds npc tiles per split, split-major.  Blocks are dealt to the eight
-// XCDs in turn; each XCD takes a contiguous eighth of the (split, pair) list, so
-// the pairs of a split mostly run on one XCD, whose L2 serves the rows they share.
-template <int XT, int NB, bool ALIGNED>
-__global__ __launch_bounds__(256, 2) void gram_tile_kernel(XLayout x, double* __restrict__ work, uint32_t nt,
-                                                           uint32_t pair0, uint32_t npc, uint32_t nsplit,
-                                                           uint32_t rows_per_split, uint32_t split0) {
+// Pair idx of a class (GramGeometry): tile column tj, tile row ti.
+__device__ __forceinline__ void pair_of(uint32_t cls, uint32_t idx, uint32_t nt, uint32_t& ti, uint32_t& tj) {
+    ti = idx;
+    tj = cls == kGramDiag ? idx : nt - 1;
+    if (cls == kGramLastDiag) ti = tj;
+    if (cls != kGramFull) return;
+    uint32_t r = 0;
+    while (idx >= nt - 2 - r) { idx -= nt - 2 - r; ++r; }
+    ti = r;
+    tj = r + 1 + idx;
+}
+
+// Item w of a launch's (split, pair) list.  The classes have different numbers of
+// splits; their items are merged by where in the rows they start, (i + 1/2) / n of
+// a class's n items, ties to the lower class.  Sixteen lanes try the items of a
+// class around the expected one, each counting the items ahead of its own; the
+// lane whose count is w knows its class and item (each w has one: merging is a
+// bijection, and the expected item is at most three off).
+__device__ __forceinline__ void gram_item(const GramGeometry& g, const GramPart& part, uint32_t w, uint32_t& cls,
+                                          uint32_t& item) {
+    const uint32_t lane = threadIdx.x & 63u, c = lane >> 4;
+    uint64_t n[kGramClasses], sum = 0, own = 0;
+#pragma unroll
+    for (int k = 0; k < kGramClasses; ++k) {
+        n[k] = (uint64_t)part.count[k] * g.nsplit[k];
+        sum += n[k];
+        if (c == (uint32_t)k) own = n[k];
+    }
+    const int64_t j = (int64_t)((2ull * w + 1ull) * own / (2ull * sum)) + (int64_t)(lane & 15u) - 8;
+    uint64_t rank = (uint64_t)j;
+    const bool in = j >= 0 && j < (int64_t)own;
+    if (in) {
+#pragma unroll
+        for (int k = 0; k < kGramClasses; ++k)
+            if ((uint32_t)k != c && n[k] > 0) {
+                const uint64_t at = (2ull * (uint64_t)j + 1ull) * n[k];
+                rank += (((uint32_t)k < c ? at : at - 1ull) / own + 1ull) / 2ull;
+            }
+    }
+    const int who = __builtin_ctzll(__ballot(in && rank == w));
+    cls = (uint32_t)who >> 4;
+    item = (uint32_t)__builtin_amdgcn_readlane((int)j, who);
+}
+
+// The pairs of part over the rows of x.  CHUNK: these are rows row0, row0 + 1, ...
+// of the N rows that the splits cut up, and a split that began before row0 goes on
+// from its partial tile (else row0 = 0, N = x.N).  work holds, class after class, a tile per (split, pair of the
+// part), split-major.  Blocks are dealt to the eight XCDs in turn; each XCD takes
+// a contiguous eighth of the list, so the pairs of one range of rows mostly run
+// on one XCD, whose L2 serves the rows they share.
+template <int XT, int NB, bool ALIGNED, bool CHUNK>
+__global__ __launch_bounds__(256, 2) void gram_tile_kernel(XLayout x, double* __restrict__ work, GramGeometry g,
+                                                           GramPart part, uint32_t items, uint64_t row0, uint64_t N) {
     constexpr int T = 32 * NB, LD = gram_stride<NB>();
     constexpr int VN = XT == 0 ? 4 : 8, TPR = T / VN, RPP = 256 / TPR, PASSES = kGramK / RPP;
     static_assert(RPP * PASSES == kGramK, "whole passes per stage");
     __shared__ __align__(16) float lds[2][2][kGramK * LD];
-    const uint32_t per_xcd = (npc * nsplit + 7u) / 8u, w = (blockIdx.x & 7u) * per_xcd + (blockIdx.x >> 3);
-    if (w >= npc * nsplit) return;
-    const uint32_t split = w / npc, pc = w % npc;
-    uint32_t ti, tj;
-    pair_of(pair0 + pc, nt, ti, tj);
-    const size_t r_begin = (size_t)split * rows_per_split;
-    const size_t r_end = min((size_t)x.N, r_begin + rows_per_split);
+    const uint32_t per_xcd = (items + 7u) / 8u, w = (blockIdx.x & 7u) * per_xcd + (blockIdx.x >> 3);
+    if (w >= items) return;
+    uint32_t cls, item, ti, tj, count = 1, first = 0, rows_per_split = 0;
+    gram_item(g, part, w, cls, item);
+    size_t tile = item;
+#pragma unroll
+    for (uint32_t k = 0; k < kGramClasses; ++k) {
+        if (k < cls) tile += (size_t)part.count[k] * g.nsplit[k];
+        if (k == cls) {
+            count = part.count[k];
+            first = part.first[k];
+            rows_per_split = g.rows[k];
+        }
+    }
+    const uint32_t nt = g.nt, split = item / count;
+    pair_of(cls, first + item % count, nt, ti, tj);
+    size_t r_begin = (size_t)split * rows_per_split;
+    size_t r_end = min((size_t)(CHUNK ? N : x.N), r_begin + rows_per_split);
+    bool resume = false;
+    if constexpr (CHUNK) {
+        if (r_begin >= row0 + x.N || r_end <= row0) return;
+        resume = r_begin < row0;
+        r_begin = resume ? 0 : r_begin - row0;
+        r_end = min((size_t)x.N, r_end - row0);
+    }
+    double* out = work + tile * (T * T);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wr = wave >> 1, wc = wave & 1;
     const bool diag = ti == tj;
@@ -183,6 +239,22 @@ __global__ __launch_bounds__(256, 2) void gram_tile_kernel(XLayout x, double* __
     for (int i = 0; i < NB; ++i)
 #pragma unroll
         for (int j = 0; j < NB; ++j) acc[i][j] = GAcc{0.0, 0.0, 0.0, 0.0};
+    const int lane = threadIdx.x & 63, kr = lane >> 4, cc = lane & 15;
+    // block (2 i + wr, 2 j + wc) is inside the matrix and not below its diagonal
+    auto held = [&](int i, int j) { return 2 * i + wr < nI && 2 * j + wc < nJ && (!diag || 2 * i + wr <= 2 * j + wc); };
+    if (CHUNK && resume) {
+        uint32_t at = kr * T + cc;
+        asm volatile("" : "+v"(at));  // the addresses are not kept for the stores at the end
+#pragma unroll
+        for (int i = 0; i < NB; ++i)
+#pragma unroll
+            for (int j = 0; j < NB; ++j)
+                if (held(i, j)) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        acc[i][j][r] = out[(16 * (2 * i + wr) + 4 * r) * T + 16 * (2 * j + wc) + at];
+                }
+    }
     // staging: thread t takes VN columns of stage rows t / TPR + RPP s
     const uint32_t c = threadIdx.x % TPR * VN, rb = threadIdx.x / TPR;
     uint4 va[PASSES], vb[PASSES];
@@ -214,10 +286,8 @@ __global__ __launch_bounds__(256, 2) void gram_tile_kernel(XLayout x, double* __
             if (!diag) widen(vb[s], in, &lds[buf][1][row * LD + c]);
         }
     };
-    if (r_begin < r_end) {
-        fetch(r_begin);
-        put(0, r_begin);
-    }
+    fetch(r_begin);
+    put(0, r_begin);
     __syncthreads();
     auto rows = [&](auto jl, auto dg) {
         int buf = 0;
@@ -239,47 +309,61 @@ __global__ __launch_bounds__(256, 2) void gram_tile_kernel(XLayout x, double* __
     };
     if (diag) columns(std::true_type{});
     else columns(std::false_type{});
-    const int lane = threadIdx.x & 63, kr = lane >> 4, cc = lane & 15;
-    double* out = work + ((size_t)(split0 + split) * npc + pc) * (T * T);
 #pragma unroll
     for (int i = 0; i < NB; ++i)
 #pragma unroll
         for (int j = 0; j < NB; ++j)
-            if (2 * i + wr < nI && 2 * j + wc < nJ && (!diag || 2 * i + wr <= 2 * j + wc)) {
+            if (held(i, j)) {
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
                     out[(16 * (2 * i + wr) + kr + 4 * r) * T + 16 * (2 * j + wc) + cc] = acc[i][j][r];
             }
 }
 
-// G from the partial tiles of pairs [pair0, pair0 + npc), mirrored, and unscaled
+// G from the partial tiles of part, mirrored, and unscaled
 // by 2^(e_i + e_j) (exact) if e.  A block takes 64 entries; wave w sums the
 // splits of the w-th quarter in order, eight loads in flight, and the four sums
 // are added in wave order: a fixed order, and four times the loads in flight of
 // one thread per entry (N = 1e5, p = 100, 342 splits: 80 -> 8 us).
-__global__ __launch_bounds__(256) void gram_reduce_kernel(const double* __restrict__ work, uint32_t nsplit, uint32_t npc,
-                                                          uint32_t pair0, uint32_t nt, uint32_t T, uint32_t p,
-                                                          const int32_t* __restrict__ e, double* __restrict__ G) {
-    __shared__ double part[4][64];
-    const uint32_t tt = T * T, lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+__global__ __launch_bounds__(256) void gram_reduce_kernel(const double* __restrict__ work, GramGeometry g, GramPart part,
+                                                          uint32_t p, const int32_t* __restrict__ e,
+                                                          double* __restrict__ G) {
+    __shared__ double part_sum[4][64];
+    const uint32_t T = g.tile, tt = T * T, lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
     const size_t idx = blockIdx.x * (size_t)64 + lane;  // 64 divides T * T: a block's entries share a pair
-    const uint32_t pc = (uint32_t)(idx / tt), local = (uint32_t)(idx % tt);
-    uint32_t ti, tj;
-    pair_of(pair0 + pc, nt, ti, tj);
+    uint32_t pc = (uint32_t)(blockIdx.x * (size_t)64 / tt), cls = 0, count = 0, first = 0, nsplit = 1, ti, tj;
+    const uint32_t local = (uint32_t)(idx % tt);
+    size_t base = 0;
+    bool found = false;
+#pragma unroll
+    for (uint32_t k = 0; k < kGramClasses; ++k) {
+        if (found) continue;
+        if (pc < part.count[k]) {
+            found = true;
+            cls = k;
+            count = part.count[k];
+            first = part.first[k];
+            nsplit = g.nsplit[k];
+        } else {
+            pc -= part.count[k];
+            base += (size_t)part.count[k] * g.nsplit[k];
+        }
+    }
+    pair_of(cls, first + pc, g.nt, ti, tj);
     const uint32_t i = ti * T + local / T, j = tj * T + local % T;
     const bool live = i < p && j < p && !(ti == tj && j < i);
     const uint32_t per = (nsplit + 3u) / 4u, s0 = min(wave * per, nsplit), s1 = min(s0 + per, nsplit);
-    const double* src = work + (size_t)pc * tt + local;
-    const size_t step = (size_t)npc * tt;
+    const double* src = work + (base + pc) * tt + local;
+    const size_t step = (size_t)count * tt;
     double s = 0.0;
     if (live) {
 #pragma unroll 8
         for (uint32_t sp = s0; sp < s1; ++sp) s += src[sp * step];
     }
-    part[wave][lane] = s;
+    part_sum[wave][lane] = s;
     __syncthreads();
     if (wave != 0 || !live) return;
-    s = ((part[0][lane] + part[1][lane]) + part[2][lane]) + part[3][lane];
+    s = ((part_sum[0][lane] + part_sum[1][lane]) + part_sum[2][lane]) + part_sum[3][lane];
     if (e) s = ldexp(s, e[i] + e[j]);
     G[(size_t)i * p + j] = s;
     G[(size_t)j * p + i] = s;
@@ -308,96 +392,139 @@ __global__ void pad_gram_kernel(const double* __restrict__ G, uint32_t p, uint32
 
 }  // namespace
 
+namespace {
+bool gram_aligned(const XLayout& x) {
+    return (size_t)x.ld * (x.xtype == 0 ? 4 : 2) % 16 == 0 && (uintptr_t)x.X % 16 == 0;
+}
+}  // namespace
+
 // Tile width: 64 up to p = 128, where 128-wide tiles would be mostly padding.
 // Row splits: at least four 64-wide-tile blocks per compute unit in all.  With
-// 128-wide tiles more splits are taken while they shorten the model's time: the
-// blocks of the busiest unit one after another (its FP64 matrix cores do 64
-// multiply-adds a cycle at 2.4 GHz; a block alone on its unit keeps them a little
-// less busy) plus, per block, its 128 KB of partials written and read at 4 TB/s
-// and allocated and freed (about 1.6 us per MB).
-GramGeometry gram_geometry(const XLayout& x, int num_cus, uint64_t max_rows_per_split) {
-    GramGeometry g;
+// 128-wide tiles a class takes splits in proportion to the products of a row of
+// its tiles (16 per wave for a whole tile, 10 on the diagonal, fewer in a narrow
+// last tile column) plus a stage's loads and barrier, which cost about as much as
+// 2 products (24 where rows of bfloat16 are off 16-byte boundaries and loaded one
+// by one, 4 float32): the blocks on the device at one time then end together.
+// Their number is the one with the shortest modelled time: the blocks of the
+// busiest unit one after another (its FP64 matrix cores do 64 multiply-adds a
+// cycle at 2.4 GHz; a block alone on its unit keeps them a little less busy) plus,
+// per block, its 128 KB of partials written and read at 4 TB/s and allocated and
+// freed (about 1.6 us per MB).  With as many splits for every pair, blocks of the
+// diagonal and of a narrow last column left their units early: N = 1e6, p = 1000
+// float32 18.3 ms, N = 3e5, p = 777 bfloat16 (9 columns in the last tile) 4.35 ms,
+// N = 1e5, p = 129 float32 0.46 ms; now 16.9, 3.4 and 0.13 ms.
+GramGeometry gram_geometry(const XLayout& x, int num_cus) {
+    GramGeometry g{};
     const uint64_t nt64 = (x.p + 63) / 64, np64 = nt64 * (nt64 + 1) / 2;
     const uint64_t max_split = ((uint64_t)x.N + 63) / 64;
     const uint64_t lo = std::max<uint64_t>(1, std::min(max_split, ((uint64_t)num_cus * 4 + np64 - 1) / np64));
     g.tile = x.p <= 128u ? 64u : 128u;
     g.nt = (x.p + g.tile - 1) / g.tile;
-    g.npairs = g.nt * (g.nt + 1) / 2;
-    uint64_t ns = lo;
-    if (g.tile == 128u) {
-        // one pair's partials over every split fit the fixed workspace
-        const uint64_t hi = std::min({max_split, ((uint64_t)num_cus * 16 + g.npairs - 1) / g.npairs,
-                                      (uint64_t)kGramScratchDoubles / (128 * 128)});
-        double best = 1e300;
-        for (uint64_t n = lo; n <= std::max(lo, hi); ++n) {
-            const double rows = (double)((((uint64_t)x.N + n - 1) / n + 63) / 64 * 64);
-            const uint64_t blocks = n * g.npairs, q = (blocks + num_cus - 1) / num_cus;
-            const double us = (double)q * rows * (128.0 * 128 / (64 * 2400.0)) * (q == 1 ? 1.15 : 1.0) +
-                              (double)blocks * 0.265;
-            if (us < best) {
-                best = us;
-                ns = n;
-            }
+    const uint32_t inner = g.nt - 1;
+    g.npairs[kGramFull] = inner > 0 ? inner * (inner - 1) / 2 : 0u;
+    g.npairs[kGramDiag] = g.npairs[kGramLast] = inner;
+    g.npairs[kGramLastDiag] = 1;
+    const uint32_t jl = (std::min(8u, (x.p - inner * g.tile + 15) / 16) + 1) / 2;
+    const uint32_t stage = gram_aligned(x) ? 2 : x.xtype == 0 ? 4 : 24;
+    const uint32_t cost[kGramClasses] = {16 + stage, 10 + stage, 4 * jl + stage, jl * (jl + 1) / 2 + stage};
+    auto cut = [&](uint64_t n, GramGeometry* h) {  // n splits of a whole pair
+        for (int c = 0; c < kGramClasses; ++c) {
+            const uint64_t nc = g.tile == 64u ? n : (n * cost[c] + cost[0] - 1) / cost[0];
+            const uint64_t rows = (((uint64_t)x.N + nc - 1) / nc + 63) / 64 * 64;
+            h->rows[c] = (uint32_t)rows;
+            h->nsplit[c] = (uint32_t)(((uint64_t)x.N + rows - 1) / rows);
+        }
+    };
+    cut(lo, &g);
+    if (g.tile == 64u) return g;
+    // one pair's partials over every split fit the fixed workspace
+    const uint64_t np = (uint64_t)g.nt * (g.nt + 1) / 2;
+    const uint64_t hi = std::min({max_split, ((uint64_t)num_cus * 16 + np - 1) / np,
+                                  (uint64_t)kGramScratchDoubles / (128 * 128)});
+    GramGeometry best = g;
+    double best_us = 1e300;
+    for (uint64_t n = lo; n <= std::max(lo, hi); n += std::max<uint64_t>(1, n / 64)) {
+        cut(n, &g);
+        double rows = 0.0;
+        uint64_t blocks = 0;
+        for (int c = 0; c < kGramClasses; ++c) {
+            if (g.npairs[c] > 0) rows = std::max(rows, g.rows[c] * cost[c] / 16.0);
+            blocks += (uint64_t)g.npairs[c] * g.nsplit[c];
+        }
+        const uint64_t q = (blocks + num_cus - 1) / num_cus;
+        const double us = ((double)q + (q & 1 ? 0.15 : 0.0)) * rows * (128.0 * 128 / (64 * 2400.0)) + (double)blocks * 0.265;
+        if (us < best_us) {
+            best_us = us;
+            best = g;
         }
     }
-    uint64_t rps = ((uint64_t)x.N + ns - 1) / ns;
-    rps = (rps + 63) / 64 * 64;
-    if (max_rows_per_split >= 64 && rps > max_rows_per_split) rps = max_rows_per_split / 64 * 64;
-    g.nsplit = (uint32_t)((x.N + rps - 1) / rps);
-    g.rows_per_split = (uint32_t)rps;
-    return g;
+    return best;
 }
 
-size_t gram_work_doubles(const GramGeometry& g) { return (size_t)g.nsplit * g.npairs * g.tile * g.tile; }
-size_t gram_work_doubles(const XLayout& x, int num_cus) { return gram_work_doubles(gram_geometry(x, num_cus)); }
+size_t gram_work_doubles(const GramGeometry& g) {
+    size_t tiles = 0;
+    for (int c = 0; c < kGramClasses; ++c) tiles += (size_t)g.npairs[c] * g.nsplit[c];
+    return tiles * g.tile * g.tile;
+}
 
 namespace {
 
 template <int XT, int NB>
-void gram_tiles(const XLayout& x, double* work, const GramGeometry& g, uint32_t pair0, uint32_t npc, uint32_t ns,
-                uint32_t split0, hipStream_t st) {
-    const size_t row_bytes = (size_t)x.ld * (XT == 0 ? 4 : 2);
-    const bool aligned = row_bytes % 16 == 0 && (uintptr_t)x.X % 16 == 0;
-    const dim3 grid((npc * ns + 7u) / 8u * 8u);
-    if (aligned)
-        hipLaunchKernelGGL((gram_tile_kernel<XT, NB, true>), grid, dim3(256), 0, st, x, work, g.nt, pair0, npc, ns,
-                           g.rows_per_split, split0);
-    else
-        hipLaunchKernelGGL((gram_tile_kernel<XT, NB, false>), grid, dim3(256), 0, st, x, work, g.nt, pair0, npc, ns,
-                           g.rows_per_split, split0);
+void gram_tiles(const XLayout& x, double* work, const GramGeometry& g, const GramPart& part, uint64_t row0, uint64_t N,
+                hipStream_t st) {
+    const bool aligned = gram_aligned(x);
+    uint32_t items = 0;
+    for (int c = 0; c < kGramClasses; ++c) items += part.count[c] * g.nsplit[c];
+    const dim3 grid((items + 7u) / 8u * 8u);
+    auto f = x.N < N ? &gram_tile_kernel<XT, NB, true, true> : aligned ? &gram_tile_kernel<XT, NB, true, false>
+                                                                       : &gram_tile_kernel<XT, NB, false, false>;
+    hipLaunchKernelGGL(f, grid, dim3(256), 0, st, x, work, g, part, items, row0, N);
 }
 
-// The partial tiles of pairs [pair0, pair0 + npc) over ns row splits of x.
-void gram_tiles_launch(const XLayout& x, double* work, const GramGeometry& g, uint32_t pair0, uint32_t npc, uint32_t ns,
-                       uint32_t split0, hipStream_t st) {
-    if (x.xtype == 0 && g.tile == 64) gram_tiles<0, 2>(x, work, g, pair0, npc, ns, split0, st);
-    else if (x.xtype == 0) gram_tiles<0, 4>(x, work, g, pair0, npc, ns, split0, st);
-    else if (g.tile == 64) gram_tiles<1, 2>(x, work, g, pair0, npc, ns, split0, st);
-    else gram_tiles<1, 4>(x, work, g, pair0, npc, ns, split0, st);
+// The partial tiles of part over x, rows row0 ... of N.
+void gram_tiles_launch(const XLayout& x, double* work, const GramGeometry& g, const GramPart& part, uint64_t row0,
+                       uint64_t N, hipStream_t st) {
+    if (x.xtype == 0 && g.tile == 64) gram_tiles<0, 2>(x, work, g, part, row0, N, st);
+    else if (x.xtype == 0) gram_tiles<0, 4>(x, work, g, part, row0, N, st);
+    else if (g.tile == 64) gram_tiles<1, 2>(x, work, g, part, row0, N, st);
+    else gram_tiles<1, 4>(x, work, g, part, row0, N, st);
 }
 
-hipError_t gram_sum_launch(const double* work, const GramGeometry& g, uint32_t pair0, uint32_t npc, uint32_t p,
+hipError_t gram_sum_launch(const double* work, const GramGeometry& g, const GramPart& part, uint32_t p,
                            const int32_t* e, double* G, hipStream_t st) {
-    const size_t n = (size_t)npc * g.tile * g.tile;
-    hipLaunchKernelGGL(gram_reduce_kernel, dim3((unsigned)(n / 64)), dim3(256), 0, st, work, g.nsplit, npc,
-                       pair0, g.nt, g.tile, p, e, G);
+    size_t pairs = 0;
+    for (int c = 0; c < kGramClasses; ++c) pairs += part.count[c];
+    hipLaunchKernelGGL(gram_reduce_kernel, dim3((unsigned)(pairs * g.tile * g.tile / 64)), dim3(256), 0, st, work, g,
+                       part, p, e, G);
     return hipGetLastError();
+}
+
+GramPart whole(const GramGeometry& g) {
+    GramPart part{};
+    for (int c = 0; c < kGramClasses; ++c) part.count[c] = g.npairs[c];
+    return part;
 }
 
 }  // namespace
 
-hipError_t gram_launch_chunked(const XLayout& x, const int32_t* e, double* G, double* work,
-                               size_t work_doubles, int num_cus, hipStream_t st) {
-    const GramGeometry g = gram_geometry(x, num_cus);
-    const size_t per_pair = (size_t)g.nsplit * g.tile * g.tile;
-    const size_t chunk = std::min<size_t>(g.npairs, work_doubles / per_pair);
-    if (chunk < 1) return hipErrorInvalidValue;
-    for (uint32_t pair0 = 0; pair0 < g.npairs; pair0 += (uint32_t)chunk) {
-        const uint32_t npc = (uint32_t)std::min<size_t>(chunk, g.npairs - pair0);
-        gram_tiles_launch(x, work, g, pair0, npc, g.nsplit, 0u, st);
-        if (hipError_t err = gram_sum_launch(work, g, pair0, npc, x.p, e, G, st)) return err;
+hipError_t gram_launch(const XLayout& x, const GramGeometry& g, const int32_t* e, double* G, double* work,
+                       size_t work_doubles, hipStream_t st) {
+    GramPart part{};
+    while (true) {
+        size_t room = work_doubles / ((size_t)g.tile * g.tile), taken = 0;
+        bool left = false;
+        for (int c = 0; c < kGramClasses; ++c) {
+            part.first[c] += part.count[c];
+            part.count[c] = (uint32_t)std::min<size_t>(g.npairs[c] - part.first[c], room / g.nsplit[c]);
+            room -= (size_t)part.count[c] * g.nsplit[c];
+            taken += part.count[c];
+            left |= part.first[c] < g.npairs[c];
+        }
+        if (!left) return hipSuccess;
+        if (taken == 0) return hipErrorInvalidValue;
+        gram_tiles_launch(x, work, g, part, 0, x.N, st);
+        if (hipError_t err = gram_sum_launch(work, g, part, x.p, e, G, st)) return err;
     }
-    return hipSuccess;
 }
 
 // A fixed device workspace for callers that cannot allocate: gram_scratch()
@@ -429,28 +556,24 @@ hipError_t gram_scratch(double** ptr) {
     return hipSuccess;
 }
 
-size_t gram_pair_doubles(const XLayout& x, int num_cus) {
-    const GramGeometry g = gram_geometry(x, num_cus);
-    return (size_t)g.nsplit * g.tile * g.tile;
+size_t gram_pair_doubles(const GramGeometry& g) {
+    uint32_t ns = 0;
+    for (int c = 0; c < kGramClasses; ++c)
+        if (g.npairs[c] > 0) ns = std::max(ns, g.nsplit[c]);
+    return (size_t)ns * g.tile * g.tile;
 }
 
-hipError_t gram_launch(const XLayout& x, const int32_t* e, double* G, double* work, int num_cus,
-                       hipStream_t st) {
-    return gram_launch_chunked(x, e, G, work, gram_work_doubles(x, num_cus), num_cus, st);
-}
-
-hipError_t gram_chunk_launch(const XLayout& chunk, const GramGeometry& g, uint32_t split0, double* work,
+hipError_t gram_chunk_launch(const XLayout& chunk, const GramGeometry& g, uint64_t row0, uint64_t N, double* work,
                              hipStream_t st) {
-    const uint32_t ns = (chunk.N + g.rows_per_split - 1) / g.rows_per_split;
-    if (ns == 0) return hipSuccess;
-    if (split0 + ns > g.nsplit) return hipErrorInvalidValue;
-    gram_tiles_launch(chunk, work, g, 0u, g.npairs, ns, split0, st);
+    if (chunk.N == 0) return hipSuccess;
+    if (row0 % 64 != 0 || row0 + chunk.N > N || !gram_aligned(chunk)) return hipErrorInvalidValue;
+    gram_tiles_launch(chunk, work, g, whole(g), row0, N, st);
     return hipGetLastError();
 }
 
 hipError_t gram_reduce_launch(const double* work, const GramGeometry& g, uint32_t p, const int32_t* e, double* G,
                               hipStream_t st) {
-    return gram_sum_launch(work, g, 0u, g.npairs, p, e, G, st);
+    return gram_sum_launch(work, g, whole(g), p, e, G, st);
 }
 
 hipError_t pad_gram_launch(const double* G, uint32_t p, uint32_t P, double* Gp, hipStream_t st) {

@@ -340,39 +340,39 @@ hipError_t pack_launch(int xtype, int chunks, const SweepArgs* const* table, con
 hipError_t mc_launch(const McArgs* mc, uint32_t ld, uint32_t gz, uint32_t nchains, hipStream_t st);
 
 // G = X^T X (p x p float64, leading dimension p) of the stored X, unscaled
-// with the column exponents e (null: none).  The rows are cut into nsplit
-// splits of rows_per_split rows and the upper triangle of G into npairs
-// tile x tile tiles; every (split, tile) partial is summed in split order.
+// with the column exponents e (null: none).  The upper triangle of G is cut into
+// tile x tile tiles, "pairs" of tile columns, of four classes by how much of a
+// tile is computed (one column counts as the last): off the diagonal, on it, in
+// the last tile column, and the last diagonal one.  The rows are cut into
+// nsplit[class] splits of rows[class] rows (a multiple of 64); every pair's
+// partials are summed in split order.
+enum : uint32_t { kGramFull, kGramDiag, kGramLast, kGramLastDiag, kGramClasses };
 struct GramGeometry {
-    uint32_t tile, nt, npairs, nsplit, rows_per_split;
+    uint32_t tile, nt, npairs[kGramClasses], nsplit[kGramClasses], rows[kGramClasses];
 };
-// max_rows_per_split > 0 caps the rows of a split (more splits), so that a
-// design streamed in chunks of whole splits can form its partials chunk by chunk.
-GramGeometry gram_geometry(const XLayout& x, int num_cus, uint64_t max_rows_per_split = 0);
-// The partial tiles of every tile pair over the splits of one chunk of rows
-// (chunk.N rows, the splits split0, split0 + 1, ... of geometry g, chunk.N a
-// multiple of g.rows_per_split except for the last chunk) into work, which
-// holds g.nsplit x g.npairs tiles; then G from all of them, summed in split
-// order exactly as gram_launch sums them (the same G, bit for bit, when g is
-// the same geometry).
-hipError_t gram_chunk_launch(const XLayout& chunk, const GramGeometry& g, uint32_t split0, double* work,
+// Pairs [first, first + count) of each class.
+struct GramPart {
+    uint32_t first[kGramClasses], count[kGramClasses];
+};
+GramGeometry gram_geometry(const XLayout& x, int num_cus);
+// The partial tiles of every pair over one chunk of rows (chunk.N rows from row0,
+// a multiple of 64, of the N rows of geometry g; rows start on 16-byte boundaries;
+// chunks follow each other on the stream) into work, which holds gram_work_doubles(g); then G from all of them,
+// the same G, bit for bit, as gram_launch's.
+hipError_t gram_chunk_launch(const XLayout& chunk, const GramGeometry& g, uint64_t row0, uint64_t N, double* work,
                              hipStream_t st);
 hipError_t gram_reduce_launch(const double* work, const GramGeometry& g, uint32_t p, const int32_t* e, double* G,
                               hipStream_t st);
 // Doubles of workspace that hold every partial tile at once.
 size_t gram_work_doubles(const GramGeometry& g);
-size_t gram_work_doubles(const XLayout& x, int num_cus);
-// work must hold gram_work_doubles(x) doubles.
-hipError_t gram_launch(const XLayout& x, const int32_t* e, double* G, double* work, int num_cus,
-                       hipStream_t st);
-// The same G (bit for bit) with a workspace of work_doubles doubles: the
-// tiles are processed in chunks whose partials fit it (at least one tile's
-// nsplit partials, else hipErrorInvalidValue).
-hipError_t gram_launch_chunked(const XLayout& x, const int32_t* e, double* G, double* work,
-                               size_t work_doubles, int num_cus, hipStream_t st);
-// Doubles of workspace one tile pair needs (its partials over every
-// row split); gram_launch_chunked needs at least this much.
-size_t gram_pair_doubles(const XLayout& x, int num_cus);
+// G with a workspace of work_doubles doubles: the pairs are processed in parts
+// whose partials fit it (the same G, bit for bit, whatever its size; at least one
+// pair's partials over its splits, else hipErrorInvalidValue).
+hipError_t gram_launch(const XLayout& x, const GramGeometry& g, const int32_t* e, double* G, double* work,
+                       size_t work_doubles, hipStream_t st);
+// Doubles of workspace one tile pair needs (its partials over every row
+// split); gram_launch needs at least this much.
+size_t gram_pair_doubles(const GramGeometry& g);
 // The library's fixed Gram workspace (kGramScratchDoubles doubles, 32 MiB,
 // one per device, held until the process ends): its device address on the
 // current device.  Calls that use it on one device at the same time race.

@@ -16,7 +16,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("xt", ["f32", "bf16"])
 @pytest.mark.parametrize("N,p,ld", [(1, 1, 1), (33, 15, 16), (63, 16, 16), (65, 17, 19), (1000, 64, 64), (517, 65, 72),
                                     (2049, 128, 128), (2048, 129, 136), (999, 145, 145), (131, 255, 256),
-                                    (3001, 257, 259), (4100, 400, 400)])
+                                    (3001, 257, 259), (4100, 400, 400), (20011, 300, 300), (9001, 352, 352),
+                                    (9001, 383, 383)])
 def test_gram_tile_edges(xt, N, p, ld):
     torch, hsp = need_gpu()
     X = np.random.default_rng(N + p).standard_normal((N, p)).astype(np.float32)
@@ -37,3 +38,19 @@ def test_gram_tile_edges(xt, N, p, ld):
     s = np.sqrt(np.outer(np.diag(ref), np.diag(ref)))
     assert np.all(np.abs(got - ref) <= 2 * N * 2.0 ** -52 * s)
     assert np.array_equal(got, got.T)
+
+
+@pytest.mark.parametrize("xt,N,p,rows", [("f32", 2049, 150, 64), ("bf16", 3000, 140, 192), ("f32", 3000, 60, 128)])
+def test_gram_of_row_chunks(xt, N, p, rows):
+    """Row splits that end inside a chunk of streamed rows, and go on from one
+    chunk to the next: the resident design's G, bit for bit."""
+    torch, hsp = need_gpu()
+    rng = np.random.default_rng(p)
+    X, y = rng.standard_normal((N, p)).astype(np.float32), (rng.random(N) < 0.5).astype(np.uint8)
+    G = []
+    for stream in (False, True):
+        s = hsp.Sampler(X if stream else torch.from_numpy(X).cuda(), y if stream else torch.from_numpy(y).cuda(), seed=1,
+                        x_type=xt, x_stream=stream, stream_rows=rows)
+        G.append(s.gram())
+        s.close()
+    assert np.array_equal(G[0], G[1])
