@@ -85,8 +85,8 @@ typedef struct {
                                last z step for hsp_get_debug (costs N*8 bytes
                                of writes per sweep) */
     int32_t use_graph;      /* no effect on draws or speed: a chain's sweep is one kernel,
-                               launched directly; a batch of several launches replays a
-                               captured HIP graph whatever this says (default 1) */
+                               launched directly; a batch with launches side by side
+                               replays a captured HIP graph whatever this says (default 1) */
     int32_t multi_chain_z;  /* batches: 1 (default) = chains sharing a bfloat16 design
                                with rows of at most 1024 elements run one z pass for
                                up to 16 of them (X beta and X^T z as matrix-core
@@ -224,18 +224,17 @@ hsp_status hsp_destroy(hsp_state* s);
  * the last failure of hsp_create on this thread. */
 const char* hsp_last_error(const hsp_state* s);
 
-/* ---- Batches: many independent chains, one graph launch per sweep ----------
+/* ---- Batches: many independent chains, a few launches per sweep -------------
  * (A batch is its own handle, hsp_batch, created by hsp_batch_create; its
  * chains are reached as ordinary hsp_state handles through hsp_batch_chain,
  * so every state entry point applies to them.)
  * A batch runs chains of the same sweep on several designs at once (the
  * chains of one design share its library copy of X, y and G = X^T X).  One
  * hsp_batch_sweep advances every chain by the same number of sweeps; each
- * batched sweep is a single replay of a captured HIP graph holding every
- * chain's sweep kernel (or, if one launch holds them all, that launch), one
- * after another on the batch's stream (the
- * multi-chain passes described below may run on a second stream beside the
- * other chains' launches; the graph joins it before their p-side launch).
+ * batched sweep is a few launches, each holding many chains' sweeps, one after
+ * another on the batch's stream; where some may run side by side (the
+ * multi-chain passes described below beside the other chains' launches, joined
+ * before their p-side launch) they are a captured HIP graph.
  * Every dataset of a batch is resident (x_stream is ignored).  Chain i
  * (dataset-major order) uses Philox counter word 3 = opt->chain_id + i, so it
  * draws exactly what a lone sampler created with that chain id draws --
@@ -275,7 +274,7 @@ hsp_status hsp_batch_sweep(hsp_batch* b, int64_t n_iter);
 /* Wait for the batch's work and report the first chain's device failure. */
 hsp_status hsp_batch_sync(hsp_batch* b);
 /* Timing of the batched sweeps enqueued while enabled (a pair of HIP events
- * on the batch's stream around each graph replay, at most 256 pairs in use
+ * on the batch's stream around each batched sweep, at most 256 pairs in use
  * as for hsp_set_timing): mean ms per batched sweep. */
 hsp_status hsp_batch_set_timing(hsp_batch* b, int32_t enable);
 hsp_status hsp_batch_get_timing(hsp_batch* b, double* ms_per_sweep, int64_t* n_sweeps);

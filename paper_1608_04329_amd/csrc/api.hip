@@ -1415,13 +1415,47 @@ hsp_status plan_packs(hsp_batch* b) {
     return HSP_OK;
 }
 
-// Whether a batched sweep is a single launch, which needs no graph.
-bool one_launch(const hsp_batch* b) { return b->packs.size() == 1 && !b->packs[0].mc; }
+// Packs of plain sweeps run side by side if every launch that may then be resident
+// at once leaves at least half of the device to blocks that never wait.
+bool may_spread(const hsp_batch* b) {
+    size_t plain = 0;
+    int waiting = 0, cap = 0;
+    for (const Pack& pk : b->packs) {
+        if (!pk.mc) waiting += (int)pk.waiting;  // pre packs wait inside too
+        if (!pk.mc && !pk.pre) ++plain;
+        cap = cap ? std::min(cap, pk.capacity) : pk.capacity;
+    }
+    return plain > 1 && 2 * waiting <= cap;
+}
+
+// Whether a batched sweep has launches side by side.  These are captured into a
+// graph; launches that follow each other on the batch's stream go out directly,
+// which costs less between two batched sweeps than a graph launch (us per batched
+// sweep: 16 chains on a bfloat16 design, N = 2.5e5, 994 -> 985; 24 uneven float32
+// datasets in two packs 568 -> 566).
+bool forks(const hsp_batch* b) {
+    bool any_mc = false, any_pre = false, any_plain = false;
+    for (const Pack& pk : b->packs) (pk.pre ? any_pre : pk.mc ? any_mc : any_plain) = true;
+    return b->overlap && ((any_mc && (any_plain || any_pre)) || may_spread(b));
+}
+
+hipError_t launch_pack(const Pack& pk, hipStream_t st) {
+    return pack_launch(pk.xtype, pk.chunks, pk.dtab, pk.dmap, pk.blocks, st);
+}
+
+hipError_t launch_pass(const Pack& pk, hipStream_t st) {
+    return mc_launch(pk.dmc, pk.mc_ld, pk.mc_gz, (uint32_t)pk.chains.size(), st);
+}
 
 hipError_t batch_enqueue(hsp_batch* b) {
     if (b->graph) return hipGraphLaunch(b->graph, b->stream);
-    const Pack& pk = b->packs[0];
-    return pack_launch(pk.xtype, pk.chunks, pk.dtab, pk.dmap, pk.blocks, b->stream);
+    // in pack order: a pre pack comes just before its multi-chain pack
+    hipError_t e = hipSuccess;
+    for (size_t i = 0; !e && i < b->packs.size(); ++i) {
+        if (b->packs[i].mc) e = launch_pass(b->packs[i], b->stream);
+        if (!e) e = launch_pack(b->packs[i], b->stream);
+    }
+    return e;
 }
 
 // The packs (if not planned yet) and the graph of one batched sweep.
@@ -1430,82 +1464,55 @@ hsp_status batch_build(hsp_batch* b) {
         hsp_status st = plan_packs(b);
         if (st != HSP_OK) return st;
     }
-    if (b->graph || one_launch(b)) return HSP_OK;
-    bool any_mc = false, any_pre = false;
-    size_t n_plain = 0;
-    for (const Pack& pk : b->packs) {
-        if (pk.pre) any_pre = true;
-        else if (pk.mc) any_mc = true;
-        else ++n_plain;
-    }
-    const bool overlap = b->overlap && ((any_mc && (n_plain > 0 || any_pre)) || n_plain > 1);
+    if (b->graph || !forks(b)) return HSP_OK;
+    const bool any_pre = std::any_of(b->packs.begin(), b->packs.end(), [](const Pack& pk) { return pk.pre; });
     hipError_t e = hipSuccess;
-    if (overlap && !b->side) {
+    if (!b->side) {
         e = hipStreamCreateWithFlags(&b->side, hipStreamNonBlocking);
         if (!e) e = hipEventCreateWithFlags(&b->fork, hipEventDisableTiming);
         if (!e) e = hipEventCreateWithFlags(&b->join, hipEventDisableTiming);
         if (!e) e = hipEventCreateWithFlags(&b->join3, hipEventDisableTiming);
         if (e) return batch_fail(b, HSP_EHIP, std::string("batch side stream: ") + hipGetErrorString(e));
     }
-    if (overlap && any_pre && !b->side2) {
+    if (any_pre && !b->side2) {
         e = hipStreamCreateWithFlags(&b->side2, hipStreamNonBlocking);
         if (!e) e = hipEventCreateWithFlags(&b->join2, hipEventDisableTiming);
         if (e) return batch_fail(b, HSP_EHIP, std::string("batch side stream: ") + hipGetErrorString(e));
     }
     hipGraph_t g = nullptr;
     e = hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal);
-    auto launch = [&](const Pack& pk, hipStream_t st) {
-        return pack_launch(pk.xtype, pk.chunks, pk.dtab, pk.dmap, pk.blocks, st);
-    };
-    if (overlap) {
-        // The multi-chain passes, and the pre packs (whose blocks wait only
-        // on blocks of their own launch), may run beside the other packs, on
-        // streams of their own; blocks of one launch become resident as
-        // blocks of another finish.  The launches that take b from a pass
-        // follow them on the batch's stream.
-        if (!e) e = hipEventRecord(b->fork, b->stream);
-        if (!e) e = hipStreamWaitEvent(b->side, b->fork, 0);
+    // The multi-chain passes, and the pre packs (whose blocks wait only
+    // on blocks of their own launch), may run beside the other packs, on
+    // streams of their own; blocks of one launch become resident as
+    // blocks of another finish.  The launches that take b from a pass
+    // follow them on the batch's stream.
+    if (!e) e = hipEventRecord(b->fork, b->stream);
+    if (!e) e = hipStreamWaitEvent(b->side, b->fork, 0);
+    for (size_t i = 0; !e && i < b->packs.size(); ++i)
+        if (b->packs[i].mc) e = launch_pass(b->packs[i], b->side);
+    if (!e) e = hipEventRecord(b->join, b->side);
+    if (any_pre) {
+        if (!e) e = hipStreamWaitEvent(b->side2, b->fork, 0);
         for (size_t i = 0; !e && i < b->packs.size(); ++i)
-            if (b->packs[i].mc) e = mc_launch(b->packs[i].dmc, b->packs[i].mc_ld, b->packs[i].mc_gz,
-                                               (uint32_t)b->packs[i].chains.size(), b->side);
-        if (!e) e = hipEventRecord(b->join, b->side);
-        if (any_pre) {
-            if (!e) e = hipStreamWaitEvent(b->side2, b->fork, 0);
-            for (size_t i = 0; !e && i < b->packs.size(); ++i)
-                if (b->packs[i].pre) e = launch(b->packs[i], b->side2);
-            if (!e) e = hipEventRecord(b->join2, b->side2);
-        }
-        // The other packs: the one with the most X on the batch's stream, the
-        // rest after the passes on theirs, if every launch that may then be
-        // resident at once leaves at least half of the device to blocks that
-        // never wait.
-        std::vector<size_t> plain;
-        int waiting = 0, cap = 0;
-        for (size_t i = 0; i < b->packs.size(); ++i) {
-            const Pack& pk = b->packs[i];
-            if (!pk.mc) waiting += (int)pk.waiting;  // pre packs wait inside too
-            if (!pk.mc && !pk.pre) plain.push_back(i);
-            cap = cap ? std::min(cap, pk.capacity) : pk.capacity;
-        }
-        std::stable_sort(plain.begin(), plain.end(),
-                         [&](size_t x, size_t y) { return b->packs[x].bytes > b->packs[y].bytes; });
-        const bool spread = plain.size() > 1 && 2 * waiting <= cap;
-        for (size_t k = 0; !e && k < plain.size(); ++k)
-            e = launch(b->packs[plain[k]], spread && k > 0 ? b->side : b->stream);
-        if (!e && spread) e = hipEventRecord(b->join3, b->side);
-        if (!e) e = hipStreamWaitEvent(b->stream, b->join, 0);
-        if (!e && any_pre) e = hipStreamWaitEvent(b->stream, b->join2, 0);
-        for (size_t i = 0; !e && i < b->packs.size(); ++i)
-            if (b->packs[i].mc) e = launch(b->packs[i], b->stream);
-        if (!e && spread) e = hipStreamWaitEvent(b->stream, b->join3, 0);
-    } else {
-        // in pack order: a pre pack comes just before its multi-chain pack
-        for (size_t i = 0; !e && i < b->packs.size(); ++i) {
-            const Pack& pk = b->packs[i];
-            if (pk.mc) e = mc_launch(pk.dmc, pk.mc_ld, pk.mc_gz, (uint32_t)pk.chains.size(), b->stream);
-            if (!e) e = launch(pk, b->stream);
-        }
+            if (b->packs[i].pre) e = launch_pack(b->packs[i], b->side2);
+        if (!e) e = hipEventRecord(b->join2, b->side2);
     }
+    // The other packs: the one with the most X on the batch's stream, the
+    // rest after the passes on theirs, if they may.
+    std::vector<size_t> plain;
+    for (size_t i = 0; i < b->packs.size(); ++i)
+        if (!b->packs[i].mc && !b->packs[i].pre) plain.push_back(i);
+    std::stable_sort(plain.begin(), plain.end(),
+                     [&](size_t x, size_t y) { return b->packs[x].bytes > b->packs[y].bytes; });
+    const bool spread = may_spread(b);
+    for (size_t k = 0; !e && k < plain.size(); ++k)
+        e = launch_pack(b->packs[plain[k]], spread && k > 0 ? b->side : b->stream);
+    if (!e && spread) e = hipEventRecord(b->join3, b->side);
+    if (!e) e = hipStreamWaitEvent(b->stream, b->join, 0);
+    if (!e && any_pre) e = hipStreamWaitEvent(b->stream, b->join2, 0);
+    for (size_t i = 0; !e && i < b->packs.size(); ++i)
+        if (b->packs[i].mc) e = launch_pack(b->packs[i], b->stream);
+    if (!e && spread) e = hipStreamWaitEvent(b->stream, b->join3, 0);
     hipError_t e2 = hipStreamEndCapture(b->stream, &g);
     if (!e) e = e2;
     if (!e) e = hipGraphInstantiate(&b->graph, g, nullptr, nullptr, 0);
@@ -1822,7 +1829,7 @@ hsp_status hsp_batch_sweep(hsp_batch* b, int64_t n) {
         if (s->sweeps_done + (uint64_t)n >= (uint64_t(1) << 32) - 1)
             return batch_fail(b, HSP_EINVAL, "the sweep counter would exceed 2^32");
     }
-    if (!b->graph && !(one_launch(b) && !b->autotune)) {
+    if (!b->graph && (b->packs.empty() || b->autotune || forks(b))) {
         if (b->autotune) {
             b->autotune = false;  // once per batch
             hsp_status st = batch_tune(b);

@@ -6,8 +6,8 @@
 // z pass (z | beta and the partial sums of X^T z).  The group then waits for
 // the z pass, reduces X^T z and draws beta.  This is the schedule of
 // Section 5 -- (i) z in parallel with lambda, then tau; (ii) beta with nu and
-// xi -- inside a single launch, so a sweep costs one graph node and the
-// p-side work hides under the bandwidth-bound pass over X.
+// xi -- inside a single launch, and the p-side work hides under the
+// bandwidth-bound pass over X.
 //
 // The group blocks come first in the grid: they are dispatched before any
 // z-pass block and stay resident, so their barriers only ever wait on

@@ -477,7 +477,7 @@ class Sampler:
 
 
 class Batch:
-    """Many independent chains, advanced together by one graph replay per sweep.
+    """Many independent chains, advanced together by a few launches per sweep.
 
     datasets: list of (X, y) or (X, y, x_type) with X, y as for Sampler (all on
     the GPU, or all numpy); chains: chains per dataset (an int for all).
