@@ -18,7 +18,7 @@ line also carries
                 sweep rate and roofline (N p 2 + N bytes per launch)
   batch         the batched form: 64 uneven float32 datasets (one chain each)
                 plus 16 chains sharing the N = 1e6, p = 1000 bfloat16 design,
-                one graph replay per batched sweep: chain-sweeps/s batched and
+                a few launches per batched sweep: chain-sweeps/s batched and
                 the same chains swept one at a time, with the roofline of the
                 whole batched sweep (one read of every distinct design)
   rare_event    the stand-in for the data of Section 6.2 (N = 1,295,848,
