@@ -215,8 +215,8 @@ hipError_t sweep_plan(const XLayout& x, int num_cus, SweepPlan* plan, uint32_t g
 // launch fills the device at two blocks per unit, block 0 (the p-side's
 // critical chain) would share its unit with a z-pass block; that block is
 // left idle instead, and the z pass takes one block fewer: the chain then
-// has its unit to itself (N = 1e6, p = 1000 bfloat16: 0.415 -> 0.402 ms per
-// sweep; float32, bound by its z pass, unchanged).
+// has its unit to itself (N = 1e6, p = 1000 bfloat16, while that chain was its bound:
+// 0.415 -> 0.402 ms per sweep; float32, bound by its z pass, unchanged).
 void sweep_finish_args(SweepArgs* a, const SweepPlan& plan) {
     a->gp = plan.gp;
     a->gz = (a->mode & kModeZ) ? plan.gz : 0u;
