@@ -509,9 +509,12 @@ GramPart whole(const GramGeometry& g) {
 
 hipError_t gram_launch(const XLayout& x, const GramGeometry& g, const int32_t* e, double* G, double* work,
                        size_t work_doubles, hipStream_t st) {
+    // (the sum launches 4 threads per entry of a tile, and a launch takes fewer than
+    // 2^32: 65535 pairs of 128-wide tiles, which G has from p = 46209 on)
+    const size_t most = std::min<size_t>(work_doubles / ((size_t)g.tile * g.tile), 65535);
     GramPart part{};
     while (true) {
-        size_t room = work_doubles / ((size_t)g.tile * g.tile), taken = 0;
+        size_t room = most, taken = 0;
         bool left = false;
         for (int c = 0; c < kGramClasses; ++c) {
             part.first[c] += part.count[c];
