@@ -77,3 +77,16 @@ def test_diagonal_q():
         err = np.abs((x1.astype(L) - x2.astype(L)) - (b1.astype(L) - b2.astype(L)) / q)
         assert np.all(err <= U * (3 * (np.abs(b1) + np.abs(b2)) / q + (np.abs(x1) + np.abs(x2))))
     s.close()
+
+
+@pytest.mark.parametrize("p", [2, 5, 16])
+def test_infinite_precision_pins_beta_to_zero(p):
+    """tau^-2 lambda^-2 that overflows is an infinite pivot, not a failed one."""
+    torch, hsp = need_gpu()
+    rng = np.random.default_rng(p)
+    s = sampler(torch, hsp, rng.standard_normal((300, p)).astype(np.float32), rng)
+    s.set_state(beta=np.zeros(p), lam_m2=np.full(p, 1e300), nu_m1=np.ones(p), tau_m2=1e100, xi_m1=1.0, sweep=2)
+    s.step(hsp.HSP_STEP_Z | hsp.HSP_STEP_BETA)
+    s.sync()
+    assert np.all(s.state()["beta"] == 0.0)
+    s.close()
