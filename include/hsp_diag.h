@@ -31,6 +31,12 @@ hsp_status hsp_set_phase_trace(hsp_state* s, int32_t enable);
 hsp_status hsp_get_phase_trace(hsp_state* s, uint64_t* out, int64_t* group_blocks, int64_t* slots,
                                double* ticks_per_us);
 
+/* Whether hsp_draws may gather a few draws into pinned host memory (1, as
+ * created) or copies them as it does where that memory is not to be had (0).
+ * The draws are the same.  Test hook for the copies.  Errors: HSP_EINVAL
+ * (NULL). */
+hsp_status hsp_set_gather(hsp_state* s, int32_t enable);
+
 /* The factorisation schedule for p > 16 (host only, no device work): the
  * Cholesky factorisation of Q by 64 x 64 tiles (Section 5, beta step iii),
  * with the same row operations applied to an identity block, is split into

@@ -88,6 +88,29 @@ struct EventTimer {
 };
 }  // namespace
 
+// kFetchDoubles of pinned host memory that a few draws are gathered into,
+// allocated when first wanted.
+struct Gather {
+    double *host = nullptr, *dev = nullptr;
+    bool off = false;  // not to be had: draws are copied
+    bool ready() {
+        if (host || off) return !off;
+        void* d = nullptr;
+        if (hipHostMalloc(reinterpret_cast<void**>(&host), kFetchDoubles * 8, hipHostMallocDefault) != hipSuccess ||
+            hipHostGetDevicePointer(&d, host, 0) != hipSuccess) {
+            (void)hipGetLastError();
+            release();
+            off = true;
+        }
+        dev = static_cast<double*>(d);
+        return !off;
+    }
+    void release() {
+        if (host) (void)hipHostFree(host);
+        host = dev = nullptr;
+    }
+};
+
 struct hsp_state {
     int device = 0;
     int num_cus = 0;
@@ -112,7 +135,7 @@ struct hsp_state {
     float* zdbg = nullptr;
     int32_t* adbg = nullptr;
     double *ring_beta = nullptr, *ring_tau = nullptr, *ring_lam = nullptr;
-    double* fetch = nullptr;   // kFetchDoubles of pinned host memory that small hsp_draws are gathered into
+    Gather gather;
     SweepPlan plan{};
     uint64_t timeout_ticks = 0;
     uint64_t sweeps_done = 0;  // host mirror of ctrl->sweep
@@ -279,7 +302,7 @@ void free_state(hsp_state* s) {
                     s->zgrp_count, s->dargs, s->dtab, s->tasks, s->task_off, s->runs, s->ver, s->row_id};
     for (void* p : bufs)
         if (p) (void)hipFree(p);
-    if (s->fetch) (void)hipHostFree(s->fetch);
+    s->gather.release();
     if (s->streamed) {
         // s->Xbuf is null for a streamed state: X lives in Xhost and the stages
         if (s->Xhost) (void)hipHostFree(s->Xhost);
@@ -1929,19 +1952,16 @@ hsp_status hsp_draws(hsp_state* s, double* beta, double* tau_m2, double* lam_m2,
     const size_t p = s->x.p;
     const bool stored = count > 0 && first >= 0 && first <= recorded - count && first >= recorded - cap;
     const size_t per = (beta ? p : 0) + (tau_m2 ? 1 : 0) + (lam_m2 ? p : 0);
-    if (stored && (!lam_m2 || s->ring_lam) && (size_t)count * per <= kFetchDoubles - kFetchHead) {
+    if (stored && (!lam_m2 || s->ring_lam) && (size_t)count * per <= kFetchDoubles - kFetchHead &&
+        s->gather.ready()) {
         // a few draws: one kernel writes them, behind the failure flags, straight
         // into pinned host memory (launch and wait: 11-12 us up to 64 KB; each
         // copy into pageable memory takes 12-180 us)
-        if (!s->fetch)
-            HIP_TRY(hipHostMalloc(reinterpret_cast<void**>(&s->fetch), kFetchDoubles * 8, hipHostMallocDefault));
-        void* dev = nullptr;
-        HIP_TRY(hipHostGetDevicePointer(&dev, s->fetch, 0));
         HIP_TRY(fetch_draws_launch(s->ctrl, beta ? s->ring_beta : nullptr, tau_m2 ? s->ring_tau : nullptr,
                                    lam_m2 ? s->ring_lam : nullptr, (uint32_t)p, (uint32_t)(first % cap), (uint32_t)cap,
-                                   (uint32_t)count, static_cast<double*>(dev), s->stream));
+                                   (uint32_t)count, s->gather.dev, s->stream));
         HIP_TRY(hipStreamSynchronize(s->stream));
-        const double* host = s->fetch;
+        const double* host = s->gather.host;
         hsp_status st = flag_status(s, (uint32_t)host[0], (int32_t)host[1], (uint32_t)host[2]);
         if (st) return st;
         if (n_out) *n_out = recorded;
@@ -2375,6 +2395,13 @@ hsp_status hsp_read_ceiling(hsp_state* s, int32_t iters, double* ms_per_pass, do
     HIP_TRY(e);
     *ms_per_pass = ms / iters;
     if (bytes_per_pass) *bytes_per_pass = (double)bytes;
+    return HSP_OK;
+}
+
+hsp_status hsp_set_gather(hsp_state* s, int32_t enable) {
+    if (!s) return HSP_EINVAL;
+    s->gather.release();
+    s->gather.off = enable == 0;
     return HSP_OK;
 }
 

@@ -31,7 +31,7 @@ EXPORTS = ["hsp_default_options", "hsp_max_p", "hsp_gram", "hsp_gram_noalloc", "
            "hsp_batch_chain", "hsp_batch_sweep", "hsp_batch_sync", "hsp_batch_set_timing",
            "hsp_batch_get_timing", "hsp_batch_last_error", "hsp_batch_destroy", "hsp_get_plan",
            "hsp_sort_rows", "hsp_batch_get_plan", "hsp_tune_key", "hsp_tune_cache_put", "hsp_tune_cache_get",
-           "hsp_batch_set_shape"]
+           "hsp_batch_set_shape", "hsp_set_gather"]
 
 
 class hsp_options(C.Structure):
@@ -93,6 +93,7 @@ def load():
     L.hsp_set_phase_trace.argtypes = [vp, i32]; L.hsp_set_phase_trace.restype = st
     L.hsp_get_phase_trace.argtypes = [vp, vp, C.POINTER(i64), C.POINTER(i64), C.POINTER(d)]
     L.hsp_get_phase_trace.restype = st
+    L.hsp_set_gather.argtypes = [vp, i32]; L.hsp_set_gather.restype = st
     L.hsp_tile_schedule.argtypes = [i64, i64, i32, vp, i64, vp, C.POINTER(i64)]
     L.hsp_tile_schedule.restype = st
     L.hsp_read_ceiling.argtypes = [vp, i32, C.POINTER(d), C.POINTER(d)]
@@ -238,6 +239,11 @@ def hsp_philox(seed, ctr):
     out = np.zeros_like(ctr)
     _check(load().hsp_philox(seed, _hp(ctr), ctr.shape[0], _hp(out)))
     return out
+
+
+def hsp_set_gather(h, enable):
+    """Whether hsp_draws may gather a few draws into pinned host memory."""
+    _check(load().hsp_set_gather(h, int(bool(enable))), h)
 
 
 def hsp_tile_schedule(nt, gp, inverse=None):
