@@ -8,6 +8,8 @@
 #include <cstring>
 #include <algorithm>
 #include <array>
+#include <memory>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -89,8 +91,11 @@ struct EventTimer {
 }  // namespace
 
 // kFetchDoubles of pinned host memory that a few draws are gathered into,
-// allocated when first wanted.
+// allocated when first wanted (14 us, up to 110 for a process's first).  The
+// chains of a batch, which share its stream, share one: held by mu from the
+// launch until its draws are copied out.
 struct Gather {
+    std::mutex mu;
     double *host = nullptr, *dev = nullptr;
     bool off = false;  // not to be had: draws are copied
     bool ready() {
@@ -109,6 +114,7 @@ struct Gather {
         if (host) (void)hipHostFree(host);
         host = dev = nullptr;
     }
+    ~Gather() { release(); }
 };
 
 struct hsp_state {
@@ -135,7 +141,8 @@ struct hsp_state {
     float* zdbg = nullptr;
     int32_t* adbg = nullptr;
     double *ring_beta = nullptr, *ring_tau = nullptr, *ring_lam = nullptr;
-    Gather gather;
+    std::shared_ptr<Gather> gather = std::make_shared<Gather>();
+    bool copy_draws = false;   // never gather (diagnostics)
     SweepPlan plan{};
     uint64_t timeout_ticks = 0;
     uint64_t sweeps_done = 0;  // host mirror of ctrl->sweep
@@ -302,7 +309,6 @@ void free_state(hsp_state* s) {
                     s->zgrp_count, s->dargs, s->dtab, s->tasks, s->task_off, s->runs, s->ver, s->row_id};
     for (void* p : bufs)
         if (p) (void)hipFree(p);
-    s->gather.release();
     if (s->streamed) {
         // s->Xbuf is null for a streamed state: X lives in Xhost and the stages
         if (s->Xhost) (void)hipHostFree(s->Xhost);
@@ -1826,6 +1832,7 @@ hsp_status hsp_batch_create(const hsp_dataset* ds, int32_t n_ds, const int32_t* 
                 return st;
             }
             s->in_batch = true;
+            if (!b->chains.empty()) s->gather = b->chains[0]->gather;
             if (c == 0) owner = s;
             b->chains.push_back(s);
         }
@@ -1952,24 +1959,26 @@ hsp_status hsp_draws(hsp_state* s, double* beta, double* tau_m2, double* lam_m2,
     const size_t p = s->x.p;
     const bool stored = count > 0 && first >= 0 && first <= recorded - count && first >= recorded - cap;
     const size_t per = (beta ? p : 0) + (tau_m2 ? 1 : 0) + (lam_m2 ? p : 0);
-    if (stored && (!lam_m2 || s->ring_lam) && (size_t)count * per <= kFetchDoubles - kFetchHead &&
-        s->gather.ready()) {
+    if (stored && (!lam_m2 || s->ring_lam) && (size_t)count * per <= kFetchDoubles - kFetchHead && !s->copy_draws) {
         // a few draws: one kernel writes them, behind the failure flags, straight
         // into pinned host memory (launch and wait: 11-12 us up to 64 KB; each
         // copy into pageable memory takes 12-180 us)
-        HIP_TRY(fetch_draws_launch(s->ctrl, beta ? s->ring_beta : nullptr, tau_m2 ? s->ring_tau : nullptr,
-                                   lam_m2 ? s->ring_lam : nullptr, (uint32_t)p, (uint32_t)(first % cap), (uint32_t)cap,
-                                   (uint32_t)count, s->gather.dev, s->stream));
-        HIP_TRY(hipStreamSynchronize(s->stream));
-        const double* host = s->gather.host;
-        hsp_status st = flag_status(s, (uint32_t)host[0], (int32_t)host[1], (uint32_t)host[2]);
-        if (st) return st;
-        if (n_out) *n_out = recorded;
-        const double* src = host + kFetchHead;
-        if (beta) std::memcpy(beta, src, count * p * 8), src += count * p;
-        if (tau_m2) std::memcpy(tau_m2, src, count * 8), src += count;
-        if (lam_m2) std::memcpy(lam_m2, src, count * p * 8);
-        return HSP_OK;
+        std::lock_guard<std::mutex> lock(s->gather->mu);
+        if (s->gather->ready()) {
+            HIP_TRY(fetch_draws_launch(s->ctrl, beta ? s->ring_beta : nullptr, tau_m2 ? s->ring_tau : nullptr,
+                                       lam_m2 ? s->ring_lam : nullptr, (uint32_t)p, (uint32_t)(first % cap), (uint32_t)cap,
+                                       (uint32_t)count, s->gather->dev, s->stream));
+            HIP_TRY(hipStreamSynchronize(s->stream));
+            const double* host = s->gather->host;
+            hsp_status st = flag_status(s, (uint32_t)host[0], (int32_t)host[1], (uint32_t)host[2]);
+            if (st) return st;
+            if (n_out) *n_out = recorded;
+            const double* src = host + kFetchHead;
+            if (beta) std::memcpy(beta, src, count * p * 8), src += count * p;
+            if (tau_m2) std::memcpy(tau_m2, src, count * 8), src += count;
+            if (lam_m2) std::memcpy(lam_m2, src, count * p * 8);
+            return HSP_OK;
+        }
     }
     hsp_status st = sync_state(s);
     if (st) return st;
@@ -2400,8 +2409,7 @@ hsp_status hsp_read_ceiling(hsp_state* s, int32_t iters, double* ms_per_pass, do
 
 hsp_status hsp_set_gather(hsp_state* s, int32_t enable) {
     if (!s) return HSP_EINVAL;
-    s->gather.release();
-    s->gather.off = enable == 0;
+    s->copy_draws = enable == 0;
     return HSP_OK;
 }
 
