@@ -1012,16 +1012,15 @@ struct Pack {
     // chains sharing one bfloat16 design: a multi-chain z pass (its own
     // launch, mc_gz blocks) precedes the launch of their p-side groups
     bool mc = false;
-    McArgs* dmc = nullptr;          // device copy of the pass's description
+    McArgs* dmc = nullptr;          // the pass's description (device, in hsp_batch::desc)
     double* mc_partial = nullptr;   // mc_gz x kMcChains x mc_stride(ld)
-    uint32_t* mc_count = nullptr;   // the pass's next unit
+    uint32_t* mc_count = nullptr;   // the pass's next unit (likewise)
     uint32_t mc_gz = 0, mc_ld = 0;
     std::vector<size_t> chains;             // indices into hsp_batch::chains
     std::vector<uint32_t> gp, gz;           // the pack's blocks per chain
-    SweepArgs* dargs = nullptr;             // one launch description per chain (device)
-    const SweepArgs** dtab = nullptr;       // pointers to them (device)
-    uint16_t* dmap = nullptr;               // block -> chain within the pack (device)
-    std::vector<uint32_t*> sched;           // per-chain task lists and bounds for its gp (device)
+    SweepArgs* dargs = nullptr;             // one launch description per chain (likewise)
+    const SweepArgs** dtab = nullptr;       // pointers to them (likewise)
+    uint16_t* dmap = nullptr;               // block -> chain within the pack (likewise)
     // a shared z queue: the chains have no z blocks of their own; `workers`
     // blocks after every p-side group take all their z passes
     bool queue = false;
@@ -1032,12 +1031,13 @@ struct Pack {
     bool pre = false, split = false;
     std::vector<uint32_t> home;             // home chain of each worker (pack-local index)
     std::vector<uint32_t> unit_tiles;       // row tiles per unit of each chain
-    PackQ* dq = nullptr;                    // the queue's counters (device)
+    PackQ* dq = nullptr;                    // the queue's counters (likewise)
 };
 
 struct hsp_batch {
     std::vector<hsp_state*> chains;  // dataset-major; the first chain of each dataset owns its data
     std::vector<Pack> packs;         // how the chains share launches
+    char* desc = nullptr;            // every pack's descriptions, block maps, schedules and counters (device)
     hipStream_t stream = nullptr;
     bool own_stream = false;
     hipGraphExec_t graph = nullptr;  // every chain's sweep, one after another (more than one launch)
@@ -1065,17 +1065,10 @@ void free_packs(hsp_batch* b) {
     if (b->stream) (void)hipStreamSynchronize(b->stream);
     if (b->graph) (void)hipGraphExecDestroy(b->graph);
     b->graph = nullptr;
-    for (Pack& pk : b->packs) {
-        if (pk.dmc) (void)hipFree(pk.dmc);
+    for (Pack& pk : b->packs)
         if (pk.mc_partial) (void)hipFree(pk.mc_partial);
-        if (pk.mc_count) (void)hipFree(pk.mc_count);
-        if (pk.dargs) (void)hipFree(pk.dargs);
-        if (pk.dtab) (void)hipFree(pk.dtab);
-        if (pk.dmap) (void)hipFree(pk.dmap);
-        if (pk.dq) (void)hipFree(pk.dq);
-        for (uint32_t* q : pk.sched)
-            if (q) (void)hipFree(q);
-    }
+    if (b->desc) (void)hipFree(b->desc);
+    b->desc = nullptr;
     b->packs.clear();
 }
 
@@ -1330,17 +1323,77 @@ hsp_status plan_packs(hsp_batch* b) {
             b->packs.push_back(std::move(pk));
         }
     }
-    // device descriptions, block maps and schedules
-    for (Pack& pk : b->packs) {
+    return HSP_OK;
+}
+
+// The packs' device descriptions, block maps, schedules and counters: one
+// allocation, filled by one copy (an allocation and a blocking copy for each of
+// 24 chains' task lists, bounds and runs took 1 ms of a batch's first sweep).
+hsp_status upload_packs(hsp_batch* b) {
+    std::vector<char> img;
+    auto place = [&](size_t bytes, const void* src = nullptr) {
+        const size_t at = (img.size() + 255) / 256 * 256;
+        img.resize(at + bytes);
+        if (src) std::memcpy(img.data() + at, src, bytes);
+        return at;
+    };
+    struct Sched {
+        size_t tasks = 0, off = 0, runs = 0;
+        uint32_t nruns = 0;
+    };
+    struct At {
+        size_t args = 0, tab = 0, map = 0, q = 0, mc = 0, count = 0;
+        std::vector<Sched> sched;
+    };
+    std::vector<At> ats(b->packs.size());
+    auto subst = [](const Pack& pk, const hsp_state* s) {
+        // the chains of a multi-chain pass factor Q beside or after the
+        // pass, not under a pass of their own: there the factorisation
+        // without L^-1 (half the tile tasks and their traffic) and beta
+        // by substitution take less time than the inverse and the two
+        // products (they already round differently from a lone chain)
+        return s->x.p > (uint32_t)kSmallP &&
+               (pk.mc || pk.pre || pk.split || !chain_inverse((s->x.p + kTile - 1) / kTile));
+    };
+    for (size_t i = 0; i < b->packs.size(); ++i) {
+        const Pack& pk = b->packs[i];
+        At& at = ats[i];
         const size_t nc = pk.chains.size();
-        if (dalloc(&pk.dargs, nc) || dalloc(&pk.dtab, nc) || dalloc(&pk.dmap, pk.blocks))
-            return batch_fail(b, HSP_ENOMEM, "pack allocation failed");
-        std::vector<SweepArgs> host(nc);
+        at.args = place(nc * sizeof(SweepArgs));
+        at.tab = place(nc * sizeof(const SweepArgs*));
+        at.map = place(pk.blocks * sizeof(uint16_t));
+        if (pk.queue) at.q = place(sizeof(PackQ));
+        if (pk.mc) {
+            at.mc = place(sizeof(McArgs));
+            at.count = place(sizeof(uint32_t));
+        }
+        at.sched.resize(nc);
+        for (size_t j = 0; j < nc; ++j) {
+            const hsp_state* s = b->chains[pk.chains[j]];
+            if (s->x.p <= (uint32_t)kSmallP || pk.split) continue;
+            std::vector<uint32_t> tasks, off, runs;
+            chol_schedule((s->x.p + kTile - 1) / kTile, pk.gp[j], &tasks, &off, !subst(pk, s), &runs);
+            Sched& sc = at.sched[j];
+            sc.tasks = place(tasks.size() * 4, tasks.data());
+            sc.off = place(off.size() * 4, off.data());
+            if (!subst(pk, s)) continue;
+            sc.runs = place(runs.size() * 4, runs.data());
+            sc.nruns = (uint32_t)runs.size() - 1;
+        }
+    }
+    if (dalloc(&b->desc, img.size())) return batch_fail(b, HSP_ENOMEM, "pack allocation failed");
+    for (size_t i = 0; i < b->packs.size(); ++i) {
+        Pack& pk = b->packs[i];
+        const At& at = ats[i];
+        const size_t nc = pk.chains.size();
+        pk.dargs = reinterpret_cast<SweepArgs*>(b->desc + at.args);
+        pk.dtab = reinterpret_cast<const SweepArgs**>(b->desc + at.tab);
+        pk.dmap = reinterpret_cast<uint16_t*>(b->desc + at.map);
         std::vector<const SweepArgs*> tab(nc);
         std::vector<uint16_t> map(pk.blocks);
         PackQ hq{};
         if (pk.queue) {
-            if (dalloc(&pk.dq, 1)) return batch_fail(b, HSP_ENOMEM, "pack allocation failed");
+            pk.dq = reinterpret_cast<PackQ*>(b->desc + at.q);
             hq.nchains = (uint32_t)nc;
             hq.workers = pk.workers;
         }
@@ -1368,37 +1421,15 @@ hsp_status plan_packs(hsp_batch* b) {
                 h.zq = dev_ptr(pk.dq);
             }
             h.block0 = blk;
-            // the chains of a multi-chain pass factor Q beside or after the
-            // pass, not under a pass of their own: there the factorisation
-            // without L^-1 (half the tile tasks and their traffic) and beta
-            // by substitution take less time than the inverse and the two
-            // products (they already round differently from a lone chain)
-            if ((pk.mc || pk.pre || pk.split) && s->x.p > (uint32_t)kSmallP) h.subst = 1u;
+            h.subst = subst(pk, s) ? 1u : 0u;
             if (s->x.p > (uint32_t)kSmallP && !pk.split) {
-                const uint32_t nt = (s->x.p + kTile - 1) / kTile;
-                std::vector<uint32_t> tasks, off, runs;
-                chol_schedule(nt, h.gp, &tasks, &off, h.subst == 0u, &runs);
-                uint32_t *dt = nullptr, *doff = nullptr, *druns = nullptr;
-                if (dalloc(&dt, tasks.size()) || dalloc(&doff, off.size()))
-                    return batch_fail(b, HSP_ENOMEM, "pack allocation failed");
-                pk.sched.push_back(dt);
-                pk.sched.push_back(doff);
-                h.runs = nullptr;
-                if (h.subst) {
-                    if (dalloc(&druns, runs.size())) return batch_fail(b, HSP_ENOMEM, "pack allocation failed");
-                    pk.sched.push_back(druns);
-                    if (hipMemcpy(druns, runs.data(), runs.size() * 4, hipMemcpyHostToDevice))
-                        return batch_fail(b, HSP_EHIP, "pack schedule upload");
-                    h.runs = dev_ptr(static_cast<const uint32_t*>(druns));
-                    h.nruns = (uint32_t)runs.size() - 1;
-                }
-                if (hipMemcpy(dt, tasks.data(), tasks.size() * 4, hipMemcpyHostToDevice) ||
-                    hipMemcpy(doff, off.data(), off.size() * 4, hipMemcpyHostToDevice))
-                    return batch_fail(b, HSP_EHIP, "pack schedule upload");
-                h.tasks = dev_ptr(static_cast<const uint32_t*>(dt));
-                h.task_off = dev_ptr(static_cast<const uint32_t*>(doff));
+                const Sched& sc = at.sched[j];
+                h.tasks = dev_ptr(reinterpret_cast<const uint32_t*>(b->desc + sc.tasks));
+                h.task_off = dev_ptr(reinterpret_cast<const uint32_t*>(b->desc + sc.off));
+                h.runs = h.subst ? dev_ptr(reinterpret_cast<const uint32_t*>(b->desc + sc.runs)) : nullptr;
+                h.nruns = sc.nruns;
             }
-            host[j] = h;
+            std::memcpy(img.data() + at.args + j * sizeof h, &h, sizeof h);
             tab[j] = pk.dargs + j;
             for (uint32_t q = 0; q < h.gp + h.gz; ++q) map[blk + q] = (uint16_t)j;
             blk += h.gp + h.gz;
@@ -1415,33 +1446,39 @@ hsp_status plan_packs(hsp_batch* b) {
             // the workers follow every p-side group
             for (uint32_t w = 0; w < pk.workers; ++w) map[blk + w] = (uint16_t)(kWorkerBit | pk.home[w]);
             blk += pk.workers;
-            if (hipMemcpy(pk.dq, &hq, sizeof hq, hipMemcpyHostToDevice))
-                return batch_fail(b, HSP_EHIP, "pack upload");
+            std::memcpy(img.data() + at.q, &hq, sizeof hq);
         }
         if (blk != pk.blocks) return batch_fail(b, HSP_EHIP, "pack block map does not cover the launch");
-        if (hipMemcpy(pk.dargs, host.data(), nc * sizeof(SweepArgs), hipMemcpyHostToDevice) ||
-            hipMemcpy(pk.dtab, tab.data(), nc * sizeof(const SweepArgs*), hipMemcpyHostToDevice) ||
-            hipMemcpy(pk.dmap, map.data(), map.size() * 2, hipMemcpyHostToDevice))
-            return batch_fail(b, HSP_EHIP, "pack upload");
+        std::memcpy(img.data() + at.tab, tab.data(), nc * sizeof(const SweepArgs*));
+        std::memcpy(img.data() + at.map, map.data(), map.size() * 2);
         if (pk.mc) {
             const hsp_state* own = b->chains[pk.chains[0]];
+            pk.dmc = reinterpret_cast<McArgs*>(b->desc + at.mc);
+            pk.mc_count = reinterpret_cast<uint32_t*>(b->desc + at.count);
             McArgs m{};
             m.x = own->x;
             m.y = dev_ptr(static_cast<const uint8_t*>(own->y));
             m.nchains = (uint32_t)nc;
             m.gz = pk.mc_gz;
             m.pstride = mc_stride(pk.mc_ld);
-            if (dalloc(&pk.dmc, 1) || dalloc(&pk.mc_partial, (size_t)m.gz * kMcChains * m.pstride) ||
-                dalloc(&pk.mc_count, 1))
+            if (dalloc(&pk.mc_partial, (size_t)m.gz * kMcChains * m.pstride))
                 return batch_fail(b, HSP_ENOMEM, "pack allocation failed");
             m.partial = dev_ptr(pk.mc_partial);
             m.next_unit = dev_ptr(pk.mc_count);
             for (size_t j = 0; j < nc; ++j) m.chain[j] = dev_ptr(static_cast<const SweepArgs*>(pk.dargs + j));
-            if (hipMemset(pk.mc_count, 0, 4) || hipMemcpy(pk.dmc, &m, sizeof m, hipMemcpyHostToDevice))
-                return batch_fail(b, HSP_EHIP, "pack upload");
+            std::memcpy(img.data() + at.mc, &m, sizeof m);
         }
     }
+    if (hipMemcpy(b->desc, img.data(), img.size(), hipMemcpyHostToDevice)) return batch_fail(b, HSP_EHIP, "pack upload");
     return HSP_OK;
+}
+
+// The packs and what the device needs of them, or after a failure none.
+hsp_status make_packs(hsp_batch* b) {
+    hsp_status st = plan_packs(b);
+    if (st == HSP_OK) st = upload_packs(b);
+    if (st != HSP_OK) free_packs(b);
+    return st;
 }
 
 // Packs of plain sweeps run side by side if every launch that may then be resident
@@ -1490,7 +1527,7 @@ hipError_t batch_enqueue(hsp_batch* b) {
 // The packs (if not planned yet) and the graph of one batched sweep.
 hsp_status batch_build(hsp_batch* b) {
     if (b->packs.empty()) {
-        hsp_status st = plan_packs(b);
+        hsp_status st = make_packs(b);
         if (st != HSP_OK) return st;
     }
     if (b->graph || !forks(b)) return HSP_OK;
@@ -1633,7 +1670,7 @@ hsp_status batch_tune(hsp_batch* b) {
         if (st) return batch_fail(b, st, b->chains[i]->err);
     }
     // is there a multi-chain pass to size?
-    hsp_status st = plan_packs(b);
+    hsp_status st = make_packs(b);
     if (st) return st;
     uint32_t units = 0;
     for (const Pack& pk : b->packs)
