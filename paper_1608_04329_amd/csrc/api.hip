@@ -134,8 +134,8 @@ struct hsp_state {
     double *b = nullptr, *G = nullptr, *Gp = nullptr, *A = nullptr, *Linv = nullptr;
     double *vec = nullptr, *partial = nullptr, *bsum = nullptr;
     uint32_t* zgrp_count = nullptr;
-    uint32_t *tasks = nullptr, *task_off = nullptr, *ver = nullptr;  // tile path schedule
-    uint32_t* runs = nullptr;  // its items without L^-1
+    uint32_t *tasks = nullptr, *ver = nullptr;  // tile path schedule
+    uint32_t *task_off = nullptr, *runs = nullptr;  // its lists' bounds, and its items without L^-1 (in tasks)
     uint32_t nruns = 0;
     float* beta32 = nullptr;
     float* zdbg = nullptr;
@@ -306,7 +306,7 @@ void free_state(hsp_state* s) {
     void* bufs[] = {s->Xbuf, s->xexp, s->xscale, s->y, s->ctrl, s->beta, s->lam, s->nu, s->tau, s->xi, s->b, s->G, s->Gp,
                     s->A, s->Linv, s->vec, s->partial, s->beta32, s->zdbg, s->adbg,
                     s->ring_beta, s->ring_tau, s->ring_lam, s->trace, s->bsum,
-                    s->zgrp_count, s->dargs, s->dtab, s->tasks, s->task_off, s->runs, s->ver, s->row_id};
+                    s->zgrp_count, s->dargs, s->dtab, s->tasks, s->ver, s->row_id};
     for (void* p : bufs)
         if (p) (void)hipFree(p);
     if (s->streamed) {
@@ -361,18 +361,18 @@ hsp_status upload_schedule(hsp_state* s) {
     const bool inverse = chain_inverse(nt);
     chol_schedule(nt, s->plan.gp, &tasks, &off, inverse, &runs);
     if (s->tasks) (void)hipFree(s->tasks);
-    if (s->task_off) (void)hipFree(s->task_off);
-    if (s->runs) (void)hipFree(s->runs);
     s->tasks = s->task_off = s->runs = nullptr;
+    // one allocation and one copy for all three
+    const size_t ntasks = tasks.size(), noff = off.size();
+    tasks.insert(tasks.end(), off.begin(), off.end());
+    if (!inverse) tasks.insert(tasks.end(), runs.begin(), runs.end());
     HIP_TRY(dalloc(&s->tasks, tasks.size()));
-    HIP_TRY(dalloc(&s->task_off, off.size()));
-    HIP_TRY(hipMemcpy(s->tasks, tasks.data(), tasks.size() * 4, hipMemcpyHostToDevice));
-    HIP_TRY(hipMemcpy(s->task_off, off.data(), off.size() * 4, hipMemcpyHostToDevice));
+    s->task_off = s->tasks + ntasks;
     if (!inverse) {
-        HIP_TRY(dalloc(&s->runs, runs.size()));
-        HIP_TRY(hipMemcpy(s->runs, runs.data(), runs.size() * 4, hipMemcpyHostToDevice));
+        s->runs = s->task_off + noff;
         s->nruns = (uint32_t)runs.size() - 1;
     }
+    HIP_TRY(hipMemcpy(s->tasks, tasks.data(), tasks.size() * 4, hipMemcpyHostToDevice));
     return HSP_OK;
 }
 
@@ -872,11 +872,10 @@ hsp_status chain_impl(hsp_state* s) {
         HIP_TRY(hipMemsetAsync(s->Linv, 0, P * P * sizeof(double), s->stream));
     }
     {
-        const size_t off = handoff_offset((uint32_t)p), n = off + (p > kSmallP ? 2 * P : 0);
-        std::vector<unsigned long long> init(n, 0ull);
-        std::fill(init.begin() + off, init.end(), kNotReady);
-        HIP_TRY(dalloc(&s->vec, n));
-        HIP_TRY(hipMemcpy(s->vec, init.data(), n * 8, hipMemcpyHostToDevice));
+        const size_t off = handoff_offset((uint32_t)p);
+        const std::vector<unsigned long long> none(p > kSmallP ? 2 * P : 0, kNotReady);
+        HIP_TRY(dalloc(&s->vec, off + none.size()));
+        if (p > kSmallP) HIP_TRY(hipMemcpy(s->vec + off, none.data(), none.size() * 8, hipMemcpyHostToDevice));
     }
 
     HIP_TRY(sweep_plan(s->x, s->num_cus, &s->plan));
