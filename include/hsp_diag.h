@@ -102,6 +102,11 @@ hsp_status hsp_batch_set_shape(hsp_batch* b, int32_t zq_kib, int32_t pre_blocks)
 /* The autotuner's cache key of a state (its device, shape and plan format). */
 hsp_status hsp_tune_key(hsp_state* s, char* key, int64_t cap);
 
+/* Plan i of those that the autotuner would time for a resident state, the plan
+ * the state has first; HSP_ERANGE past the last.  Nothing is run or changed.
+ * Errors: HSP_EINVAL (NULL pointers, i < 0); HSP_EHIP. */
+hsp_status hsp_tune_candidate(hsp_state* s, int64_t i, int64_t* group_blocks, int64_t* static_pct, int64_t* unit);
+
 /* The autotuner's cache file (host only, no device work): store value under
  * key (replacing an earlier entry of that key; keys hold no tab or newline,
  * values no newline), and read it back (HSP_ERANGE if absent). */

@@ -401,7 +401,7 @@ std::string device_tag(int device, int num_cus) {
 
 // Cache key of a single chain's plan: the device, the shape and the plan format.
 std::string sweep_tune_key(const hsp_state* s) {
-    return "sweep-v1 " + device_tag(s->device, s->num_cus) + " xt=" + std::to_string(s->x.xtype) +
+    return "sweep-v2 " + device_tag(s->device, s->num_cus) + " xt=" + std::to_string(s->x.xtype) +
            " N=" + std::to_string(s->x.N) + " p=" + std::to_string(s->x.p);
 }
 
@@ -479,20 +479,10 @@ std::string plan_text(const SweepPlan& pl) {
            std::to_string(pl.unit);
 }
 
-// The autotuner for one chain: the p-side group size and how the z pass deals
-// out its tiles, by timing a few sweeps of every candidate (or from the cache).
-hsp_status tune_impl(hsp_state* s) {
-    const std::string key = sweep_tune_key(s);
-    const char* path = tune_cache_path();
-    std::string cached;
-    SweepPlan pl;
-    if (path && tune_cache_get(path, key, &cached) && plan_from_text(s, cached, &pl)) {
-        s->plan_note = plan_text(pl) + " (cache)";
-        return apply_plan(s, pl);
-    }
-    SavedChain saved;
-    hsp_status st = save_chain(s, &saved);
-    if (st) return st;
+// The plans that the autotuner times: the one the state has, so that tuning
+// never ends with a slower one than without, then other group sizes and ways to
+// deal out the z pass's tiles.
+hsp_status tune_candidates(hsp_state* s, std::vector<SweepPlan>* out) {
     const uint32_t gmax = max_group(s->x, s->plan.capacity);
     // beyond p = 4096 the factorisation sets the pace: only the group size is
     // tried (each size builds a task schedule of ~p^3 / 10^5 tasks)
@@ -513,11 +503,7 @@ hsp_status tune_impl(hsp_state* s) {
                                              : std::vector<uint32_t>{0u, 40u, 75u};
     const std::vector<uint32_t> units = large ? std::vector<uint32_t>{kZUnitDefault}
                                               : std::vector<uint32_t>{4u, 8u, 16u};
-    // shorter runs for big designs: every candidate sweeps all of X
-    const double bytes = (double)s->x.N * s->x.ld * (s->x.xtype == 0 ? 4 : 2);
-    const int timed = bytes > 1e10 ? 3 : bytes > 1e9 ? 4 : 8;
-    SweepPlan best = s->plan;
-    double best_ms = 1e300;
+    out->assign(1, s->plan);
     for (uint32_t gp : gps)
         for (uint32_t pct : pcts)
             for (uint32_t unit : units) {
@@ -525,15 +511,42 @@ hsp_status tune_impl(hsp_state* s) {
                 HIP_TRY(sweep_plan(s->x, s->num_cus, &c, gp));
                 c.static_pct = pct;
                 c.unit = unit;
-                st = apply_plan(s, c);
-                double ms = 0.0;
-                if (!st) st = time_sweeps(s, 2, timed, &ms);
-                if (st) return st;
-                if (ms < best_ms) {
-                    best_ms = ms;
-                    best = c;
-                }
+                if (plan_text(c) != plan_text(s->plan)) out->push_back(c);
             }
+    return HSP_OK;
+}
+
+// The autotuner for one chain: the p-side group size and how the z pass deals
+// out its tiles, by timing a few sweeps of every candidate (or from the cache).
+hsp_status tune_impl(hsp_state* s) {
+    const std::string key = sweep_tune_key(s);
+    const char* path = tune_cache_path();
+    std::string cached;
+    SweepPlan pl;
+    if (path && tune_cache_get(path, key, &cached) && plan_from_text(s, cached, &pl)) {
+        s->plan_note = plan_text(pl) + " (cache)";
+        return apply_plan(s, pl);
+    }
+    SavedChain saved;
+    hsp_status st = save_chain(s, &saved);
+    if (st) return st;
+    std::vector<SweepPlan> cands;
+    if ((st = tune_candidates(s, &cands))) return st;
+    // shorter runs for big designs: every candidate sweeps all of X
+    const double bytes = (double)s->x.N * s->x.ld * (s->x.xtype == 0 ? 4 : 2);
+    const int timed = bytes > 1e10 ? 3 : bytes > 1e9 ? 4 : 8;
+    SweepPlan best = s->plan;
+    double best_ms = 1e300;
+    for (const SweepPlan& c : cands) {
+        st = apply_plan(s, c);
+        double ms = 0.0;
+        if (!st) st = time_sweeps(s, 2, timed, &ms);
+        if (st) return st;
+        if (ms < best_ms) {
+            best_ms = ms;
+            best = c;
+        }
+    }
     st = apply_plan(s, best);
     if (!st) st = restore_chain(s, saved);
     if (st) return st;
@@ -1609,7 +1622,7 @@ std::string batch_tune_key(const hsp_batch* b) {
     char hex[17];
     std::snprintf(hex, sizeof hex, "%016llx", (unsigned long long)h);
     const hsp_state* s0 = b->chains[0];
-    return "batch-v6 " + device_tag(s0->device, s0->num_cus) + " chains=" + std::to_string(b->chains.size()) +
+    return "batch-v7 " + device_tag(s0->device, s0->num_cus) + " chains=" + std::to_string(b->chains.size()) +
            " h=" + hex;
 }
 
@@ -2354,6 +2367,17 @@ hsp_status hsp_tune_key(hsp_state* s, char* key, int64_t cap) {
     const std::string k = sweep_tune_key(s);
     if ((int64_t)k.size() >= cap) return fail(s, HSP_EINVAL, "key buffer too small");
     std::memcpy(key, k.c_str(), k.size() + 1);
+    return HSP_OK;
+}
+
+hsp_status hsp_tune_candidate(hsp_state* s, int64_t i, int64_t* group_blocks, int64_t* static_pct, int64_t* unit) {
+    if (!s || i < 0 || !group_blocks || !static_pct || !unit) return HSP_EINVAL;
+    std::vector<SweepPlan> c;
+    if (hsp_status st = tune_candidates(s, &c)) return st;
+    if (i >= (int64_t)c.size()) return HSP_ERANGE;
+    *group_blocks = c[(size_t)i].gp;
+    *static_pct = c[(size_t)i].static_pct;
+    *unit = c[(size_t)i].unit;
     return HSP_OK;
 }
 

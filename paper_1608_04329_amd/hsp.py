@@ -31,7 +31,7 @@ EXPORTS = ["hsp_default_options", "hsp_max_p", "hsp_gram", "hsp_gram_noalloc", "
            "hsp_batch_chain", "hsp_batch_sweep", "hsp_batch_sync", "hsp_batch_set_timing",
            "hsp_batch_get_timing", "hsp_batch_last_error", "hsp_batch_destroy", "hsp_get_plan",
            "hsp_sort_rows", "hsp_batch_get_plan", "hsp_tune_key", "hsp_tune_cache_put", "hsp_tune_cache_get",
-           "hsp_batch_set_shape", "hsp_set_gather"]
+           "hsp_batch_set_shape", "hsp_set_gather", "hsp_tune_candidate"]
 
 
 class hsp_options(C.Structure):
@@ -117,6 +117,7 @@ def load():
     L.hsp_batch_get_plan.restype = st
     L.hsp_batch_set_shape.argtypes = [vp, C.c_int32, C.c_int32]; L.hsp_batch_set_shape.restype = st
     L.hsp_tune_key.argtypes = [vp, C.c_char_p, i64]; L.hsp_tune_key.restype = st
+    L.hsp_tune_candidate.argtypes = [vp, i64, pi64, pi64, pi64]; L.hsp_tune_candidate.restype = st
     L.hsp_tune_cache_put.argtypes = [C.c_char_p, C.c_char_p, C.c_char_p]; L.hsp_tune_cache_put.restype = st
     L.hsp_tune_cache_get.argtypes = [C.c_char_p, C.c_char_p, C.c_char_p, i64]
     L.hsp_tune_cache_get.restype = st
@@ -358,6 +359,18 @@ def hsp_tune_key(h):
     buf = C.create_string_buffer(512)
     _check(load().hsp_tune_key(h, buf, 512), h)
     return buf.value.decode()
+
+
+def hsp_tune_candidates(h):
+    """(group_blocks, static_pct, unit) of every plan the autotuner would time."""
+    out = []
+    while True:
+        v = [C.c_int64() for _ in range(3)]
+        st = load().hsp_tune_candidate(h, len(out), *[C.byref(x) for x in v])
+        if st == HSP_ERANGE:
+            return out
+        _check(st, h)
+        out.append(tuple(x.value for x in v))
 
 
 def hsp_tune_cache_put(path, key, value):
