@@ -751,7 +751,7 @@ hsp_status create_stream_impl(hsp_state* s, const float* X, const uint8_t* y, in
         const size_t r0 = (size_t)c * s->chunk_rows;
         if (!e) e = pack_x_launch(src, cl, s->xexp, s->stream);
         if (!e) e = validate_launch(cl, s->y + r0, s->ctrl, s->stream);
-        if (!e) e = gram_chunk_launch(cl, gg, r0, (uint64_t)N, work, s->stream);
+        if (!e) e = gram_chunk_launch(cl, gg, r0, (uint64_t)N, s->num_cus, work, s->stream);
         if (!e) e = hipMemcpyAsync(static_cast<char*>(s->Xhost) + r0 * row_bytes, s->stage[0], rows * row_bytes,
                                    hipMemcpyDeviceToHost, s->stream);
         if (!e) e = hipStreamSynchronize(s->stream);  // the stage and raw buffers are reused

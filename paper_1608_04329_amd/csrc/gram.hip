@@ -191,19 +191,30 @@ __device__ __forceinline__ void gram_item(const GramGeometry& g, const GramPart&
 
 // The pairs of part over the rows of x.  CHUNK: these are rows row0, row0 + 1, ...
 // of the N rows that the splits cut up, and a split that began before row0 goes on
-// from its partial tile (else row0 = 0, N = x.N).  work holds, class after class, a tile per (split, pair of the
-// part), split-major.  Blocks are dealt to the eight XCDs in turn; each XCD takes
-// a contiguous eighth of the list, so the pairs of one range of rows mostly run
-// on one XCD, whose L2 serves the rows they share.
-template <int XT, int NB, bool ALIGNED, bool CHUNK>
+// from its partial tile (else row0 = 0, N = x.N).  work holds, class after class, a
+// tile per (split, pair of the part), split-major.  Blocks are dealt to the eight
+// XCDs in turn; each XCD takes a contiguous eighth of the list, so the pairs of one
+// range of rows mostly run on one XCD, whose L2 serves the rows they share.  Not so
+// with CHUNK: the items with rows of the chunk are next to each other in the list,
+// and go to all XCDs (as eighths of the list they ran on one or two of them: the
+// first of those creations 252 -> 217 ms, the second 283 -> 211).
+//
+// QUARTER (with CHUNK): blocks of a 64-wide quarter of a 128-wide tile each, four
+// times as many.  An entry's products are added in the same order, so G is the same
+// bit for bit.  For chunks that lie in one or a few splits: whole tiles are then
+// about npairs blocks, fewer than there are compute units (gram_chunk_launch).
+template <int XT, int NB, bool ALIGNED, bool CHUNK, bool QUARTER = false>
 __global__ __launch_bounds__(256, 2) void gram_tile_kernel(XLayout x, double* __restrict__ work, GramGeometry g,
                                                            GramPart part, uint32_t items, uint64_t row0, uint64_t N) {
-    constexpr int T = 32 * NB, LD = gram_stride<NB>();
+    constexpr int T = 32 * NB, LD = gram_stride<NB>(), WT = QUARTER ? 2 * T : T;  // WT: width of work's tiles
     constexpr int VN = XT == 0 ? 4 : 8, TPR = T / VN, RPP = 256 / TPR, PASSES = kGramK / RPP;
     static_assert(RPP * PASSES == kGramK, "whole passes per stage");
     __shared__ __align__(16) float lds[2][2][kGramK * LD];
-    const uint32_t per_xcd = (items + 7u) / 8u, w = (blockIdx.x & 7u) * per_xcd + (blockIdx.x >> 3);
-    if (w >= items) return;
+    constexpr uint32_t kParts = QUARTER ? 4u : 1u;
+    const uint32_t per_xcd = (kParts * items + 7u) / 8u;
+    const uint32_t b = CHUNK ? blockIdx.x : (blockIdx.x & 7u) * per_xcd + (blockIdx.x >> 3);
+    if (b >= kParts * items) return;
+    const uint32_t w = b / kParts, qi = b % kParts >> 1, qj = b % kParts & 1u;
     uint32_t cls, item, ti, tj, count = 1, first = 0, rows_per_split = 0;
     gram_item(g, part, w, cls, item);
     size_t tile = item;
@@ -227,7 +238,12 @@ __global__ __launch_bounds__(256, 2) void gram_tile_kernel(XLayout x, double* __
         r_begin = resume ? 0 : r_begin - row0;
         r_end = min((size_t)x.N, r_end - row0);
     }
-    double* out = work + tile * (T * T);
+    double* out = work + tile * (WT * WT) + (qi * WT + qj) * T;
+    if constexpr (QUARTER) {
+        ti = 2 * ti + qi;
+        tj = 2 * tj + qj;
+        if (ti > tj || tj * T >= x.p) return;
+    }
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wr = wave >> 1, wc = wave & 1;
     const bool diag = ti == tj;
@@ -243,7 +259,7 @@ __global__ __launch_bounds__(256, 2) void gram_tile_kernel(XLayout x, double* __
     // block (2 i + wr, 2 j + wc) is inside the matrix and not below its diagonal
     auto held = [&](int i, int j) { return 2 * i + wr < nI && 2 * j + wc < nJ && (!diag || 2 * i + wr <= 2 * j + wc); };
     if (CHUNK && resume) {
-        uint32_t at = kr * T + cc;
+        uint32_t at = kr * WT + cc;
         asm volatile("" : "+v"(at));  // the addresses are not kept for the stores at the end
 #pragma unroll
         for (int i = 0; i < NB; ++i)
@@ -252,7 +268,7 @@ __global__ __launch_bounds__(256, 2) void gram_tile_kernel(XLayout x, double* __
                 if (held(i, j)) {
 #pragma unroll
                     for (int r = 0; r < 4; ++r)
-                        acc[i][j][r] = out[(16 * (2 * i + wr) + 4 * r) * T + 16 * (2 * j + wc) + at];
+                        acc[i][j][r] = out[(16 * (2 * i + wr) + 4 * r) * WT + 16 * (2 * j + wc) + at];
                 }
     }
     // staging: thread t takes VN columns of stage rows t / TPR + RPP s
@@ -316,7 +332,7 @@ __global__ __launch_bounds__(256, 2) void gram_tile_kernel(XLayout x, double* __
             if (held(i, j)) {
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
-                    out[(16 * (2 * i + wr) + kr + 4 * r) * T + 16 * (2 * j + wc) + cc] = acc[i][j][r];
+                    out[(16 * (2 * i + wr) + kr + 4 * r) * WT + 16 * (2 * j + wc) + cc] = acc[i][j][r];
             }
 }
 
@@ -566,11 +582,26 @@ size_t gram_pair_doubles(const GramGeometry& g) {
     return (size_t)ns * g.tile * g.tile;
 }
 
-hipError_t gram_chunk_launch(const XLayout& chunk, const GramGeometry& g, uint64_t row0, uint64_t N, double* work,
-                             hipStream_t st) {
+hipError_t gram_chunk_launch(const XLayout& chunk, const GramGeometry& g, uint64_t row0, uint64_t N, int num_cus,
+                             double* work, hipStream_t st) {
     if (chunk.N == 0) return hipSuccess;
     if (row0 % 64 != 0 || row0 + chunk.N > N || !gram_aligned(chunk)) return hipErrorInvalidValue;
-    gram_tiles_launch(chunk, work, g, whole(g), row0, N, st);
+    // Blocks with rows of this chunk.  Up to one per compute unit, quarters of tiles:
+    // creation from N = 4e5, p = 1000 float32 in chunks of 4096 rows (36 pairs) 217
+    // -> 189 ms, from N = 2e5, p = 2000 in chunks of 2048 (136 pairs) 211 -> 191;
+    // with more, whole tiles read X fewer times.
+    uint64_t live = 0, items = 0;
+    for (int c = 0; c < kGramClasses; ++c) {
+        live += g.npairs[c] * ((row0 + chunk.N - 1) / g.rows[c] - row0 / g.rows[c] + 1);
+        items += (uint64_t)g.npairs[c] * g.nsplit[c];
+    }
+    if (g.tile == 128 && chunk.N < N && live <= (uint64_t)num_cus) {
+        const dim3 grid((unsigned)((4 * items + 7) / 8 * 8));
+        auto f = chunk.xtype == 0 ? &gram_tile_kernel<0, 2, true, true, true> : &gram_tile_kernel<1, 2, true, true, true>;
+        hipLaunchKernelGGL(f, grid, dim3(256), 0, st, chunk, work, g, whole(g), (uint32_t)items, row0, N);
+    } else {
+        gram_tiles_launch(chunk, work, g, whole(g), row0, N, st);
+    }
     return hipGetLastError();
 }
 

@@ -357,10 +357,11 @@ struct GramPart {
 GramGeometry gram_geometry(const XLayout& x, int num_cus);
 // The partial tiles of every pair over one chunk of rows (chunk.N rows from row0,
 // a multiple of 64, of the N rows of geometry g; rows start on 16-byte boundaries;
-// chunks follow each other on the stream) into work, which holds gram_work_doubles(g); then G from all of them,
-// the same G, bit for bit, as gram_launch's.
-hipError_t gram_chunk_launch(const XLayout& chunk, const GramGeometry& g, uint64_t row0, uint64_t N, double* work,
-                             hipStream_t st);
+// chunks follow each other on the stream) into work, which holds
+// gram_work_doubles(g); then G from all of them, the same G, bit for bit, as
+// gram_launch's.
+hipError_t gram_chunk_launch(const XLayout& chunk, const GramGeometry& g, uint64_t row0, uint64_t N, int num_cus,
+                             double* work, hipStream_t st);
 hipError_t gram_reduce_launch(const double* work, const GramGeometry& g, uint32_t p, const int32_t* e, double* G,
                               hipStream_t st);
 // Doubles of workspace that hold every partial tile at once.

@@ -70,3 +70,12 @@ def test_gram_of_very_many_columns():
         assert torch.equal(G[i:i + 4096], d[i:i + 4096, None] * d[None, :])
     del G
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("xt,N,p,rows", [("f32", 1500, 129, 64), ("bf16", 1500, 192, 320), ("f32", 2100, 193, 512),
+                                         ("bf16", 2100, 257, 64), ("f32", 1000, 384, 128),  # quarters of tiles
+                                         ("f32", 1000, 2900, 512), ("bf16", 700, 2820, 320)])  # whole ones
+def test_gram_of_row_chunks_by_quarters_and_whole_tiles(xt, N, p, rows):
+    """A chunk that few blocks have rows of is taken in 64-wide quarters of the
+    128-wide tiles: the resident design's G, bit for bit."""
+    test_gram_of_row_chunks(xt, N, p, rows)
