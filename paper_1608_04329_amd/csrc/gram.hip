@@ -340,14 +340,18 @@ __global__ __launch_bounds__(256, 2) void gram_tile_kernel(XLayout x, double* __
 // by 2^(e_i + e_j) (exact) if e.  A block takes 64 entries; wave w sums the
 // splits of the w-th quarter in order, eight loads in flight, and the four sums
 // are added in wave order: a fixed order, and four times the loads in flight of
-// one thread per entry (N = 1e5, p = 100, 342 splits: 80 -> 8 us).
+// one thread per entry (N = 1e5, p = 100, 342 splits: 80 -> 8 us).  FEW (at most four
+// splits of any pair, so that a quarter is one): 256 entries per block, one thread
+// sums all of an entry's, which is the same sum (hsp_gram, N = 3, p = 2100: 107 -> 72 us).
+template <bool FEW>
 __global__ __launch_bounds__(256) void gram_reduce_kernel(const double* __restrict__ work, GramGeometry g, GramPart part,
                                                           uint32_t p, const int32_t* __restrict__ e,
                                                           double* __restrict__ G) {
     __shared__ double part_sum[4][64];
     const uint32_t T = g.tile, tt = T * T, lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
-    const size_t idx = blockIdx.x * (size_t)64 + lane;  // 64 divides T * T: a block's entries share a pair
-    uint32_t pc = (uint32_t)(blockIdx.x * (size_t)64 / tt), cls = 0, count = 0, first = 0, nsplit = 1, ti, tj;
+    constexpr uint32_t E = FEW ? 256u : 64u;  // entries of a block; E divides T * T: they share a pair
+    const size_t idx = blockIdx.x * (size_t)E + (FEW ? threadIdx.x : lane);
+    uint32_t pc = (uint32_t)(blockIdx.x * (size_t)E / tt), cls = 0, count = 0, first = 0, nsplit = 1, ti, tj;
     const uint32_t local = (uint32_t)(idx % tt);
     size_t base = 0;
     bool found = false;
@@ -368,7 +372,7 @@ __global__ __launch_bounds__(256) void gram_reduce_kernel(const double* __restri
     pair_of(cls, first + pc, g.nt, ti, tj);
     const uint32_t i = ti * T + local / T, j = tj * T + local % T;
     const bool live = i < p && j < p && !(ti == tj && j < i);
-    const uint32_t per = (nsplit + 3u) / 4u, s0 = min(wave * per, nsplit), s1 = min(s0 + per, nsplit);
+    const uint32_t per = (nsplit + 3u) / 4u, s0 = FEW ? 0u : min(wave * per, nsplit), s1 = FEW ? nsplit : min(s0 + per, nsplit);
     const double* src = work + (base + pc) * tt + local;
     const size_t step = (size_t)count * tt;
     double s = 0.0;
@@ -376,10 +380,13 @@ __global__ __launch_bounds__(256) void gram_reduce_kernel(const double* __restri
 #pragma unroll 8
         for (uint32_t sp = s0; sp < s1; ++sp) s += src[sp * step];
     }
-    part_sum[wave][lane] = s;
-    __syncthreads();
-    if (wave != 0 || !live) return;
-    s = ((part_sum[0][lane] + part_sum[1][lane]) + part_sum[2][lane]) + part_sum[3][lane];
+    if constexpr (!FEW) {
+        part_sum[wave][lane] = s;
+        __syncthreads();
+        if (wave != 0) return;
+        s = ((part_sum[0][lane] + part_sum[1][lane]) + part_sum[2][lane]) + part_sum[3][lane];
+    }
+    if (!live) return;
     if (e) s = ldexp(s, e[i] + e[j]);
     G[(size_t)i * p + j] = s;
     G[(size_t)j * p + i] = s;
@@ -414,7 +421,14 @@ bool gram_aligned(const XLayout& x) {
 }
 }  // namespace
 
-// Tile width: 64 up to p = 128, where 128-wide tiles would be mostly padding.
+// Tile width: 64 up to p = 128, where 128-wide tiles would be mostly padding, and
+// for short designs, which are too few blocks of 128-wide tiles (us with 128- and
+// 64-wide tiles, float32: N = 500, p = 130 31 / 22, p = 333 70 / 59, p = 2100 162 /
+// 148; N = 2000, p = 130 68 / 58, p = 1000 135 / 115, but p = 2100 277 / 281;
+// N = 3000, p = 1000 167 / 137, p = 700 99 / 100, p = 2100 359 / 370).  These take as
+// many splits of up to 256 rows as 2 MB of partials hold, if that many: a larger
+// workspace is not one that the runtime has at hand (about 30 us; N = 800, p = 130
+// 54 -> 25 us, N = 500, p = 200 52 -> 25).
 // Row splits: at least four 64-wide-tile blocks per compute unit in all.  With
 // 128-wide tiles a class takes splits in proportion to the products of a row of
 // its tiles (16 per wave for a whole tile, 10 on the diagonal, fewer in a narrow
@@ -434,7 +448,7 @@ GramGeometry gram_geometry(const XLayout& x, int num_cus) {
     const uint64_t nt64 = (x.p + 63) / 64, np64 = nt64 * (nt64 + 1) / 2;
     const uint64_t max_split = ((uint64_t)x.N + 63) / 64;
     const uint64_t lo = std::max<uint64_t>(1, std::min(max_split, ((uint64_t)num_cus * 4 + np64 - 1) / np64));
-    g.tile = x.p <= 128u ? 64u : 128u;
+    g.tile = x.p <= 128u || x.N <= 1024u || (x.N <= 2048u && x.p <= 1024u) ? 64u : 128u;
     g.nt = (x.p + g.tile - 1) / g.tile;
     const uint32_t inner = g.nt - 1;
     g.npairs[kGramFull] = inner > 0 ? inner * (inner - 1) / 2 : 0u;
@@ -451,8 +465,12 @@ GramGeometry gram_geometry(const XLayout& x, int num_cus) {
             h->nsplit[c] = (uint32_t)(((uint64_t)x.N + rows - 1) / rows);
         }
     };
+    if (g.tile == 64u) {
+        const uint64_t fit = ((2u << 20) - 1u) / (np64 * 64 * 64 * sizeof(double));
+        cut(x.p > 128u && x.N <= 256u * fit ? std::min(lo, fit) : lo, &g);
+        return g;
+    }
     cut(lo, &g);
-    if (g.tile == 64u) return g;
     // one pair's partials over every split fit the fixed workspace
     const uint64_t np = (uint64_t)g.nt * (g.nt + 1) / 2;
     const uint64_t hi = std::min({max_split, ((uint64_t)num_cus * 16 + np - 1) / np,
@@ -510,8 +528,9 @@ hipError_t gram_sum_launch(const double* work, const GramGeometry& g, const Gram
                            const int32_t* e, double* G, hipStream_t st) {
     size_t pairs = 0;
     for (int c = 0; c < kGramClasses; ++c) pairs += part.count[c];
-    hipLaunchKernelGGL(gram_reduce_kernel, dim3((unsigned)(pairs * g.tile * g.tile / 64)), dim3(256), 0, st, work, g,
-                       part, p, e, G);
+    const bool few = *std::max_element(g.nsplit, g.nsplit + kGramClasses) <= 4;
+    hipLaunchKernelGGL(few ? &gram_reduce_kernel<true> : &gram_reduce_kernel<false>,
+                       dim3((unsigned)(pairs * g.tile * g.tile / (few ? 256 : 64))), dim3(256), 0, st, work, g, part, p, e, G);
     return hipGetLastError();
 }
 

@@ -72,10 +72,19 @@ def test_gram_of_very_many_columns():
     torch.cuda.empty_cache()
 
 
-@pytest.mark.parametrize("xt,N,p,rows", [("f32", 1500, 129, 64), ("bf16", 1500, 192, 320), ("f32", 2100, 193, 512),
-                                         ("bf16", 2100, 257, 64), ("f32", 1000, 384, 128),  # quarters of tiles
-                                         ("f32", 1000, 2900, 512), ("bf16", 700, 2820, 320)])  # whole ones
+@pytest.mark.parametrize("xt,N,p,rows", [("f32", 2500, 129, 64), ("bf16", 2500, 192, 320), ("f32", 3100, 193, 512),
+                                         ("bf16", 2100, 257, 64), ("f32", 2400, 384, 128),  # quarters of tiles
+                                         ("f32", 2200, 2900, 512), ("bf16", 2100, 2820, 1088)])  # whole ones
 def test_gram_of_row_chunks_by_quarters_and_whole_tiles(xt, N, p, rows):
     """A chunk that few blocks have rows of is taken in 64-wide quarters of the
     128-wide tiles: the resident design's G, bit for bit."""
     test_gram_of_row_chunks(xt, N, p, rows)
+
+
+@pytest.mark.parametrize("xt", ["f32", "bf16"])
+@pytest.mark.parametrize("N,p,ld", [(2048, 130, 130), (2049, 130, 131), (2049, 145, 145), (2100, 255, 256), (2500, 383, 383),
+                                    (1024, 1025, 1032), (1025, 1025, 1027), (3, 700, 700), (250, 200, 200), (257, 140, 144)])
+def test_gram_of_short_designs(xt, N, p, ld):
+    """Where 64-wide tiles take over from 128-wide ones (up to N = 1024, or 2048
+    with p <= 1024), and where one thread sums an entry's splits (up to four)."""
+    test_gram_tile_edges(xt, N, p, ld)
