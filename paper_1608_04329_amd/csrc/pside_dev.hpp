@@ -479,51 +479,129 @@ template <int C>
 __device__ __forceinline__ double row_bcast(double v) {
     return __builtin_amdgcn_update_dpp(0.0, v, 0x150 + C, 0xf, 0xf, true);
 }
-// acc -= (lane C of x's row of 16 lanes) * y, in one instruction.  x must have
-// passed settle() since it was written.
-template <int C>
-__device__ __forceinline__ void fmsub_bcast(double& acc, double x, double y) {
-    asm("v_fmac_f64_dpp %0, -%1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(x), "v"(y), "n"(C));
-}
-// The two wait states that a vector write of x needs before its use as the source
-// of a cross-lane operand, where the write or the use is inside fmsub_bcast and
-// the compiler does not see it.
+// A vector register that is written needs two wait states before a cross-lane
+// operand reads it, and the compiler, which keeps to that for its own instructions,
+// sees neither the write nor the read of one inside asm.  settle() stands between a
+// write inside asm and a cross-lane operand of the compiler's.
 __device__ __forceinline__ void settle(double& x) { asm("s_nop 1" : "+v"(x)); }
 
-// Pivots C .. 15 of a 16-row panel: d holds the panel's diagonal block (column
-// l % 16 in lane l, a copy in each row of 16 lanes), a the 64 other columns of
-// the panel, one per lane.  Row C is scaled by 1 / sqrt(pivot), then every later
-// row i loses (row C's entry at column i) times row C: the multiplier is lane
-// i's entry of row C's diagonal part, which a row of 16 lanes broadcasts to
-// itself, so each row costs two instructions and no scalar registers.
-template <int C, int I>
-__device__ __forceinline__ void panel_rows(double (&d)[16], double (&a)[16]) {
-    if constexpr (I < 16) {
-        fmsub_bcast<I>(d[I], d[C], d[C]);
-        fmsub_bcast<I>(a[I], d[C], a[C]);
-        panel_rows<C, I + 1>(d, a);
-    }
+// acc -= (lane C of x's row of 16 lanes) * y is one instruction (HSP_FMSUB).  Blocks
+// of them wait for x themselves, in the same asm: whatever the compiler puts before
+// it, a copy or a reload of x from a spill among others, has then settled.  (Their
+// results are early clobbers: no operand read later may share a register with one.)
+#define HSP_FMSUB(acc, x, y, lane) \
+    "v_fmac_f64_dpp %" #acc ", -%" #x ", %" #y " row_newbcast:%" #lane " row_mask:0xf bank_mask:0xf\n\t"
+
+// Pivots of a 16-row panel: d holds the panel's diagonal block (column l % 16 in
+// lane l, a copy in each row of 16 lanes), a the 64 other columns of the panel, one
+// per lane.  Row C is scaled by 1 / sqrt(pivot), then every later row i loses (row
+// C's entry at column i) times row C: the multiplier is lane i's entry of row C's
+// diagonal part, which a row of 16 lanes broadcasts to itself, so each row costs
+// two instructions and no scalar registers.
+//
+// The n rows I .. 15 lose their part of row I - 1 in one asm block, which also
+// returns 1 / sqrt(pivot I) (rsqrt_nr's operations) for the next step: the first
+// row is done first, and the root's chain runs between the other rows' instructions,
+// with two of them or waits before the pivot's broadcast and one after the
+// hardware's estimate.  N = 1e5, p = 100, us per 8 sweeps: one asm statement per
+// instruction, arranged by the compiler (which could put a copy before any) 348,
+// blocks of up to four with a wait each 366, this 337.
+#define HSP_D(r) "v_fmac_f64_dpp %[d" #r "], -%[x], %[x] row_newbcast:%[l" #r "] row_mask:0xf bank_mask:0xf\n\t"
+#define HSP_A(r) "v_fmac_f64_dpp %[a" #r "], -%[x], %[y] row_newbcast:%[l" #r "] row_mask:0xf bank_mask:0xf\n\t"
+#define HSP_DA(r) HSP_D(r) HSP_A(r)
+#define HSP_ROOT1 "v_mov_b64_dpp %[t], %[d0] row_newbcast:%[l0] row_mask:0xf bank_mask:0xf\n\t"
+#define HSP_ROOT2 "v_rsq_f64 %[rs], %[t]\n\t"
+#define HSP_ROOT3 "v_mul_f64 %[e], %[rs], -%[t]\n\t"
+#define HSP_ROOT4 "v_fma_f64 %[e], %[e], %[rs], 1.0\n\tv_mul_f64 %[t], %[rs], 0.5\n\t"
+#define HSP_ROOT5 "v_fmac_f64 %[rs], %[t], %[e]\n\t"
+#define HSP_T1 "s_nop 1\n\t" HSP_DA(0) "s_nop 0\n\t" HSP_ROOT1 HSP_ROOT2 "s_nop 0\n\t" HSP_ROOT3 HSP_ROOT4 HSP_ROOT5
+#define HSP_T2 "s_nop 1\n\t" HSP_DA(0) HSP_D(1) HSP_ROOT1 HSP_ROOT2 HSP_A(1) HSP_ROOT3 HSP_ROOT4 HSP_ROOT5
+#define HSP_HEAD "s_nop 1\n\t" HSP_DA(0) HSP_D(1) HSP_ROOT1 HSP_A(1) HSP_ROOT2 HSP_DA(2)
+#define HSP_T3 HSP_HEAD HSP_ROOT3 HSP_ROOT4 HSP_ROOT5
+#define HSP_T4 HSP_HEAD HSP_ROOT3 HSP_DA(3) HSP_ROOT4 HSP_ROOT5
+#define HSP_T5 HSP_HEAD HSP_ROOT3 HSP_DA(3) HSP_ROOT4 HSP_DA(4) HSP_ROOT5
+#define HSP_T6 HSP_HEAD HSP_DA(3) HSP_ROOT3 HSP_DA(4) HSP_ROOT4 HSP_DA(5) HSP_ROOT5
+#define HSP_T7 HSP_T6 HSP_DA(6)
+#define HSP_T8 HSP_T7 HSP_DA(7)
+#define HSP_T9 HSP_T8 HSP_DA(8)
+#define HSP_T10 HSP_T9 HSP_DA(9)
+#define HSP_T11 HSP_T10 HSP_DA(10)
+#define HSP_T12 HSP_T11 HSP_DA(11)
+#define HSP_T13 HSP_T12 HSP_DA(12)
+#define HSP_T14 HSP_T13 HSP_DA(13)
+#define HSP_T15 HSP_T14 HSP_DA(14)
+#define HSP_OUT(r) [d##r] "+&v"(d[I + r]), [a##r] "+&v"(a[I + r])
+#define HSP_O1 HSP_OUT(0)
+#define HSP_O2 HSP_O1, HSP_OUT(1)
+#define HSP_O3 HSP_O2, HSP_OUT(2)
+#define HSP_O4 HSP_O3, HSP_OUT(3)
+#define HSP_O5 HSP_O4, HSP_OUT(4)
+#define HSP_O6 HSP_O5, HSP_OUT(5)
+#define HSP_O7 HSP_O6, HSP_OUT(6)
+#define HSP_O8 HSP_O7, HSP_OUT(7)
+#define HSP_O9 HSP_O8, HSP_OUT(8)
+#define HSP_O10 HSP_O9, HSP_OUT(9)
+#define HSP_O11 HSP_O10, HSP_OUT(10)
+#define HSP_O12 HSP_O11, HSP_OUT(11)
+#define HSP_O13 HSP_O12, HSP_OUT(12)
+#define HSP_O14 HSP_O13, HSP_OUT(13)
+#define HSP_O15 HSP_O14, HSP_OUT(14)
+#define HSP_LANE(r) [l##r] "n"(I + r)
+#define HSP_L1 HSP_LANE(0)
+#define HSP_L2 HSP_L1, HSP_LANE(1)
+#define HSP_L3 HSP_L2, HSP_LANE(2)
+#define HSP_L4 HSP_L3, HSP_LANE(3)
+#define HSP_L5 HSP_L4, HSP_LANE(4)
+#define HSP_L6 HSP_L5, HSP_LANE(5)
+#define HSP_L7 HSP_L6, HSP_LANE(6)
+#define HSP_L8 HSP_L7, HSP_LANE(7)
+#define HSP_L9 HSP_L8, HSP_LANE(8)
+#define HSP_L10 HSP_L9, HSP_LANE(9)
+#define HSP_L11 HSP_L10, HSP_LANE(10)
+#define HSP_L12 HSP_L11, HSP_LANE(11)
+#define HSP_L13 HSP_L12, HSP_LANE(12)
+#define HSP_L14 HSP_L13, HSP_LANE(13)
+#define HSP_L15 HSP_L14, HSP_LANE(14)
+#define HSP_PIVOT(n)                                                                                                  \
+    if constexpr (16 - I == n)                                                                                        \
+        asm(HSP_T##n : HSP_O##n, [rs] "=&v"(rs), [t] "=&v"(t), [e] "=&v"(e) : [x] "v"(d[I - 1]), [y] "v"(a[I - 1]), HSP_L##n);
+template <int I>
+__device__ __forceinline__ double panel_rows(double (&d)[16], double (&a)[16]) {
+    double rs, t, e;
+    HSP_PIVOT(1)
+    HSP_PIVOT(2)
+    HSP_PIVOT(3)
+    HSP_PIVOT(4)
+    HSP_PIVOT(5)
+    HSP_PIVOT(6)
+    HSP_PIVOT(7)
+    HSP_PIVOT(8)
+    HSP_PIVOT(9)
+    HSP_PIVOT(10)
+    HSP_PIVOT(11)
+    HSP_PIVOT(12)
+    HSP_PIVOT(13)
+    HSP_PIVOT(14)
+    HSP_PIVOT(15)
+    return rs;
 }
-template <int C>
-__device__ __forceinline__ void panel_pivots(double (&d)[16], double (&a)[16]) {
-    if constexpr (C < 16) {
-        settle(d[C]);
-        const double rs = rsqrt_nr(row_bcast<C>(d[C]));
-        d[C] *= rs;
-        a[C] *= rs;
-        settle(d[C]);
-        panel_rows<C, C + 1>(d, a);
-        panel_pivots<C + 1>(d, a);
-    }
+template <int C = 0>
+__device__ __forceinline__ void panel_pivots(double (&d)[16], double (&a)[16], double rs) {
+    d[C] *= rs;
+    a[C] *= rs;
+    if constexpr (C < 15) panel_pivots<C + 1>(d, a, panel_rows<C + 1>(d, a));
 }
 
 // acc += sum_j x_j y[j], x_j being lane j of x's row of 16 lanes.
-template <int J = 0>
 __device__ __forceinline__ void dot_bcast(double& acc, double minus_x, const double (&y)[16]) {
-    if constexpr (J < 16) {
-        fmsub_bcast<J>(acc, minus_x, y[J]);
-        dot_bcast<J + 1>(acc, minus_x, y);
-    }
+    asm("s_nop 1\n\t" HSP_FMSUB(0, 1, 2, 18) HSP_FMSUB(0, 1, 3, 19) HSP_FMSUB(0, 1, 4, 20) HSP_FMSUB(0, 1, 5, 21)
+            HSP_FMSUB(0, 1, 6, 22) HSP_FMSUB(0, 1, 7, 23) HSP_FMSUB(0, 1, 8, 24) HSP_FMSUB(0, 1, 9, 25)
+                HSP_FMSUB(0, 1, 10, 26) HSP_FMSUB(0, 1, 11, 27) HSP_FMSUB(0, 1, 12, 28) HSP_FMSUB(0, 1, 13, 29)
+                    HSP_FMSUB(0, 1, 14, 30) HSP_FMSUB(0, 1, 15, 31) HSP_FMSUB(0, 1, 16, 32) HSP_FMSUB(0, 1, 17, 33)
+        : "+&v"(acc)
+        : "v"(minus_x), "v"(y[0]), "v"(y[1]), "v"(y[2]), "v"(y[3]), "v"(y[4]), "v"(y[5]), "v"(y[6]), "v"(y[7]), "v"(y[8]),
+          "v"(y[9]), "v"(y[10]), "v"(y[11]), "v"(y[12]), "v"(y[13]), "v"(y[14]), "v"(y[15]), "n"(0), "n"(1), "n"(2), "n"(3),
+          "n"(4), "n"(5), "n"(6), "n"(7), "n"(8), "n"(9), "n"(10), "n"(11), "n"(12), "n"(13), "n"(14), "n"(15));
 }
 
 // One wave eliminates row panel P (16 rows from r0 = 16 P) of [S | T]: the
@@ -544,7 +622,7 @@ __device__ __forceinline__ bool factor_panel(Tile& S, Tile& T, int P) {
     }
 #pragma unroll
     for (int i = 0; i < 16; ++i) a[i] = tcol < r0 ? a[i] : (tcol - r0 == i ? 1.0 : 0.0);
-    panel_pivots<0>(d, a);
+    panel_pivots(d, a, rsqrt_nr(row_bcast<0>(d[0])));
     if (lane < 16) {
         double* dw = &S[r0][r0 + lane];
 #pragma unroll
@@ -1046,7 +1124,6 @@ __device__ __forceinline__ void subst_solve(Args& a, Group& g, uint32_t rank, ui
                 for (int j = 0; j < 16; ++j) nx[j] = 0.0;
             }
             double w = take(hw + kk * kTile + 16 * q, c, a.ctrl, g.timeout, min(i - kk, 8u));
-            settle(w);
             dot_bcast(acc, w, t);
 #pragma unroll
             for (int j = 0; j < 16; ++j) t[j] = nx[j];
@@ -1054,7 +1131,6 @@ __device__ __forceinline__ void subst_solve(Args& a, Group& g, uint32_t rank, ui
         part[q * kTile + lane] = acc;
         __syncthreads();
         double r = -(b + ((part[lane] + part[kTile + lane]) + (part[2 * kTile + lane] + part[3 * kTile + lane])));
-        settle(r);
         double w = 0.0;
         dot_bcast(w, r, l);
         w = over_groups(w);
@@ -1112,7 +1188,6 @@ __device__ __forceinline__ void subst_solve(Args& a, Group& g, uint32_t rank, ui
         if ((lane & 3) == 0) part[16 * q + (lane >> 2)] = acc[0];
         __syncthreads();
         double r = part[lane] - ws;  // minus the right-hand side
-        settle(r);
         double bi = 0.0;
         dot_bcast(bi, r, l);
         bi = over_groups(bi);
@@ -1142,23 +1217,32 @@ __device__ __forceinline__ void subst_solve(Args& a, Group& g, uint32_t rank, ui
 constexpr int kSmallNoise = 32, kSmallF = 48, kSmallFail = kSmallF + 16 * 17, kSmallLds = 384;
 static_assert(kSmallFail < kSmallLds, "one-block path LDS layout");
 
-// acc -= (lane C of acc's row of 16 lanes) * y, with the wait states that acc needs
-// since it was written.
+// acc -= (lane C of acc's row of 16 lanes) * y.
 template <int C>
 __device__ __forceinline__ void eliminate(double& acc, double y) {
-    asm("s_nop 1\n\tv_fmac_f64_dpp %0, -%0, %1 row_newbcast:%2 row_mask:0xf bank_mask:0xf"
-        : "+v"(acc)
-        : "v"(y), "n"(C));
+    asm("s_nop 1\n\t" HSP_FMSUB(0, 0, 1, 2) : "+v"(acc) : "v"(y), "n"(C));
 }
 
 // Q = F^T D F, F unit upper triangular, by the pivots of D one after another: d
 // holds Q (column l % 16 in lane l, a copy in each row of 16 lanes), and on return
-// d[i] row i of F right of the diagonal; piv is D's entry l % 16.
+// d[i] row i of F right of the diagonal; piv is D's entry l % 16.  Row I (or rows I
+// and I + 1) of v loses x_I y, x_I being lane I of x's row of 16 lanes.
+template <int I>
+__device__ __forceinline__ void fmsub1(double (&v)[16], double x, double y) {
+    asm("s_nop 1\n\t" HSP_FMSUB(0, 1, 2, 3) : "+v"(v[I]) : "v"(x), "v"(y), "n"(I));
+}
+template <int I>
+__device__ __forceinline__ void fmsub2(double (&v)[16], double x, double y) {
+    asm("s_nop 1\n\t" HSP_FMSUB(0, 2, 3, 4) HSP_FMSUB(1, 2, 3, 5)
+        : "+&v"(v[I]), "+&v"(v[I + 1])
+        : "v"(x), "v"(y), "n"(I), "n"(I + 1));
+}
 template <int C, int I>
 __device__ __forceinline__ void ldl_rows(double (&d)[16], double f) {
     if constexpr (I < 16) {
-        fmsub_bcast<I>(d[I], f, d[C]);
-        ldl_rows<C, I + 1>(d, f);
+        if constexpr (I > C + 1 && I < 15) fmsub2<I>(d, f, d[C]);
+        else fmsub1<I>(d, f, d[C]);
+        ldl_rows<C, I + (I > C + 1 && I < 15 ? 2 : 1)>(d, f);
     }
 }
 template <int C = 0>
@@ -1166,8 +1250,7 @@ __device__ __forceinline__ void ldl_pivots(double (&d)[16], double& piv) {
     if constexpr (C < 16) {
         const int c = threadIdx.x & 15;
         settle(d[C]);
-        double f = d[C] / row_bcast<C>(d[C]);
-        settle(f);
+        const double f = d[C] / row_bcast<C>(d[C]);
         ldl_rows<C, C + 1>(d, f);
         piv = c == C ? d[C] : piv;
         d[C] = c > C ? f : 0.0;
