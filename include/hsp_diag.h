@@ -43,7 +43,7 @@ hsp_status hsp_set_gather(hsp_state* s, int32_t enable);
  * tile tasks that the p-side blocks of the sweep kernel run.  nt =
  * ceil(p / 64) tiles per side, gp blocks; inverse: 1 with the L^-1 tasks,
  * 0 without them (beta then by blocked substitution), -1 with them up to 24
- * tiles (a lone chain also leaves them out below 7 tiles).
+ * tiles (hsp_lone_inverse says what a lone chain of nt tiles does).
  * Task code: type (bits 0-1: 0 factor a diagonal tile, 1 triangular solve of
  * a tile of the block row, 2 tile update, 3 the next diagonal tile's solve,
  * update and factorisation in one block) | part (bit 2: 0 U, 1 L^-1) | step
@@ -57,6 +57,18 @@ hsp_status hsp_set_gather(hsp_state* s, int32_t enable);
  * Test hook for the schedule's coverage and deadlock freedom. */
 hsp_status hsp_tile_schedule(int64_t nt, int64_t gp, int32_t inverse, uint32_t* tasks, int64_t cap,
                              uint32_t* off, int64_t* n_tasks);
+
+/* Without L^-1 (inverse = 0) the shared queue, and with gp = 1 the one list, is
+ * claimed by items: item i is tasks starts[i] .. starts[i + 1] - 1 of
+ * hsp_tile_schedule's, one task, or several updates of one tile, steps k, k + 1,
+ * ..., that a block sums up before it stores the tile.  starts (capacity cap)
+ * receives *n_items + 1 entries (*n_items also when cap is too small, then
+ * HSP_ERANGE).  Errors: HSP_EINVAL as above.  Test hook, host only. */
+hsp_status hsp_tile_runs(int64_t nt, int64_t gp, uint32_t* starts, int64_t cap, int64_t* n_items);
+
+/* Whether a lone chain of nt tiles carries L^-1 along: 1 from 7 to 24 tiles,
+ * else 0 (beta by substitution). */
+int32_t hsp_lone_inverse(int64_t nt);
 
 /* Read ceiling of this GPU for the state's design: the mean milliseconds of
  * one pass of a plain streaming read (16-byte non-temporal loads, nothing

@@ -2487,4 +2487,16 @@ hsp_status hsp_tile_schedule(int64_t nt, int64_t gp, int32_t inverse, uint32_t* 
     return HSP_OK;
 }
 
+hsp_status hsp_tile_runs(int64_t nt, int64_t gp, uint32_t* starts, int64_t cap, int64_t* n_items) {
+    if (nt < 1 || nt > kMaxP / kTile || gp < 1 || gp > 4096 || !n_items) return fail(nullptr, HSP_EINVAL, "bad arguments");
+    std::vector<uint32_t> t, o, r;
+    chol_schedule((uint32_t)nt, (uint32_t)gp, &t, &o, false, &r);
+    *n_items = (int64_t)r.size() - 1;
+    if ((int64_t)r.size() > cap || !starts) return fail(nullptr, HSP_ERANGE, "run buffer too small");
+    std::copy(r.begin(), r.end(), starts);
+    return HSP_OK;
+}
+
+int32_t hsp_lone_inverse(int64_t nt) { return nt >= 1 && nt <= kMaxP / kTile && chain_inverse((uint32_t)nt) ? 1 : 0; }
+
 }  // extern "C"

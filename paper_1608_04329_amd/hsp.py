@@ -31,7 +31,8 @@ EXPORTS = ["hsp_default_options", "hsp_max_p", "hsp_gram", "hsp_gram_noalloc", "
            "hsp_batch_chain", "hsp_batch_sweep", "hsp_batch_sync", "hsp_batch_set_timing",
            "hsp_batch_get_timing", "hsp_batch_last_error", "hsp_batch_destroy", "hsp_get_plan",
            "hsp_sort_rows", "hsp_batch_get_plan", "hsp_tune_key", "hsp_tune_cache_put", "hsp_tune_cache_get",
-           "hsp_batch_set_shape", "hsp_set_gather", "hsp_tune_candidate"]
+           "hsp_batch_set_shape", "hsp_set_gather", "hsp_tune_candidate",
+           "hsp_tile_runs", "hsp_lone_inverse"]
 
 
 class hsp_options(C.Structure):
@@ -96,6 +97,9 @@ def load():
     L.hsp_set_gather.argtypes = [vp, i32]; L.hsp_set_gather.restype = st
     L.hsp_tile_schedule.argtypes = [i64, i64, i32, vp, i64, vp, C.POINTER(i64)]
     L.hsp_tile_schedule.restype = st
+    L.hsp_tile_runs.argtypes = [i64, i64, vp, i64, C.POINTER(i64)]
+    L.hsp_tile_runs.restype = st
+    L.hsp_lone_inverse.argtypes = [i64]; L.hsp_lone_inverse.restype = i32
     L.hsp_read_ceiling.argtypes = [vp, i32, C.POINTER(d), C.POINTER(d)]
     L.hsp_read_ceiling.restype = st
     L.hsp_batch_create.argtypes = [C.POINTER(hsp_dataset), i32, C.POINTER(i32), C.POINTER(hsp_options),
@@ -252,7 +256,8 @@ def hsp_tile_schedule(nt, gp, inverse=None):
 
     One list for a group of one block; otherwise block 0's chain list and the
     shared queue of the other blocks.  inverse: with the L^-1 tasks (True),
-    without (False), or as a lone chain of nt tiles has it (None)."""
+    without (False), or with them up to 24 tiles (None); hsp_lone_inverse(nt)
+    is what a lone chain of nt tiles does."""
     inv = -1 if inverse is None else int(bool(inverse))
     n = C.c_int64()
     st = load().hsp_tile_schedule(nt, gp, inv, None, 0, None, C.byref(n))
@@ -262,6 +267,22 @@ def hsp_tile_schedule(nt, gp, inverse=None):
     off = np.zeros(3, np.uint32)
     _check(load().hsp_tile_schedule(nt, gp, inv, _hp(tasks), tasks.size, _hp(off), C.byref(n)))
     return tasks[: n.value], off[: 2 if gp == 1 else 3]
+
+
+def hsp_tile_runs(nt, gp):
+    """Starts of the claimed items in hsp_tile_schedule(nt, gp, False)'s tasks, and the end."""
+    n = C.c_int64()
+    st = load().hsp_tile_runs(nt, gp, None, 0, C.byref(n))
+    if st not in (HSP_OK, HSP_ERANGE):
+        _check(st)
+    starts = np.zeros(n.value + 1, np.uint32)
+    _check(load().hsp_tile_runs(nt, gp, _hp(starts), starts.size, C.byref(n)))
+    return starts
+
+
+def hsp_lone_inverse(nt):
+    """Whether a lone chain of nt tiles carries L^-1 along."""
+    return bool(load().hsp_lone_inverse(nt))
 
 
 def hsp_read_ceiling(h, iters=10):
