@@ -66,6 +66,13 @@ hsp_status hsp_tile_schedule(int64_t nt, int64_t gp, int32_t inverse, uint32_t* 
  * HSP_ERANGE).  Errors: HSP_EINVAL as above.  Test hook, host only. */
 hsp_status hsp_tile_runs(int64_t nt, int64_t gp, uint32_t* starts, int64_t cap, int64_t* n_items);
 
+/* X^T X: places first .. first + count - 1 of the launch list into which the n[0 ..
+ * 3] items of the four classes of tiles are merged, as the blocks of the launch
+ * find them: class and item of each.  HSP_ERANGE if a place has no item or two.
+ * Errors: HSP_EINVAL (NULL pointers, n outside [0, 2^24), places past the list's
+ * end).  Test hook, host only. */
+hsp_status hsp_gram_items(const int64_t* n, int64_t first, int64_t count, int32_t* cls, int64_t* item);
+
 /* Whether a lone chain of nt tiles carries L^-1 along: 1 from 7 to 24 tiles,
  * else 0 (beta by substitution). */
 int32_t hsp_lone_inverse(int64_t nt);

@@ -2497,6 +2497,24 @@ hsp_status hsp_tile_runs(int64_t nt, int64_t gp, uint32_t* starts, int64_t cap, 
     return HSP_OK;
 }
 
+hsp_status hsp_gram_items(const int64_t* n, int64_t first, int64_t count, int32_t* cls, int64_t* item) {
+    if (!n || first < 0 || count < 0 || !cls || !item) return fail(nullptr, HSP_EINVAL, "bad arguments");
+    uint64_t m[kGramClasses], sum = 0;
+    for (uint32_t k = 0; k < kGramClasses; ++k) {
+        if (n[k] < 0 || n[k] >= (int64_t(1) << 24)) return fail(nullptr, HSP_EINVAL, "bad arguments");
+        sum += m[k] = (uint64_t)n[k];
+    }
+    if ((uint64_t)first + (uint64_t)count > sum) return fail(nullptr, HSP_EINVAL, "bad arguments");
+    for (int64_t i = 0; i < count; ++i) {
+        uint32_t c = 0;
+        uint64_t j = 0;
+        if (!gram_item_host(m, (uint32_t)(first + i), &c, &j)) return fail(nullptr, HSP_ERANGE, "no item has this place");
+        cls[i] = (int32_t)c;
+        item[i] = (int64_t)j;
+    }
+    return HSP_OK;
+}
+
 int32_t hsp_lone_inverse(int64_t nt) { return nt >= 1 && nt <= kMaxP / kTile && chain_inverse((uint32_t)nt) ? 1 : 0; }
 
 }  // extern "C"

@@ -160,9 +160,22 @@ __device__ __forceinline__ void pair_of(uint32_t cls, uint32_t idx, uint32_t nt,
 // Item w of a launch's (split, pair) list.  The classes have different numbers of
 // splits; their items are merged by where in the rows they start, (i + 1/2) / n of
 // a class's n items, ties to the lower class.  Sixteen lanes try the items of a
-// class around the expected one, each counting the items ahead of its own; the
-// lane whose count is w knows its class and item (each w has one: merging is a
-// bijection, and the expected item is at most three off).
+// class around the expected one (gram_guess), each counting the items ahead of its
+// own (gram_rank); the lane whose count is w knows its class and item (each w has
+// one: merging is a bijection, and the expected item is at most three off).
+__host__ __device__ __forceinline__ int64_t gram_guess(uint64_t own, uint64_t sum, uint32_t w) {
+    return (int64_t)((2ull * w + 1ull) * own / (2ull * sum));
+}
+__host__ __device__ __forceinline__ uint64_t gram_rank(const uint64_t (&n)[kGramClasses], uint64_t own, uint32_t c, uint64_t j) {
+    uint64_t rank = j;
+#pragma unroll
+    for (int k = 0; k < kGramClasses; ++k)
+        if ((uint32_t)k != c && n[k] > 0) {
+            const uint64_t at = (2ull * j + 1ull) * n[k];
+            rank += (((uint32_t)k < c ? at : at - 1ull) / own + 1ull) / 2ull;
+        }
+    return rank;
+}
 __device__ __forceinline__ void gram_item(const GramGeometry& g, const GramPart& part, uint32_t w, uint32_t& cls,
                                           uint32_t& item) {
     const uint32_t lane = threadIdx.x & 63u, c = lane >> 4;
@@ -173,17 +186,9 @@ __device__ __forceinline__ void gram_item(const GramGeometry& g, const GramPart&
         sum += n[k];
         if (c == (uint32_t)k) own = n[k];
     }
-    const int64_t j = (int64_t)((2ull * w + 1ull) * own / (2ull * sum)) + (int64_t)(lane & 15u) - 8;
-    uint64_t rank = (uint64_t)j;
+    const int64_t j = gram_guess(own, sum, w) + (int64_t)(lane & 15u) - 8;
     const bool in = j >= 0 && j < (int64_t)own;
-    if (in) {
-#pragma unroll
-        for (int k = 0; k < kGramClasses; ++k)
-            if ((uint32_t)k != c && n[k] > 0) {
-                const uint64_t at = (2ull * (uint64_t)j + 1ull) * n[k];
-                rank += (((uint32_t)k < c ? at : at - 1ull) / own + 1ull) / 2ull;
-            }
-    }
+    const uint64_t rank = in ? gram_rank(n, own, c, (uint64_t)j) : 0ull;
     const int who = __builtin_ctzll(__ballot(in && rank == w));
     cls = (uint32_t)who >> 4;
     item = (uint32_t)__builtin_amdgcn_readlane((int)j, who);
@@ -493,6 +498,20 @@ GramGeometry gram_geometry(const XLayout& x, int num_cus) {
         }
     }
     return best;
+}
+
+bool gram_item_host(const uint64_t (&n)[kGramClasses], uint32_t w, uint32_t* cls, uint64_t* item) {
+    uint64_t sum = 0;
+    for (uint64_t v : n) sum += v;
+    int found = 0;
+    for (uint32_t c = 0; c < kGramClasses; ++c)
+        for (int64_t j = gram_guess(n[c], sum, w) - 8, e = j + 16; j < e; ++j)
+            if (j >= 0 && j < (int64_t)n[c] && gram_rank(n, n[c], c, (uint64_t)j) == w) {
+                *cls = c;
+                *item = (uint64_t)j;
+                ++found;
+            }
+    return found == 1;
 }
 
 size_t gram_work_doubles(const GramGeometry& g) {

@@ -364,6 +364,9 @@ hipError_t gram_chunk_launch(const XLayout& chunk, const GramGeometry& g, uint64
                              double* work, hipStream_t st);
 hipError_t gram_reduce_launch(const double* work, const GramGeometry& g, uint32_t p, const int32_t* e, double* G,
                               hipStream_t st);
+// Place w of the merged list of n[class] items each, as a block finds it: its class
+// and item.  False unless exactly one item has that place.
+bool gram_item_host(const uint64_t (&n)[kGramClasses], uint32_t w, uint32_t* cls, uint64_t* item);
 // Doubles of workspace that hold every partial tile at once.
 size_t gram_work_doubles(const GramGeometry& g);
 // G with a workspace of work_doubles doubles: the pairs are processed in parts

@@ -32,7 +32,7 @@ EXPORTS = ["hsp_default_options", "hsp_max_p", "hsp_gram", "hsp_gram_noalloc", "
            "hsp_batch_get_timing", "hsp_batch_last_error", "hsp_batch_destroy", "hsp_get_plan",
            "hsp_sort_rows", "hsp_batch_get_plan", "hsp_tune_key", "hsp_tune_cache_put", "hsp_tune_cache_get",
            "hsp_batch_set_shape", "hsp_set_gather", "hsp_tune_candidate",
-           "hsp_tile_runs", "hsp_lone_inverse"]
+           "hsp_tile_runs", "hsp_lone_inverse", "hsp_gram_items"]
 
 
 class hsp_options(C.Structure):
@@ -99,6 +99,7 @@ def load():
     L.hsp_tile_schedule.restype = st
     L.hsp_tile_runs.argtypes = [i64, i64, vp, i64, C.POINTER(i64)]
     L.hsp_tile_runs.restype = st
+    L.hsp_gram_items.argtypes = [vp, i64, i64, vp, vp]; L.hsp_gram_items.restype = st
     L.hsp_lone_inverse.argtypes = [i64]; L.hsp_lone_inverse.restype = i32
     L.hsp_read_ceiling.argtypes = [vp, i32, C.POINTER(d), C.POINTER(d)]
     L.hsp_read_ceiling.restype = st
@@ -278,6 +279,14 @@ def hsp_tile_runs(nt, gp):
     starts = np.zeros(n.value + 1, np.uint32)
     _check(load().hsp_tile_runs(nt, gp, _hp(starts), starts.size, C.byref(n)))
     return starts
+
+
+def hsp_gram_items(n, first, count):
+    """(class, item) at places first .. of the merged list of n[0 .. 3] items of X^T X."""
+    n = np.ascontiguousarray(n, np.int64)
+    cls, item = np.zeros(count, np.int32), np.zeros(count, np.int64)
+    _check(load().hsp_gram_items(_hp(n), first, count, _hp(cls), _hp(item)))
+    return cls, item
 
 
 def hsp_lone_inverse(nt):
