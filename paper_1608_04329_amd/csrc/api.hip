@@ -1009,7 +1009,7 @@ hsp_status hsp_create(const float* X, const uint8_t* y, int64_t N, int64_t p,
     return HSP_OK;
 }
 
-// ---- batches: many chains, one graph launch per sweep ------------------------------
+// ---- batches: many chains, a few launches per sweep --------------------------------
 }  // extern "C"
 
 // Chains that share one launch of the sweep kernel: each has its own p-side

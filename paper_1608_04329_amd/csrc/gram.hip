@@ -1,6 +1,7 @@
 // One-time work at creation: the column scales of X, X packed into the
 // library layout, input validation, and G = X^T X in float64 (Section 5,
-// beta step i).  Also the device Philox test hook and the read-ceiling probe.
+// beta step i).  Also small kernels outside the sweep: the sorting of rows, the
+// gathering of a few draws, the device Philox test hook and the read-ceiling probe.
 #include <mutex>
 #include <type_traits>
 

@@ -75,8 +75,7 @@ constexpr uint32_t kZStaticPctDefault = 40;
 constexpr uint32_t kZUnitDefault = 8;
 constexpr uint32_t kZUnitMax = 64;
 // LDS of one sweep-kernel block: two 64 x 66 float64 tiles (67,584 bytes; rows
-// 16-byte aligned).  The same buffer holds the z pass's reduction segment and
-// the packed Q of the one-block path (p (p + 1) / 2 <= 8256 doubles).
+// 16-byte aligned).  The same buffer holds the z pass's reduction segment.
 constexpr int kTileLd = kTile + 2;
 constexpr int kLdsDoubles = 2 * kTile * kTileLd;
 

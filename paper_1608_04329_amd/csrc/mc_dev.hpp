@@ -338,7 +338,7 @@ __device__ void mc_role(McView& m, uint32_t rank, double* lds) {
 // 64 columns of one chain per block, a quarter of the partials per wave with
 // sixteen loads in flight (sums on the grid are exact in any order), and the
 // unit counter back to zero.  As the tail of the pass itself (the last block of
-// each group of 16 summing that group's 2 MB) it took ~250 us of the 776 us pass
+// each group of 16 summing that group's 2 MB) it took ~320 us of the 776 us pass
 // at N = 2.5e5, p = 1000, 16 chains; spread over the device it takes ~10.
 __device__ __forceinline__ void mc_sum_role(McView& m, double* lds) {
     const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6, c = blockIdx.y, ld = m.x.ld;

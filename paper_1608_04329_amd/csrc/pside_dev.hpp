@@ -14,13 +14,15 @@
 // beta for p <= 16 (one block): Q in the registers of one wave, factored while the
 // z pass runs, then two triangular solves on 16 lanes.
 //
-// beta for p > 16 (gp blocks, 64 x 64 tiles): a right-looking blocked
-// Cholesky that applies the same row operations to an identity block, so it
-// produces U and L^-1 = U^-T together (the factorisation of [Q | I]).  Then
-//   y = L^-1 b + s,   beta = L^-T y = U^-1 U^-T b + U^-1 s,
-// which is mean Q^-1 b plus noise with covariance U^-1 U^-T = Q^-1: the same
-// draw as the substitutions, as two parallel triangular products that run
-// after the z pass.
+// beta for p > 16 (gp blocks, 64 x 64 tiles): a right-looking blocked Cholesky,
+// and after the z pass either of two ways to
+//   y = U^-T b + s,   beta = U^-1 y = U^-1 U^-T b + U^-1 s,
+// mean Q^-1 b plus noise with covariance U^-1 U^-T = Q^-1.  From 7 to 24 tiles
+// (p = 385 .. 1536) the factorisation applies its row operations to an identity
+// block as well, so it produces U and L^-1 = U^-T together ([Q | I]), and y and
+// beta are two parallel triangular products.  With fewer or more tiles, and for
+// the chains of a multi-chain pass, it forms the diagonal tiles of L^-1 only, and
+// y and beta come from blocked substitution (subst_solve).
 //
 // Group barriers use a monotonic device counter; every wait is bounded in
 // time and sets kErrTimeout instead of hanging.

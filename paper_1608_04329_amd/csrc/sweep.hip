@@ -166,7 +166,8 @@ uint32_t max_group(const XLayout& x, int capacity) {
         // Without L^-1 the updates run at ~4.2 us a task and block, and block 0's
         // chain at ~17 us a step: more than tasks / (2 nt) blocks would only wait for
         // the chain.  The pass over X keeps its share of the time, which is the
-        // chain's or that of all the work on all blocks, and a sixteenth.  us per sweep at 128 / 192 / 256 / 320 / 384 / 448 / 480 blocks:
+        // chain's or that of all the work on all blocks, and a sixteenth.  us per sweep
+        // at 128 / 192 / 256 / 320 / 384 / 448 / 480 blocks:
         // p = 2000, N = 2e4 float32 525 / 528 / 536 / - / 576 (96: 522, 64: 607);
         // p = 3000, N = 1e4 float32 902 / 783 / 796 / - / 891; p = 4096, N = 2e5
         // float32 1870 / 1448 / 1390 / 1503 / 1589 / 2097; p = 7003, N = 6e4 bfloat16

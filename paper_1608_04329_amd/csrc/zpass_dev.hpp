@@ -5,8 +5,9 @@
 // Rows are full-conditionally independent (Eq. 8), so every row is drawn in
 // parallel.  A wave owns a tile of R consecutive rows held in registers: each
 // lane loads 16-byte vectors of every row (coalesced across the wave), the
-// wave reduces the R dot products, its lanes draw the R truncated normals, and the same registers then feed x_i^T z_i.  X is read from HBM
-// exactly once per sweep; eta and z never touch memory.
+// wave reduces the R dot products, its lanes draw the R truncated normals, and
+// the same registers then feed x_i^T z_i.  X is read from HBM exactly once per
+// sweep; eta and z never touch memory.
 //
 // Truncated normal, divergence-free: with y* = 2y - 1 and mu* = y* eta the
 // draw is t ~ N(mu*, 1) restricted to t > 0 and z = y* t (the y* trick of
