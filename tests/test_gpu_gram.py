@@ -56,18 +56,19 @@ def test_gram_of_row_chunks(xt, N, p, rows):
     assert np.array_equal(G[0], G[1])
 
 
-def test_gram_of_very_many_columns():
-    """More tiles than one launch of the sum can take (p > 46208): one row, so that
-    every entry is one product, exact in float64."""
+@pytest.mark.parametrize("N", [1, 1030])
+def test_gram_of_very_many_columns(N):
+    """More tiles than one launch of the sum can take (p > 46208; 64- and 128-wide
+    ones): small whole numbers, so that every sum is exact."""
     torch, hsp = need_gpu()
     p = 46300
-    x = torch.randn(1, p, generator=torch.Generator(device="cuda").manual_seed(1), device="cuda")
+    x = torch.randint(-3, 4, (N, p), generator=torch.Generator(device="cuda").manual_seed(1), device="cuda").float()
     G = torch.full((p, p), float("nan"), dtype=torch.float64, device="cuda")
     torch.cuda.synchronize()
-    hsp.hsp_gram(x.data_ptr(), hsp.HSP_X_F32, 1, p, p, G.data_ptr())
-    d = x[0].double()
+    hsp.hsp_gram(x.data_ptr(), hsp.HSP_X_F32, N, p, p, G.data_ptr())
+    d = x.double()
     for i in range(0, p, 4096):
-        assert torch.equal(G[i:i + 4096], d[i:i + 4096, None] * d[None, :])
+        assert torch.equal(G[i:i + 4096], d[:, i:i + 4096].t().contiguous() @ d)
     del G
     torch.cuda.empty_cache()
 
